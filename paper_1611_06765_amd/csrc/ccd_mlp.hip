@@ -49,51 +49,107 @@ __global__ void __launch_bounds__(256) k_mlp_fwd(const float* __restrict__ P, co
 }
 
 // ---- loss and gradient ----------------------------------------------------------
-// One block takes kEPB amplitudes of the batch in chunks of 8 (32 rows = 8
-// amplitudes x 4 swap variants).  Wave w = (rt, ch): row tile rt = w / 2
-// (amplitudes 4 rt .. 4 rt + 3 of the chunk) and column half ch = w % 2 of the
-// 128 x 128 layer.  Per chunk:
+// A block takes chunks of kCh = 16 amplitudes (64 rows = 16 amplitudes x 4 swap
+// variants) of the batch, `nc` chunks in a row.  Wave w = (rt, ch): row tile
+// rt = w / 2 (amplitudes 4 rt .. 4 rt + 3 of the chunk) and column half ch =
+// w % 2 of the 128 x 128 layer.  Per chunk:
 //   h1 = relu(W1 x + b1)                      (VALU, into LDS)
 //   z2 = h1 W2^T + b2, g = W3 relu(z2)        (MFMA, W2 in LDS)
 //   y = sum_k sign_k g_k / 4, dL/dg_k = sign_k (y - y*) / (4 M)
 //   dz2 = dg W3 relu'(z2)                     (into LDS)
-//   dW2 += dz2^T h1                            (MFMA, 16 tiles per wave held in registers)
-//   dh1 = dz2 W2, dz1 = dh1 relu'(z1)         (MFMA; z1 recomputed)
+//   dW2 += dz2^T h1                            (MFMA 32x32x2, two tiles per wave held in registers)
+//   dh1 = dz2 W2, dz1 = dh1 relu'(z1)         (MFMA; relu'(z1) = [h1 > 0])
 //   dW1 += dz1^T x, db1 += sum dz1, db2 += sum dz2, dW3 += dg^T relu(z2)
 // The block's sums go to its row of the partial-gradient buffer.
-constexpr int kEPB = 64;   // amplitudes per block
+//
+// Bound by the FP32 MFMA rate: 6.3 MFLOP per chunk, 11 us of one compute unit at
+// the measured 141 TFLOP/s of all 256.  W2, h1 and dz2 take 137 KB of LDS, one
+// block per compute unit, so a batch is cut into at most kMaxBlk = 256 blocks and
+// a block loops over chunks only past 4096 amplitudes; eight waves (two per SIMD)
+// cover each other's LDS reads.  Batch 4096: 110 us in 64 blocks of eight serial
+// 32-row chunks, 30 us in 256 blocks of one 64-row chunk; what is left beside the
+// products is staging W2, the gathered features and 18 MB of partial rows.
+constexpr int kCh = 16;        // amplitudes per chunk
+constexpr int kMaxBlk = 256;   // partial-gradient rows: one block per compute unit
+constexpr int kGradThreads = 512;
 constexpr int kLdH = kW + 4;
 
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // the parameters need no more than float alignment
+// D = A B + C for 32x32x2 FP32 tiles: lane l supplies A[l % 32][l / 32] and
+// B[l / 32][l % 32] and receives D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32]
+__device__ __forceinline__ f16v mfma_f32_32(float a, float b, f16v c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
 __host__ __device__ constexpr size_t grad_lds_bytes() {
-    return lds_bytes<false>() + (size_t)2 * 32 * kLdH * 4 + (size_t)(8 * kPack + 8 + 8 + 2 * 32) * 4;
+    return (size_t)(kW * kLd32 + 2 * 4 * kCh * kLdH + kCh * kPack + 2 * kCh + 2 * 4 * kCh) * 4;
 }
 
 // Indices of `order` outside [0, n_rows) are skipped (the amplitude counts as
 // absent) and counted in *bad.
-__global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, const float* __restrict__ feat,
-                                                  const float* __restrict__ target, const int32_t* __restrict__ order,
-                                                  int64_t base, int64_t n, int64_t n_rows, float inv_m,
-                                                  float* __restrict__ work, float* __restrict__ work_loss,
-                                                  int32_t* __restrict__ bad) {
+__global__ void __launch_bounds__(kGradThreads) k_mlp_grad(
+    const float* __restrict__ P, const float* __restrict__ feat, const float* __restrict__ target,
+    const int32_t* __restrict__ order, int64_t base, int64_t n, int64_t n_rows, int nc, float inv_m,
+    float* __restrict__ work, float* __restrict__ work_loss, int32_t* __restrict__ bad) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const Lds s = lds_carve<false>(lds);
-    float* H1 = (float*)(lds + lds_bytes<false>());  // [32][kLdH]
-    float* DZ2 = H1 + 32 * kLdH;                     // [32][kLdH]
-    float* Fs = DZ2 + 32 * kLdH;                     // [8][8]
-    float* Ys = Fs + 8 * kPack;                      // [8]
-    float* Vs = Ys + 8;                              // [8] 1 = amplitude present
-    float* Gs = Vs + 8;                              // [2][32]
-    const float* W2 = (const float*)s.W2;
-    lds_load<false>(P, s, threadIdx.x, 256);
+    float* W2 = (float*)lds;                 // [128][kLd32]
+    float* H1 = W2 + kW * kLd32;             // [64][kLdH]
+    float* DZ2 = H1 + 4 * kCh * kLdH;        // [64][kLdH]
+    float* Fs = DZ2 + 4 * kCh * kLdH;        // [16][8]
+    float* Ys = Fs + kCh * kPack;            // [16]
+    float* Vs = Ys + kCh;                    // [16] 1 = amplitude present
+    float* Gs = Vs + kCh;                    // [2][64]
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, rt = w >> 1, ch = w & 1;
     const int r16 = lane & 15, kq = lane >> 4;
-    const int64_t e0 = (int64_t)blockIdx.x * kEPB;
-    const int ne = (int)std::min<int64_t>(kEPB, n - e0);
+    const int64_t e0 = (int64_t)blockIdx.x * nc * kCh;
+    const int64_t e1 = std::min<int64_t>(n, e0 + (int64_t)nc * kCh);
 
-    f4v aW2[16];
+    // feature q of amplitude el of the chunk at e (threads 0 .. 127), loaded one
+    // chunk ahead; q = 0 also carries the target and the presence flag
+    float nf = 0.f, ny = 0.f, nv = 0.f;
+    auto fetch = [&](int64_t e) {
+        if (tid < kCh * kPack) {
+            const int el = tid >> 3, q = tid & 7;
+            const int64_t li = e + el;
+            int64_t gi = li < e1 ? (order ? (int64_t)order[base + li] : base + li) : -1;
+            if (li < e1 && (gi < 0 || gi >= n_rows)) {
+                if (q == 0) atomicAdd(bad, 1);
+                gi = -1;
+            }
+            const bool ok = gi >= 0;
+            nf = ok ? feat[gi * kPack + q] : 0.f;
+            nv = ok ? 1.f : 0.f;
+            ny = ok && q == 0 ? target[gi] : 0.f;
+        }
+    };
+    fetch(e0);
+    // W2 is on its way while the first chunk's layer 1 runs
+    constexpr int kW2Per = kW * kW / (4 * kGradThreads);
+    f4v w2r[kW2Per];
 #pragma unroll
-    for (int t = 0; t < 16; t++) aW2[t] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < kW2Per; k++) w2r[k] = *(const f4u*)&P[OFF_W2 + 4 * (tid + kGradThreads * k)];
+    // layer-1 weights of unit tid % 128, and b2 / W3 of this lane's four columns
+    const int c1 = tid & 127;
+    float w1[7];
+#pragma unroll
+    for (int q = 0; q < 7; q++) w1[q] = P[OFF_W1 + c1 * kPack + q];
+    const float b1 = P[OFF_B1 + c1];
+    float b2[4], w3[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const int col = (ch * 4 + j) * 16 + r16;
+        b2[j] = P[OFF_B2 + col];
+        w3[j] = P[OFF_W3 + col];
+    }
+
+    // dW2 tiles: rows 32 (w / 2), columns 32 (2 (w % 2) + u), u = 0, 1
+    f16v aW2[2];
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) aW2[u][i] = 0.f;
     float aW3[4] = {0.f, 0.f, 0.f, 0.f}, aB2[4] = {0.f, 0.f, 0.f, 0.f}, aB1[4] = {0.f, 0.f, 0.f, 0.f};
     float aW1[4][7];
 #pragma unroll
@@ -102,31 +158,32 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
         for (int q = 0; q < 7; q++) aW1[j][q] = 0.f;
     float loss = 0.f;
 
-    for (int cb = 0; cb * 8 < ne; cb++) {
-        __syncthreads();  // previous chunk done with Fs, H1, DZ2, Gs (and W2 staged)
-        if (tid < 8 * kPack) {
-            const int el = tid >> 3, q = tid & 7;
-            const int64_t li = e0 + cb * 8 + el;
-            int64_t gi = li < n ? (order ? (int64_t)order[base + li] : base + li) : -1;
-            if (li < n && (gi < 0 || gi >= n_rows)) {
-                if (q == 0) atomicAdd(bad, 1);
-                gi = -1;
-            }
-            const bool ok = gi >= 0;
-            Fs[el * kPack + q] = ok ? feat[gi * kPack + q] : 0.f;
-            if (q == 0) {
-                Ys[el] = ok ? target[gi] : 0.f;
-                Vs[el] = ok ? 1.f : 0.f;
-            }
+    for (int64_t e = e0; e < e1; e += kCh) {
+        __syncthreads();  // previous chunk done with Fs, H1, DZ2, Gs
+        if (tid < kCh * kPack) {
+            Fs[tid] = nf;
+            if ((tid & 7) == 0) { Ys[tid >> 3] = ny; Vs[tid >> 3] = nv; }
         }
         __syncthreads();
-        // layer 1 into LDS: unit c, rows r = (tid >> 7) + 2 m
+        if (e + kCh < e1) fetch(e + kCh);
+        // layer 1 into LDS: unit c1, rows tid / 128 + 4 m (variant tid / 128 of amplitude m)
         {
-            const int c = tid & 127;
-            for (int r = tid >> 7; r < 32; r += 2) {
+            const int k = tid >> 7;
+#pragma unroll 4
+            for (int el = 0; el < kCh; el++) {
                 float x[7];
-                variant_inputs(&Fs[(r >> 2) * kPack], r & 3, x);
-                H1[r * kLdH + c] = act(layer1(s.W1, s.b1, c, x));
+                variant_inputs(&Fs[el * kPack], k, x);
+                float z = b1;
+#pragma unroll
+                for (int q = 0; q < 7; q++) z += w1[q] * x[q];
+                H1[(4 * el + k) * kLdH + c1] = act(z);
+            }
+        }
+        if (e == e0) {
+#pragma unroll
+            for (int k = 0; k < kW2Per; k++) {
+                const int q = 4 * (tid + kGradThreads * k);
+                *(f4v*)&W2[(q >> 7) * kLd32 + (q & 127)] = w2r[k];
             }
         }
         __syncthreads();
@@ -134,6 +191,7 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
         f4v z2[4];
 #pragma unroll
         for (int j = 0; j < 4; j++) z2[j] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
         for (int st = 0; st < 32; st++) {
             const float a = H1[(rt * 16 + r16) * kLdH + 4 * st + kq];
 #pragma unroll
@@ -142,28 +200,25 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
         }
         float gp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const int col = (ch * 4 + j) * 16 + r16;
-            const float b2 = s.b2[col], w3 = s.W3[col];
+        for (int j = 0; j < 4; j++)
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                z2[j][i] += b2;
-                gp[i] += act(z2[j][i]) * w3;
+                z2[j][i] += b2[j];
+                gp[i] += act(z2[j][i]) * w3[j];
             }
-        }
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
             for (int o = 1; o < 16; o <<= 1) gp[i] += __shfl_xor(gp[i], o);
         if (r16 == 0)
 #pragma unroll
-            for (int i = 0; i < 4; i++) Gs[ch * 32 + rt * 16 + 4 * kq + i] = gp[i];
+            for (int i = 0; i < 4; i++) Gs[ch * 4 * kCh + rt * 16 + 4 * kq + i] = gp[i];
         __syncthreads();
         // residual of amplitude el = 4 rt + kq; dL/dg of its four rows
         const int el = rt * 4 + kq;
         float g[4];
 #pragma unroll
-        for (int i = 0; i < 4; i++) g[i] = Gs[4 * el + i] + Gs[32 + 4 * el + i];
+        for (int i = 0; i < 4; i++) g[i] = Gs[4 * el + i] + Gs[4 * kCh + 4 * el + i];
         const float yp = 0.25f * ((g[0] - g[1]) - (g[2] - g[3]));
         const float res = Vs[el] != 0.f ? yp - Ys[el] : 0.f;
         if (ch == 0 && r16 == 0) loss += 0.5f * res * res * inv_m;
@@ -174,33 +229,32 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             const int col = (ch * 4 + j) * 16 + r16;
-            const float w3 = s.W3[col];
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                const float dz = dg[i] * w3 * dact(z2[j][i]);
+                const float dz = dg[i] * w3[j] * dact(z2[j][i]);
                 aW3[j] += dg[i] * act(z2[j][i]);
                 aB2[j] += dz;
                 DZ2[(rt * 16 + 4 * kq + i) * kLdH + col] = dz;
             }
         }
         __syncthreads();
-        // dW2 += dz2^T h1: wave w owns output rows (units) n-tiles 2w, 2w+1, all k-tiles
-        for (int st = 0; st < 8; st++) {
-            const int r = 4 * st + kq;
-            float av[2], bv[8];
+        // dW2 += dz2^T h1 over the chunk's 64 rows
+        {
+            const int r32 = lane & 31, kh = lane >> 5;
+#pragma unroll 8
+            for (int st = 0; st < 2 * kCh; st++) {
+                const int r = 2 * st + kh;
+                const float av = DZ2[r * kLdH + 32 * rt + r32];
 #pragma unroll
-            for (int u = 0; u < 2; u++) av[u] = DZ2[r * kLdH + (2 * w + u) * 16 + r16];
-#pragma unroll
-            for (int kt = 0; kt < 8; kt++) bv[kt] = H1[r * kLdH + kt * 16 + r16];
-#pragma unroll
-            for (int u = 0; u < 2; u++)
-#pragma unroll
-                for (int kt = 0; kt < 8; kt++) aW2[u * 8 + kt] = mfma_f32(av[u], bv[kt], aW2[u * 8 + kt]);
+                for (int u = 0; u < 2; u++)
+                    aW2[u] = mfma_f32_32(av, H1[r * kLdH + 32 * (2 * ch + u) + r32], aW2[u]);
+            }
         }
         // dh1 = dz2 W2 for rows of tile rt, k-tiles ch*4 .. ch*4+3
         f4v dh[4];
 #pragma unroll
         for (int j = 0; j < 4; j++) dh[j] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
         for (int st = 0; st < 32; st++) {
             const float a = DZ2[(rt * 16 + r16) * kLdH + 4 * st + kq];
 #pragma unroll
@@ -216,7 +270,7 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
             const int c = (ch * 4 + j) * 16 + r16;
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                const float dz1 = dh[j][i] * dact(layer1(s.W1, s.b1, c, xv[i]));
+                const float dz1 = dh[j][i] * dact(H1[(4 * el + i) * kLdH + c]);
                 aB1[j] += dz1;
 #pragma unroll
                 for (int q = 0; q < 7; q++) aW1[j][q] += dz1 * xv[i][q];
@@ -237,13 +291,14 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
             for (int q = 0; q < 7; q++) aW1[j][q] += __shfl_xor(aW1[j][q], o);
         }
     }
-    // waves rt = 1 hand their column sums to the waves rt = 0 of the same half
+    // the waves of row tiles 1 .. 3 hand their column sums to row tile 0's of
+    // the same half, which adds them in tile order
     __syncthreads();
-    float* X = H1;  // [2 halves][4][16][10] scratch
-    if (rt == 1 && kq == 0) {
+    float* X = H1;  // [3 row tiles][128 columns][10] scratch
+    if (rt > 0 && kq == 0) {
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            float* q = X + ((ch * 4 + j) * 16 + r16) * 10;
+            float* q = X + ((rt - 1) * kW + (ch * 4 + j) * 16 + r16) * 10;
             q[0] = aW3[j]; q[1] = aB2[j]; q[2] = aB1[j];
 #pragma unroll
             for (int f = 0; f < 7; f++) q[3 + f] = aW1[j][f];
@@ -254,58 +309,84 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ P, c
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             const int col = (ch * 4 + j) * 16 + r16;
-            const float* q = X + col * 10;
-            out[OFF_W3 + col] = aW3[j] + q[0];
-            out[OFF_B2 + col] = aB2[j] + q[1];
-            out[OFF_B1 + col] = aB1[j] + q[2];
+            float v[10] = {aW3[j], aB2[j], aB1[j]};
 #pragma unroll
-            for (int f = 0; f < 7; f++) out[OFF_W1 + col * kPack + f] = aW1[j][f] + q[3 + f];
+            for (int f = 0; f < 7; f++) v[3 + f] = aW1[j][f];
+            for (int t = 0; t < 3; t++)
+#pragma unroll
+                for (int f = 0; f < 10; f++) v[f] += X[(t * kW + col) * 10 + f];
+            out[OFF_W3 + col] = v[0];
+            out[OFF_B2 + col] = v[1];
+            out[OFF_B1 + col] = v[2];
+#pragma unroll
+            for (int f = 0; f < 7; f++) out[OFF_W1 + col * kPack + f] = v[3 + f];
             out[OFF_W1 + col * kPack + 7] = 0.f;
         }
     }
-    // dW2 tiles of this wave: rows n = (2w+u)*16 + 4 kq + i, columns k = kt*16 + r16
 #pragma unroll
     for (int u = 0; u < 2; u++)
 #pragma unroll
-        for (int kt = 0; kt < 8; kt++)
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                out[OFF_W2 + ((2 * w + u) * 16 + 4 * kq + i) * kW + kt * 16 + r16] = aW2[u * 8 + kt][i];
+        for (int i = 0; i < 16; i++)
+            out[OFF_W2 + (32 * rt + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3)) * kW + 32 * (2 * ch + u) + (lane & 31)] =
+                aW2[u][i];
     // b3 cancels in the antisymmetrised output; padding stays zero
     if (tid < kParams - OFF_B3) out[OFF_B3 + tid] = 0.f;
     // loss: lanes r16 == 0 of waves ch == 0 hold it
     loss += __shfl_xor(loss, 16);
     loss += __shfl_xor(loss, 32);
-    __syncthreads();
     if (ch == 0 && lane == 0) Gs[rt] = loss;
     __syncthreads();
-    if (tid == 0) work_loss[blockIdx.x] = Gs[0] + Gs[1];
+    if (tid == 0) work_loss[blockIdx.x] = (Gs[0] + Gs[1]) + (Gs[2] + Gs[3]);
 }
 
-// sum of the block partials (fixed order); mode 0 writes the gradient, mode 1
-// applies one Adam step.  Block 0 adds the batch loss to acc[0].
+// sum of the block partials (fixed order: four quarters of the rows, each in
+// row order, then the quarters in order); mode 0 writes the gradient, mode 1
+// applies one Adam step.  A block owns 64 parameters, one wave per quarter with
+// 16 row loads in flight (256 rows, 18 MB: 5.7 us; one thread per parameter over
+// 64 rows took 18 us, a serial chain of loads); the last block adds the batch loss
+// to acc[0].
+constexpr int kRedParams = 64, kRedBlocks = (kParams + kRedParams - 1) / kRedParams + 1;
 __global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ work, const float* __restrict__ work_loss,
                                                     int nblk, int mode, float* __restrict__ grad, float* __restrict__ P,
                                                     float* __restrict__ m, float* __restrict__ v, float lr, float b1,
                                                     float b2, float eps, float bc1, float bc2, double* acc) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p < kParams) {
-        float g = 0.f;
-        for (int b = 0; b < nblk; b++) g += work[(size_t)b * kParams + p];
-        if (mode == 0) {
-            grad[p] = g;
-        } else {
-            const float mn = b1 * m[p] + (1.f - b1) * g;
-            const float vn = b2 * v[p] + (1.f - b2) * g * g;
-            m[p] = mn;
-            v[p] = vn;
-            P[p] -= lr * (mn / bc1) / (sqrtf(vn / bc2) + eps);
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (w > 0) return;
         double l = 0.0;
-        for (int b = 0; b < nblk; b++) l += (double)work_loss[b];
-        acc[0] += l;
+        for (int b = lane; b < nblk; b += 64) l += (double)work_loss[b];
+        for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+        if (lane == 0) acc[0] += l;
+        return;
+    }
+    __shared__ float sh[4][kRedParams];
+    const int p = blockIdx.x * kRedParams + lane;
+    const int per = (nblk + 3) / 4, lo = w * per, hi = min(nblk, lo + per);
+    float g = 0.f;
+    if (p < kParams) {
+        const float* q = work + p;
+        int b = lo;
+        for (; b + 16 <= hi; b += 16) {
+            float x[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = q[(size_t)(b + k) * kParams];
+#pragma unroll
+            for (int k = 0; k < 16; k++) g += x[k];
+        }
+        for (; b < hi; b++) g += q[(size_t)b * kParams];
+    }
+    sh[w][lane] = g;
+    __syncthreads();
+    if (w > 0 || p >= kParams) return;
+    g = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
+    if (mode == 0) {
+        grad[p] = g;
+    } else {
+        const float mn = b1 * m[p] + (1.f - b1) * g;
+        const float vn = b2 * v[p] + (1.f - b2) * g * g;
+        m[p] = mn;
+        v[p] = vn;
+        P[p] -= lr * (mn / bc1) / (sqrtf(vn / bc2) + eps);
     }
 }
 
@@ -321,17 +402,35 @@ struct Work {
     int32_t* bad;   // count of out-of-range indices
 };
 
-size_t work_bytes_for(int64_t n) {
-    const int64_t nblk = std::max<int64_t>(1, (n + kEPB - 1) / kEPB);
-    return (size_t)nblk * kParams * 4 + (size_t)((nblk + 63) / 64) * 256 + 256;
+// A work area holds one partial-gradient row per block: at most kMaxBlk, one per
+// chunk of a small batch.  (The size grows with n, so an area made for n serves
+// every smaller batch.)
+size_t bytes_of_rows(int64_t rows) {
+    return (size_t)rows * kParams * 4 + (size_t)((rows + 63) / 64) * 256 + 256;
+}
+int64_t rows_for(int64_t n) { return std::max<int64_t>(1, std::min<int64_t>(kMaxBlk, (n + kCh - 1) / kCh)); }
+size_t work_bytes_for(int64_t n) { return bytes_of_rows(rows_for(n)); }
+
+// The blocks of a batch of n and the chunks of each.  An area of only one row
+// per 64 amplitudes is taken too, with fewer blocks.
+struct Split {
+    int nblk, nc;
+};
+Split split_for(int64_t n, size_t bytes) {
+    int64_t rows = rows_for(n);
+    if (bytes < bytes_of_rows(rows)) rows = std::max<int64_t>(1, std::min(rows, (n + 63) / 64));
+    const int64_t nch = (n + kCh - 1) / kCh, nc = (nch + rows - 1) / rows;
+    return {(int)((nch + nc - 1) / nc), (int)nc};
+}
+bool work_fits(int64_t n, size_t bytes) {
+    return bytes >= work_bytes_for(n) || bytes >= bytes_of_rows(std::max<int64_t>(1, (n + 63) / 64));
 }
 
-Work carve(void* w, int64_t n) {
-    const int64_t nblk = std::max<int64_t>(1, (n + kEPB - 1) / kEPB);
+Work carve(void* w, int rows) {
     Work k;
     k.part = (float*)w;
-    k.loss = k.part + (size_t)nblk * kParams;
-    k.acc = (double*)((char*)w + work_bytes_for(n) - 256);
+    k.loss = k.part + (size_t)rows * kParams;
+    k.acc = (double*)((char*)w + bytes_of_rows(rows) - 256);
     k.bad = (int32_t*)(k.acc + 1);
     return k;
 }
@@ -394,19 +493,19 @@ ccd_status ccd_mlp_loss_grad(const float* params, const float* feat, const float
         ccd::set_error("ccd_mlp_loss_grad: NULL argument or n < 1");
         return CCD_EINVAL;
     }
-    if (work_bytes < work_bytes_for(n) || !aligned(work, 256)) {
+    if (!work_fits(n, work_bytes) || !aligned(work, 256)) {
         ccd::set_error("ccd_mlp_loss_grad: work buffer too small or not 256-byte aligned");
         return CCD_EINVAL;
     }
     ccd_status s = grad_attrs();
     if (s != CCD_OK) return s;
-    const Work k = carve(work, n);
-    const int nblk = (int)((n + kEPB - 1) / kEPB);
+    const Split sp = split_for(n, work_bytes);
+    const Work k = carve(work, sp.nblk);
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(k_mlp_zero, dim3(1), dim3(1), 0, st, k.acc, k.bad);
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nblk), dim3(256), grad_lds_bytes(), st, params, feat, target,
-                       (const int32_t*)nullptr, (int64_t)0, n, n, 1.0f / (float)n, k.part, k.loss, k.bad);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 255) / 256), dim3(256), 0, st, k.part, k.loss, nblk, 0, grad,
+    hipLaunchKernelGGL(k_mlp_grad, dim3(sp.nblk), dim3(kGradThreads), grad_lds_bytes(), st, params, feat, target,
+                       (const int32_t*)nullptr, (int64_t)0, n, n, sp.nc, 1.0f / (float)n, k.part, k.loss, k.bad);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3(kRedBlocks), dim3(256), 0, st, k.part, k.loss, sp.nblk, 0, grad,
                        (float*)nullptr, (float*)nullptr, (float*)nullptr, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f, k.acc);
     MLP_TRY(hipGetLastError());
     if (loss) {
@@ -428,14 +527,14 @@ ccd_status ccd_mlp_train(float* params, float* adam_m, float* adam_v, int64_t* s
         ccd::set_error("ccd_mlp_train: need 1 <= batch <= n_order, lr > 0, 0 <= beta < 1, eps > 0, step >= 0");
         return CCD_EINVAL;
     }
-    if (work_bytes < work_bytes_for(o->batch) || !aligned(work, 256)) {
+    if (!work_fits(o->batch, work_bytes) || !aligned(work, 256)) {
         ccd::set_error("ccd_mlp_train: work buffer smaller than ccd_mlp_work_size(batch) or misaligned");
         return CCD_EINVAL;
     }
     ccd_status s = grad_attrs();
     if (s != CCD_OK) return s;
-    const Work k = carve(work, o->batch);
-    const int nblk = (int)((o->batch + kEPB - 1) / kEPB);
+    const Split sp = split_for(o->batch, work_bytes);
+    const Work k = carve(work, sp.nblk);
     const int64_t nsteps = n_order / o->batch;
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(k_mlp_zero, dim3(1), dim3(1), 0, st, k.acc, k.bad);
@@ -443,9 +542,9 @@ ccd_status ccd_mlp_train(float* params, float* adam_m, float* adam_v, int64_t* s
         const int64_t t = *step + 1;
         const float bc1 = (float)(1.0 - std::pow((double)o->beta1, (double)t));
         const float bc2 = (float)(1.0 - std::pow((double)o->beta2, (double)t));
-        hipLaunchKernelGGL(k_mlp_grad, dim3(nblk), dim3(256), grad_lds_bytes(), st, params, feat, target, order,
-                           q * o->batch, (int64_t)o->batch, n_rows, 1.0f / (float)o->batch, k.part, k.loss, k.bad);
-        hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 255) / 256), dim3(256), 0, st, k.part, k.loss, nblk, 1,
+        hipLaunchKernelGGL(k_mlp_grad, dim3(sp.nblk), dim3(kGradThreads), grad_lds_bytes(), st, params, feat, target, order,
+                           q * o->batch, (int64_t)o->batch, n_rows, sp.nc, 1.0f / (float)o->batch, k.part, k.loss, k.bad);
+        hipLaunchKernelGGL(k_mlp_reduce, dim3(kRedBlocks), dim3(256), 0, st, k.part, k.loss, sp.nblk, 1,
                            (float*)nullptr, params, adam_m, adam_v, o->lr, o->beta1, o->beta2, o->eps, bc1, bc2,
                            k.acc);
         MLP_TRY(hipGetLastError());

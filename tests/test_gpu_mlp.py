@@ -221,3 +221,41 @@ def test_training_rejects_out_of_range_indices():
         ccd.mlp_train(P, st, F, Y, order, n, 1e-3)
     assert e.value.status == ccd.CCD_EINVAL and "outside" in str(e.value)
     assert st.step.value == 1 and not torch.equal(P, p0)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 65, 4096, 4097, 8193])
+@pytest.mark.parametrize("area", ["asked for", "one row per 64 amplitudes"])
+def test_gradient_at_chunk_and_block_edges(n, area):
+    """Batches at the edges of a chunk (16 amplitudes), of one chunk per block
+    (4096) and of several chunks per block, in the work area the library asks
+    for and in one of a row per 64 amplitudes (fewer blocks, more chunks each).
+    FP32 sums of 128 products and of 4 n rows: 1e-4 of the gradient's norm."""
+    import ctypes as C
+    torch = _torch()
+    from oracle import mlp_oracle as M
+    from paper_1611_06765_amd import inputs
+    p = _params(seed=9, scale=1.5)
+    F = _rand_feats(n, seed=4)
+    Y = np.random.default_rng(5).normal(0, 0.2, n).astype(np.float32)
+    P, f, y = _dev(p), _dev(F), _dev(Y)
+    nb = C.c_size_t()
+    assert ccd._lib.ccd_mlp_work_size(n, C.byref(nb)) == 0
+    rows64 = (n + 63) // 64
+    small = rows64 * inputs.N_PARAM * 4 + (rows64 + 63) // 64 * 256 + 256
+    size = nb.value if area == "asked for" else min(nb.value, small)
+    work = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+    ptr = (work.data_ptr() + 255) & ~255
+    g = torch.empty(inputs.N_PARAM, dtype=torch.float32, device="cuda")
+    loss = C.c_double()
+    st = ccd._lib.ccd_mlp_loss_grad(P.data_ptr(), f.data_ptr(), y.data_ptr(), n, g.data_ptr(), C.byref(loss), ptr,
+                                    size, torch.cuda.current_stream().cuda_stream)
+    assert st == ccd.CCD_OK
+    L, G = M.loss_and_grad(inputs.mlp_unflatten(p), F.astype(np.float64), Y.astype(np.float64))
+    gw = inputs.mlp_flatten({k: np.asarray(v) for k, v in G.items()}).astype(np.float64)
+    gw[inputs.OFF_B3] = 0.0
+    assert loss.value == pytest.approx(L, rel=1e-5, abs=1e-9)
+    g = g.cpu().numpy()
+    for lo, hi in [(inputs.OFF_W1, inputs.OFF_B1), (inputs.OFF_B1, inputs.OFF_W2), (inputs.OFF_W2, inputs.OFF_B2),
+                   (inputs.OFF_B2, inputs.OFF_W3), (inputs.OFF_W3, inputs.OFF_B3)]:
+        assert np.linalg.norm(g[lo:hi] - gw[lo:hi]) <= 1e-4 * np.linalg.norm(gw[lo:hi]), (lo, hi)
+    assert np.all(g[inputs.OFF_B3:] == 0.0)
