@@ -197,7 +197,9 @@ ccd_status ccd_iterate(ccd_ctx* ctx, const ccd_solver_opts* opts, int32_t* sweep
  * keeps a candidate only if it beats the current one by 2%; best_ms
  * (nullable, CCD_TUNE_LEN entries) receives each slot's best time per pass.
  * It recomputes the sweep's intermediates from the current amplitudes but does
- * not advance the iteration.  A fresh context has all slots 0. */
+ * not advance the iteration.  A fresh context has all slots 0, with which a
+ * sweep runs as three launches on the context's stream; any other table runs
+ * the families as launches of their own, the rings on forked streams. */
 #define CCD_TUNE_DIRECT      0
 #define CCD_TUNE_DCHI        1
 #define CCD_TUNE_RING_SMALL  2
@@ -333,8 +335,8 @@ ccd_status ccd_export_tables(const ccd_ctx* ctx, int32_t problem, double* tkin, 
                              double* w_table);
 
 /* Per-kernel GPU timing with HIP events recorded on the context's stream.
- * While enabled every launch is bracketed by two events and the sweep runs on
- * the context's stream alone (no forked streams), so the times do not overlap;
+ * While enabled every family is a launch of its own, bracketed by two events,
+ * and the sweep runs on the context's stream alone, so the times do not overlap;
  * ccd_kernel_times returns, per kernel family, the summed milliseconds and
  * launch counts since the last reset.  Families (ccd_kernel_name, in order):
  * init, direct (the chi_klij product items), dsum (their column sums), dchi

@@ -19,7 +19,12 @@
 //   k_update  every amplitude: <ab||ij> + ladder sums + ring slots + one-body
 //             terms, t_new = R / eps_ij^ab, linear mixing, energy partial sums
 //   k_energy  deterministic per-problem energy and convergence flag (inside a
-//             run of sweeps: the last blocks of the next sweep's k_direct)
+//             run of sweeps: the last blocks of the next sweep's first launch)
+// With the default launch shapes a sweep is three launches on the caller's
+// stream: k_front (product items, every ring item, the energy step), k_ladder with
+// the one-body items beside it (chi_klij added from the product items' parts where
+// it is used), and k_update (one-body sums per row and column inline).  The
+// launches one by one remain for kernel timing and for chosen launch shapes.
 // Problems with the same (N, nmax2, twist) form a group that shares the integer
 // tables (states, pair lists, position maps, work lists); the sweep kernels'
 // work items are (item, problem) pairs over them, and the work lists are cut
@@ -115,6 +120,7 @@ struct DevPtrs {
     const int32_t* phmap;
     const int32_t* csr_ptr;
     const int32_t* csr_idx;
+    const int32_t* cinfo;    // per S_z = 0 column: offset of its first part among the column parts; n_hh | parts << 16
     const int32_t* zs;       // per pair-block position: ring slot << 1 | sign, or -1 (shared by a group)
     const double* rowE;      // per particle-pair row: eps_a + eps_b (per problem)
     const double* colE;      // per hole-pair column: eps_i + eps_j (per problem)
@@ -195,17 +201,30 @@ __device__ __forceinline__ double vas_q(const double* __restrict__ lut, double w
     return f > 0 ? w : -w;
 }
 
+// A descriptor that is the same in every lane, moved to scalar registers: a
+// kernel that loops over work items and stores in between cannot load it there
+// by itself, and then carries every field and address in vector registers.
+template <typename T>
+__device__ __forceinline__ T uni(const T& v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    struct Words { int32_t w[sizeof(T) / 4]; };
+    Words x = __builtin_bit_cast(Words, v);
+#pragma unroll
+    for (size_t k = 0; k < sizeof(T) / 4; k++) x.w[k] = __builtin_amdgcn_readfirstlane(x.w[k]);
+    return __builtin_bit_cast(T, x);
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
 
-// deterministic sum over a 256-thread block; result valid in thread 0
+// deterministic sum over the first 256 threads of a block; result valid in thread 0
 __device__ __forceinline__ double block_sum256(double v, double* sh) {
     v = wave_sum(v);
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     __syncthreads();
-    if (lane == 0) sh[w] = v;
+    if (lane == 0 && w < 4) sh[w] = v;
     __syncthreads();
     double r = 0.0;
     if (threadIdx.x == 0) r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
@@ -416,7 +435,8 @@ __device__ __forceinline__ void energy_of(const DevPtrs& d, int p, double tol, d
     const int g = d.pgi[p], n = G.elem_hi - G.elem_lo;
     const double* part = d.epart_elem + G.eelem_base + g * n;
     double s = 0.0;
-    for (int x = threadIdx.x; x < n; x += 256) s += part[x];
+    if (threadIdx.x < 256)
+        for (int x = threadIdx.x; x < n; x += 256) s += part[x];
     double e = block_sum256(s, sh);
     if (threadIdx.x == 0 && d.active[p]) {
         double old = d.ecorr[p];
@@ -443,61 +463,196 @@ __device__ __forceinline__ void energy_of(const DevPtrs& d, int p, double tol, d
 
 // per (item of kDirSplit particle-pair rows of an S_z = 0 channel, problem):
 // row sums of t v, the item's part of 1/2 sum_cd <kl||cd> t_ij^cd on MFMA over
-// LDS-staged chunks of rows (FP64 in LDS, converted at the MFMA in the mixed
-// modes), and its part of the column sums (the diagonal of that product in
-// FP64; summed from the staged chunk in the mixed modes).  Both operands are
-// amplitude-shaped blocks ([n_pp][n_hh] rows of <ab||ij> and t).  The staging
-// row stride follows the channel's tiles, so narrow channels stage more rows
-// per barrier.  With at most four 16x16 output tiles (n_hh <= 32) every wave
-// computes all tiles over every fourth 4-row K step of a chunk and the four
-// partial tiles are added in LDS in wave order; with more tiles wave w owns
-// tiles w, w+4, ...  k_dsum adds the items' parts in item order.
-constexpr int kDirBuf = 2048;  // doubles per staged operand
-template <int P>
-__global__ void __launch_bounds__(256) k_direct(DevPtrs d, int cur, uint32_t mask, int n_items, int nd, int energy,
-                                                double tol, double tol_rel, int rule) {
-    using E = double;
-    using AT = typename std::conditional<P == P_F64, d4, f4>::type;
-    constexpr int PM = P == P_F64 ? P_F64 : P_F32;   // contraction precision used here
-    __shared__ __attribute__((aligned(16))) E vs[kDirBuf];
-    __shared__ __attribute__((aligned(16))) E ts[kDirBuf];
-    __shared__ AT red[3][64];  // partial tiles of waves 1..3
-    __shared__ int live_s;
-    // blocks nd .. nd + P - 1 (energy set): the previous sweep's energy step,
-    // one problem each; it only reads the previous update's partial sums
-    if (energy && (int)blockIdx.x >= nd) {
-        energy_of(d, blockIdx.x - nd, tol, tol_rel, rule, vs);
-        return;
+// LDS-staged chunks of rows, and its part of the column sums (the diagonal of
+// that product in FP64; summed from the staged chunk in the mixed modes).  Both
+// operands are amplitude-shaped blocks ([n_pp][n_hh] rows of <ab||ij> and t).
+// k_dsum adds the items' parts in item order.
+struct DirItem {
+    const double* t;
+    const double* vt;
+    double* rows;   // row sums of the channel
+    double* part;   // the item's part of chi_klij, [n_hh][n_hh]
+    double* colp;   // and of the column sums, [n_hh]
+    int nhh, k0, k1;
+};
+__device__ __forceinline__ DirItem dir_item(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int cur,
+                                            int sub, int start) {
+    DirItem r;
+    const int64_t E0 = G.t_base + g * G.n_amp + c.t_off;
+    const int si = sub - c.dsub_lo;
+    r.t = d.t[cur] + E0;
+    r.vt = d.vt + E0;
+    r.rows = d.rowsum + G.rows_base + g * G.n_rows + c.row_off;
+    r.part = d.dpart + G.dpart_base + (int64_t)g * G.n_dpart + c.dpart_off + (int64_t)si * c.nhh * c.nhh;
+    r.colp = d.dcolp + G.dcolp_base + (int64_t)g * G.n_dcolp + c.dcolp_off + (int64_t)si * c.nhh;
+    r.nhh = c.nhh;
+    r.k0 = start;
+    r.k1 = min(c.npp, start + kDirSplit);
+    return r;
+}
+
+// FP64, eight waves.  A chunk of whole rows (all 256 of an item where n_hh <= 16)
+// is one contiguous run of memory, at most 8 doubles of each operand per thread,
+// loaded one chunk ahead of the work and kept in LDS as it is, with row stride
+// n_hh: a product tile that reads past a row's end gets the next row's numbers,
+// which reach only outputs outside the block.  With at most four 16x16 output
+// tiles (n_hh <= 32) every wave computes all tiles over every eighth 4-row K step;
+// with more, wave w takes tiles w / 2, w / 2 + 4, ... over every second step.  The
+// partial tiles are added in LDS in wave order.  The item is a chain of loads,
+// barriers and short MFMA runs, so it is bound by latency: few and large chunks,
+// eight waves and four threads per row sum shorten that chain.
+constexpr int kDirThreads = 512;
+constexpr int kDirChunk = 4096;                      // doubles of a staged chunk
+constexpr int kDirBuf64 = kDirChunk + 64;            // and the last tile's overhang
+constexpr size_t kDirLds = 2 * (size_t)kDirBuf64 * 8;
+__device__ __forceinline__ void direct64(const DirItem& it, uint32_t mask, double* lds) {
+    double* vs = lds;
+    double* ts = lds + kDirBuf64;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int nhh = it.nhh, nt = (nhh + 15) >> 4, ntt = nt * nt;
+    const int crows = min(kDirSplit, (kDirChunk / nhh) & ~3);  // rows per staged chunk
+    const bool quad = (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0;
+    const bool split = ntt <= 4;
+    constexpr int kPer = kDirChunk / kDirThreads;
+    double vr[kPer] = {}, tr[kPer] = {};
+    auto load_chunk = [&](int r0) {
+        const int ne = min(crows, it.k1 - r0) * nhh;
+        const double* vp = it.vt + (int64_t)r0 * nhh;
+        const double* tp = it.t + (int64_t)r0 * nhh;
+#pragma unroll
+        for (int i = 0; i < kPer; i++)
+            if (kDirThreads * i < ne) {
+                const int e = min(tid + kDirThreads * i, ne - 1);
+                vr[i] = vp[e];
+                tr[i] = tp[e];
+            }
+    };
+    load_chunk(it.k0);
+    d4 acc[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) acc[k] = d4{0, 0, 0, 0};
+    for (int r0 = it.k0; r0 < it.k1; r0 += crows) {
+        const int rc = min(crows, it.k1 - r0), rpad = (rc + 3) & ~3, ne = rc * nhh;
+        __syncthreads();  // the previous chunk's (or item's) reads are done
+#pragma unroll
+        for (int i = 0; i < kPer; i++)
+            if (kDirThreads * i < rpad * nhh) {  // zero in the rows up to the K step
+                const int e = tid + kDirThreads * i;
+                vs[e] = e < ne ? vr[i] : 0.0;
+                ts[e] = e < ne ? tr[i] : 0.0;
+            }
+        __syncthreads();
+        if (r0 + crows < it.k1) load_chunk(r0 + crows);
+        // row sums of t v (one-body particle terms): four threads per row
+        if (mask & CCD_T_QPART) {
+            for (int x = tid; x < 4 * rc; x += kDirThreads) {
+                const int o = (x >> 2) * nhh;
+                double sum = 0.0;
+#pragma unroll 2
+                for (int j = x & 3; j < nhh; j += 4) sum += ts[o + j] * vs[o + j];
+                sum += __shfl_xor(sum, 1);
+                sum += __shfl_xor(sum, 2);
+                if ((x & 3) == 0) it.rows[r0 + (x >> 2)] = sum;
+            }
+        }
+        if (quad) {
+            const int col = lane & 15, rq = lane >> 4;
+            if (nt == 1) {
+#pragma unroll 2
+                for (int kk = 4 * w; kk < rpad; kk += 32) {
+                    const int o = (kk + rq) * nhh + col;
+                    acc[0] = mfma64(vs[o], ts[o], acc[0]);
+                }
+            } else if (split) {
+#pragma unroll 2
+                for (int kk = 4 * w; kk < rpad; kk += 32) {
+                    const int o = (kk + rq) * nhh + col;
+                    const double a0 = vs[o], b0 = ts[o], a1 = vs[o + 16], b1 = ts[o + 16];
+                    acc[0] = mfma64(a0, b0, acc[0]);
+                    acc[1] = mfma64(a0, b1, acc[1]);
+                    acc[2] = mfma64(a1, b0, acc[2]);
+                    acc[3] = mfma64(a1, b1, acc[3]);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const int tile = (w >> 1) + 4 * k;
+                    if (tile < ntt) {
+                        const double* vp = vs + rq * nhh + col + 16 * (tile / nt);
+                        const double* tp = ts + rq * nhh + col + 16 * (tile % nt);
+#pragma unroll 2
+                        for (int kk = 4 * (w & 1); kk < rpad; kk += 8)
+                            acc[k] = mfma64(vp[kk * nhh], tp[kk * nhh], acc[k]);
+                    }
+                }
+            }
+        }
     }
-    for (int bi = blockIdx.x; bi < n_items; bi += nd) {
-    const Item it = d.it_direct[bi];
-    if (it.chan < 0) continue;
-    const Item sub = d.it_dsub[it.chan];
-    const DevChan c = d.chans[sub.chan];
-    const DevGroup G = d.groups[c.group];
-    const int g = it.start;
-    // the problem's flag, read once for the block: an energy block of this
-    // launch may clear it meanwhile, and waves that read it at different
-    // times would otherwise take different paths through the barriers below
-    __syncthreads();  // the previous item's readers of live_s are done
-    if (threadIdx.x == 0) live_s = d.active[G.p0 + g];
+    if (!quad) return;
+    // add the waves' partial tiles in wave order: eight waves for each of at
+    // most four tiles, or two for each of up to sixteen
+    d4* red = (d4*)lds;  // split: [tile][wave][64], else [tile][64]
+    auto put = [&](const d4& sum, int ti, int tj) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int kl = ti * 16 + orow<P_F64>(lane, q), ij = tj * 16 + (lane & 15);
+            if (kl < nhh && ij < nhh) {
+                it.part[kl * nhh + ij] = sum[q];
+                if (kl == ij) it.colp[kl] = sum[q];
+            }
+        }
+    };
     __syncthreads();
-    if (!live_s) continue;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int nhh = c.nhh, npp = c.npp, nt = (nhh + 15) >> 4, ntt = nt * nt;
+    if (split) {
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (k < ntt) red[(k * 8 + w) * 64 + lane] = acc[k];
+        __syncthreads();
+        if (w < ntt) {
+            const d4* p = red + w * 8 * 64 + lane;
+            d4 sum = p[0];
+#pragma unroll 1
+            for (int q = 1; q < 8; q++) sum += p[q * 64];
+            put(sum, w / nt, w % nt);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int tile = (w >> 1) + 4 * k;
+            if (tile < ntt && (w & 1)) red[tile * 64 + lane] = acc[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int tile = (w >> 1) + 4 * k;
+            if (tile < ntt && !(w & 1)) put(acc[k] + red[tile * 64 + lane], tile / nt, tile % nt);
+        }
+    }
+}
+
+// The mixed modes: FP64 in LDS, converted at the FP32 MFMA, on the first four
+// waves of the block.  The staging row stride follows the channel's tiles, so
+// narrow channels stage more rows per barrier.  With at most four 16x16 output
+// tiles every wave computes all tiles over every fourth 4-row K step of a chunk
+// and the partial tiles are added in LDS in wave order; with more, wave w owns
+// tiles w, w + 4, ...
+constexpr int kDirBuf = 2048;  // doubles per staged operand
+constexpr size_t kDirLdsMixed = 2 * (size_t)kDirBuf * 8 + 3 * 64 * sizeof(f4);
+__device__ __forceinline__ void direct32(const DirItem& it, uint32_t mask, double* lds) {
+    double* vs = lds;
+    double* ts = lds + kDirBuf;
+    f4* red = (f4*)(lds + 2 * kDirBuf);  // partial tiles of waves 1..3, [3][64]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const bool on = w < 4;
+    const int nhh = it.nhh, nt = (nhh + 15) >> 4, ntt = nt * nt;
     const int ld = nt * 16 + 1;                    // staging row stride
     const int crows = (kDirBuf / ld) & ~3;         // rows per staged chunk
-    const int k0 = sub.start, k1 = min(npp, k0 + kDirSplit), si = it.chan - c.dsub_lo;
-    const int64_t E0 = G.t_base + g * G.n_amp + c.t_off;
-    const double* t = d.t[cur] + E0;
-    const double* vt = d.vt + E0;
     const bool quad = (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0;
     const bool split = ntt <= 4;  // waves split K, each holding all tiles
-    double* rows = d.rowsum + G.rows_base + g * G.n_rows + c.row_off;
-    AT acc[4];
+    f4 acc[4];
 #pragma unroll
-    for (int k = 0; k < 4; k++) acc[k] = AT{0, 0, 0, 0};
-    double cpart = 0.0;  // mixed modes: this thread's share of a column sum
+    for (int k = 0; k < 4; k++) acc[k] = f4{0, 0, 0, 0};
+    double cpart = 0.0;  // this thread's share of a column sum
     // a chunk in the padded layout [crows][16 nt]: element e of it is loaded by
     // thread e % 256 into register e / 256 (zero past the chunk and the block),
     // one chunk ahead of the work on the previous one
@@ -505,40 +660,41 @@ __global__ void __launch_bounds__(256) k_direct(DevPtrs d, int cur, uint32_t mas
     const int cw = 16 * nt;
     double vr[kPerD], tr[kPerD];
     auto load_chunk = [&](int r0) {
-        const int rc = min(crows, k1 - r0);
+        const int rc = min(crows, it.k1 - r0);
 #pragma unroll
         for (int i = 0; i < kPerD; i++) {
-            const int e = threadIdx.x + 256 * i, r = e / cw, j = e - r * cw;
-            const bool ok = r < rc && j < nhh;
-            vr[i] = ok ? vt[(int64_t)(r0 + r) * nhh + j] : 0.0;
-            tr[i] = ok ? t[(int64_t)(r0 + r) * nhh + j] : 0.0;
+            const int e = tid + 256 * i, r = e / cw, j = e - r * cw;
+            const bool ok = on && r < rc && j < nhh;
+            vr[i] = ok ? it.vt[(int64_t)(r0 + r) * nhh + j] : 0.0;
+            tr[i] = ok ? it.t[(int64_t)(r0 + r) * nhh + j] : 0.0;
         }
     };
-    load_chunk(k0);
-    for (int r0 = k0; r0 < k1; r0 += crows) {
-        const int rc = min(crows, k1 - r0);
+    load_chunk(it.k0);
+    for (int r0 = it.k0; r0 < it.k1; r0 += crows) {
+        const int rc = min(crows, it.k1 - r0);
         const int rpad = (rc + 3) & ~3;
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kPerD; i++) {
-            const int e = threadIdx.x + 256 * i, r = e / cw, j = e - r * cw;
-            if (r < crows) { vs[r * ld + j] = vr[i]; ts[r * ld + j] = tr[i]; }
+            const int e = tid + 256 * i, r = e / cw, j = e - r * cw;
+            if (on && r < crows) { vs[r * ld + j] = vr[i]; ts[r * ld + j] = tr[i]; }
         }
         __syncthreads();
-        if (r0 + crows < k1) load_chunk(r0 + crows);
+        if (!on) continue;
+        if (r0 + crows < it.k1) load_chunk(r0 + crows);
         // row sums of t v (one-body particle terms), FP64 in every mode
         if (mask & CCD_T_QPART) {
-            for (int r = threadIdx.x; r < rc; r += 256) {
+            for (int r = tid; r < rc; r += 256) {
                 double sum = 0.0;
                 for (int j = 0; j < nhh; j++) sum += ts[r * ld + j] * vs[r * ld + j];
-                rows[r0 + r] = sum;
+                it.rows[r0 + r] = sum;
             }
         }
-        // mixed modes: this thread's share of a column sum, rows phase, phase + 4, ...
-        if constexpr (P != P_F64) {
-            const int j = threadIdx.x & 63;
+        // this thread's share of a column sum, rows phase, phase + 4, ...
+        {
+            const int j = tid & 63;
             if ((mask & CCD_T_QHOLE) && j < nhh)
-                for (int r = threadIdx.x >> 6; r < rc; r += 4) cpart += ts[r * ld + j] * vs[r * ld + j];
+                for (int r = w; r < rc; r += 4) cpart += ts[r * ld + j] * vs[r * ld + j];
         }
         if (quad) {
             const int col = lane & 15;
@@ -548,22 +704,13 @@ __global__ void __launch_bounds__(256) k_direct(DevPtrs d, int cur, uint32_t mas
                     // second column tile (nt = 2); with nt = 1 the same in-range
                     // column is read and not used
                     const int c1 = nt > 1 ? 16 + col : col;
-                    const E a0 = vs[r * ld + col], b0 = ts[r * ld + col];
-                    const E a1 = vs[r * ld + c1], b1 = ts[r * ld + c1];
-                    if constexpr (P == P_F64) {
-                        acc[0] = mfma64(a0, b0, acc[0]);
-                        if (nt > 1) {
-                            acc[1] = mfma64(a0, b1, acc[1]);
-                            acc[2] = mfma64(a1, b0, acc[2]);
-                            acc[3] = mfma64(a1, b1, acc[3]);
-                        }
-                    } else {
-                        acc[0] = mfma32((float)a0, (float)b0, acc[0]);
-                        if (nt > 1) {
-                            acc[1] = mfma32((float)a0, (float)b1, acc[1]);
-                            acc[2] = mfma32((float)a1, (float)b0, acc[2]);
-                            acc[3] = mfma32((float)a1, (float)b1, acc[3]);
-                        }
+                    const double a0 = vs[r * ld + col], b0 = ts[r * ld + col];
+                    const double a1 = vs[r * ld + c1], b1 = ts[r * ld + c1];
+                    acc[0] = mfma32((float)a0, (float)b0, acc[0]);
+                    if (nt > 1) {
+                        acc[1] = mfma32((float)a0, (float)b1, acc[1]);
+                        acc[2] = mfma32((float)a1, (float)b0, acc[2]);
+                        acc[3] = mfma32((float)a1, (float)b1, acc[3]);
                     }
                 }
             } else {
@@ -574,26 +721,23 @@ __global__ void __launch_bounds__(256) k_direct(DevPtrs d, int cur, uint32_t mas
                         const int ti = tile / nt, tj = tile - ti * nt;
                         for (int kk = 0; kk < rpad; kk += 4) {
                             const int r = kk + (lane >> 4);
-                            const E av = vs[r * ld + ti * 16 + col];
-                            const E bv = ts[r * ld + tj * 16 + col];
-                            if constexpr (P == P_F64) acc[k] = mfma64(av, bv, acc[k]);
-                            else acc[k] = mfma32((float)av, (float)bv, acc[k]);
+                            const double av = vs[r * ld + ti * 16 + col];
+                            const double bv = ts[r * ld + tj * 16 + col];
+                            acc[k] = mfma32((float)av, (float)bv, acc[k]);
                         }
                     }
                 }
             }
         }
     }
-    double* part = d.dpart + G.dpart_base + (int64_t)g * G.n_dpart + c.dpart_off + (int64_t)si * nhh * nhh;
-    double* colp = d.dcolp + G.dcolp_base + (int64_t)g * G.n_dcolp + c.dcolp_off + (int64_t)si * nhh;
     if (quad) {
         if (split) {
             // add the partial tiles of waves 1..3 to wave 0's, tile by tile, in wave order
             for (int k = 0; k < ntt; k++) {
                 __syncthreads();
-                if (w > 0) red[w - 1][lane] = acc[k];
+                if (w > 0 && on) red[(w - 1) * 64 + lane] = acc[k];
                 __syncthreads();
-                if (w == 0) acc[k] = ((acc[k] + red[0][lane]) + red[1][lane]) + red[2][lane];
+                if (w == 0) acc[k] = ((acc[k] + red[lane]) + red[64 + lane]) + red[128 + lane];
             }
         }
 #pragma unroll
@@ -605,31 +749,61 @@ __global__ void __launch_bounds__(256) k_direct(DevPtrs d, int cur, uint32_t mas
                 if (w != 0 || ti >= nt || tj >= nt) continue;
             } else {
                 const int tile = w + 4 * k;
-                if (tile >= ntt) continue;
+                if (tile >= ntt || !on) continue;
                 ti = tile / nt; tj = tile - ti * nt;
             }
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                int kl = ti * 16 + orow<PM>(lane, q), ij = tj * 16 + (lane & 15);
-                if (kl < nhh && ij < nhh) {
-                    const double qv = (double)acc[k][q];
-                    part[kl * nhh + ij] = qv;
-                    if (P == P_F64 && kl == ij) colp[kl] = qv;
-                }
+                int kl = ti * 16 + orow<P_F32>(lane, q), ij = tj * 16 + (lane & 15);
+                if (kl < nhh && ij < nhh) it.part[kl * nhh + ij] = (double)acc[k][q];
             }
         }
     }
-    if constexpr (P != P_F64) {
-        if (mask & CCD_T_QHOLE) {
-            double* cred = vs;  // 4 x 64 doubles
-            __syncthreads();
-            cred[threadIdx.x] = cpart;
-            __syncthreads();
-            if (threadIdx.x < nhh)
-                colp[threadIdx.x] = (cred[threadIdx.x] + cred[64 + threadIdx.x]) + (cred[128 + threadIdx.x] + cred[192 + threadIdx.x]);
-        }
+    if (mask & CCD_T_QHOLE) {
+        double* cred = vs;  // 4 x 64 doubles
+        __syncthreads();
+        if (on) cred[tid] = cpart;
+        __syncthreads();
+        if (tid < nhh) it.colp[tid] = (cred[tid] + cred[64 + tid]) + (cred[128 + tid] + cred[192 + tid]);
     }
+}
+
+template <int P> __host__ __device__ constexpr size_t dir_lds() { return P == P_F64 ? kDirLds : kDirLdsMixed; }
+template <int P> __host__ __device__ constexpr int dir_threads() { return P == P_F64 ? kDirThreads : 256; }
+
+// one product item of a block; live_s: a word of LDS
+template <int P>
+__device__ __forceinline__ void direct_block(const DevPtrs& d, const Item it0, int cur, uint32_t mask, double* lds,
+                                             int* live_s) {
+    const Item it = uni(it0);
+    if (it.chan < 0) return;
+    const Item sub = uni(d.it_dsub[it.chan]);
+    const DevChan c = uni(d.chans[sub.chan]);
+    const DevGroup G = uni(d.groups[c.group]);
+    // the problem's flag, read once for the block: an energy block of this
+    // launch may clear it meanwhile, and waves that read it at different
+    // times would otherwise take different paths through the barriers below
+    __syncthreads();  // the previous item's readers of live_s are done
+    if (threadIdx.x == 0) *live_s = d.active[G.p0 + it.start];
+    __syncthreads();
+    if (!*live_s) return;
+    const DirItem di = dir_item(d, c, G, it.start, cur, it.chan, sub.start);
+    if constexpr (P == P_F64) direct64(di, mask, lds);
+    else direct32(di, mask, lds);
+}
+
+template <int P>
+__global__ void __launch_bounds__(dir_threads<P>(), P == P_F64 ? 4 : 2) k_direct(DevPtrs d, int cur, uint32_t mask, int n_items, int nd,
+                                                                int energy, double tol, double tol_rel, int rule) {
+    extern __shared__ __attribute__((aligned(16))) double dir_buf[];
+    __shared__ int live_s;
+    // blocks nd .. nd + P - 1 (energy set): the previous sweep's energy step,
+    // one problem each; it only reads the previous update's partial sums
+    if (energy && (int)blockIdx.x >= nd) {
+        energy_of(d, blockIdx.x - nd, tol, tol_rel, rule, dir_buf);
+        return;
     }
+    for (int bi = blockIdx.x; bi < n_items; bi += nd) direct_block<P>(d, d.it_direct[bi], cur, mask, dir_buf, &live_s);
 }
 
 // per (S_z = 0 channel, problem): chi_klij = <kl||ij> + sum of the product
@@ -672,32 +846,43 @@ __global__ void __launch_bounds__(256) k_dsum(DevPtrs d, uint32_t mask, int n_it
 }
 
 // one-body intermediates: one wave per (state, problem); CSR entries x >= 0
-// name a column sum (holes, +), x < 0 the row sum -x-1 (particles, -)
-__global__ void __launch_bounds__(256) k_dchi(DevPtrs d, uint32_t mask, int n_items) {
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
-    const Item it = d.it_dchi[bi];
-    const DevGroup G = d.groups[it.chan];
+// name a column sum (holes, +), x < 0 the row sum -x-1 (particles, -).  PARTS: the
+// column sums are added here from the product items' parts, in item order
+template <bool PARTS>
+__device__ __forceinline__ void dchi_item(const DevPtrs& d, const Item it, uint32_t mask) {
+    const DevGroup& G = d.groups[it.chan];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int s = (it.start & 0xffff) + w, g = it.start >> 16;  // state of this wave, problem
-    if (s >= G.ns) continue;
+    if (s >= G.ns) return;
     const int x0 = d.csr_ptr[G.csr_off + s], x1 = d.csr_ptr[G.csr_off + s + 1];
-    {
-        if (!d.active[G.p0 + g]) continue;
-        const double* rows = d.rowsum + G.rows_base + g * G.n_rows;
-        const double* cols = d.colsum + G.cols_base + g * G.n_cols;
-        double acc = 0.0;
-        for (int x = x0 + lane; x < x1; x += 64) {
-            int idx = d.csr_idx[x];
-            if (idx >= 0) {
-                if (mask & CCD_T_QHOLE) acc += cols[idx];
-            } else {
-                if (mask & CCD_T_QPART) acc -= rows[-idx - 1];
+    if (!d.active[G.p0 + g]) return;
+    const double* rows = d.rowsum + G.rows_base + g * G.n_rows;
+    const double* cols = d.colsum + G.cols_base + g * G.n_cols;
+    double acc = 0.0;
+    for (int x = x0 + lane; x < x1; x += 64) {
+        int idx = d.csr_idx[x];
+        if (idx >= 0) {
+            if (mask & CCD_T_QHOLE) {
+                if constexpr (PARTS) {
+                    const int2 ci = ((const int2*)d.cinfo)[G.cinfo_off + idx];
+                    const double* cp = d.dcolp + G.dcolp_base + (int64_t)g * G.n_dcolp + ci.x;
+                    const int nhh = ci.y & 0xffff, nsub = ci.y >> 16;
+                    double q = 0.0;
+                    for (int k = 0; k < nsub; k++) q += cp[k * nhh];
+                    acc += q;
+                } else {
+                    acc += cols[idx];
+                }
             }
+        } else {
+            if (mask & CCD_T_QPART) acc -= rows[-idx - 1];
         }
-        acc = wave_sum(acc);
-        if (lane == 0) d.dchi[G.eps_base + g * G.ns + s] = acc;
     }
-    }
+    acc = wave_sum(acc);
+    if (lane == 0) d.dchi[G.eps_base + g * G.ns + s] = acc;
+}
+__global__ void __launch_bounds__(256) k_dchi(DevPtrs d, uint32_t mask, int n_items) {
+    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) dchi_item<false>(d, d.it_dchi[bi], mask);
 }
 
 // ring per pair {Q, P = -Q} of cross channels and problem.  With
@@ -766,7 +951,7 @@ __device__ __forceinline__ void pair_stage(const DevPtrs& d, int memQ, int memP,
 // right after it)
 template <int n16, int stride, int J>
 __device__ __forceinline__ void pair_maps(const PairCtx& r, int t0, int32_t* m) {
-    constexpr int tot = n16 * n16;
+    constexpr int tot = n16 * n16;  // n16: rows and columns that hold the block
 #pragma unroll
     for (int j = 0; j < J; j++) {
         const int e = t0 + j * stride, u = e / n16, x = e - u * n16;
@@ -837,11 +1022,15 @@ __device__ __forceinline__ void pair_store(const PairCtx& r, AT acc, const int32
 }
 
 // products of one 16x16 output tile, k from 0 to kmax (a multiple of 4; FP64 /
-// FP32: 16x16x4); operands of four steps are loaded before their MFMAs
-template <int P, typename E, typename AT>
+// FP32: 16x16x4); operands of four steps are loaded before their MFMAs.  Matrices
+// of fewer than n16 rows: rows and columns past the last are read from it instead
+// (they reach only outputs that are not stored).
+template <int P, int rows, typename E, typename AT>
 __device__ __forceinline__ AT mm4(const E* X, const E* Y, int lda, int tx, int ty, int kmax, int lane, AT acc) {
-    const E* xr = X + (tx * 16 + (lane & 15)) * lda + (lane >> 4);
-    const E* yc = Y + (lane >> 4) * lda + ty * 16 + (lane & 15);
+    const int xi = rows % 16 ? min(tx * 16 + (lane & 15), rows - 1) : tx * 16 + (lane & 15);
+    const int yi = rows % 16 ? min(ty * 16 + (lane & 15), rows - 1) : ty * 16 + (lane & 15);
+    const E* xr = X + xi * lda + (lane >> 4);
+    const E* yc = Y + (lane >> 4) * lda + yi;
     int k0 = 0;
     for (; k0 + 16 <= kmax; k0 += 16) {
         E a[4], b[4];
@@ -878,23 +1067,26 @@ __device__ __forceinline__ f4 mmbf(const __bf16* X, const __bf16* Yt, int lda, i
     return acc;
 }
 
-// byte offset of the matrices in a pair item's LDS (after W/2 and member states)
-__host__ __device__ constexpr size_t pair_mat_off() {
-    return ((size_t)kMaxLut * 8 + 4 * (size_t)kMaxPH * 4 + 15) & ~(size_t)15;
+// byte offset of the matrices in a pair item's LDS (after W/2 and the states of
+// at most n16 members of each list)
+__host__ __device__ constexpr size_t pair_mat_off(int n16) {
+    return ((size_t)kMaxLut * 8 + 4 * (size_t)n16 * 4 + 15) & ~(size_t)15;
 }
 
 // One pair item with NW waves, wave w owning output tiles w, w + NW, ...
 // Matrices padded to n16 (K padded to kpad = n16 for 16x16x4, 32-multiple for
-// BF16) with row stride lda.
-template <int P, int N16, int NW>
+// BF16) with row stride lda.  M < N16 (FP64, FP32): only M rows and columns are
+// kept in LDS, M a multiple of 4 and no smaller than either size of the pair.
+template <int P, int N16, int NW, int M = N16>
 __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int cur, uint32_t mask, char* lds,
                                           int tid) {
     using E = typename std::conditional<P == P_F64, double, typename std::conditional<P == P_F32, float, __bf16>::type>::type;
     using AT = typename AccT<P>::T;
     constexpr int n16 = N16, nt = N16 / 16, ntt = nt * nt, TPW = (ntt + NW - 1) / NW;
     constexpr int kpad = P == P_BF16 ? ((N16 + 31) & ~31) : N16;
-    constexpr int lda = P == P_BF16 ? kpad + 8 : N16 + 1;
-    constexpr int rows = P == P_BF16 ? kpad : N16;  // rows allocated per matrix
+    constexpr int lda = P == P_BF16 ? kpad + 8 : M + 1;
+    constexpr int rows = P == P_BF16 ? kpad : M;  // rows allocated per matrix
+    constexpr int nb = P == P_BF16 ? N16 : M;     // rows and columns filled
     PairCtx r;
     r.nq = 0; r.np = 0; r.self = false; r.map = nullptr; r.t = nullptr; r.zc = nullptr; r.zs = nullptr;
     int32_t memQ = 0, memP = 0, lo = 0, nlut = 0;
@@ -903,19 +1095,19 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
     const int lane = tid & 63, w = tid >> 6;
     double* lutS = (double*)lds;
     int32_t* qs = (int32_t*)(lutS + kMaxLut);
-    int32_t* ps = qs + 2 * kMaxPH;
+    int32_t* ps = qs + 2 * N16;
     // FP64 / FP32: A and B (B later holds X, then V_P);
     // BF16: A, At = A^T and Bt = B^T (Bt later holds X, then V_P^T)
-    E* A = (E*)(lds + pair_mat_off());
+    E* A = (E*)(lds + pair_mat_off(N16));
     E* B = A + rows * lda;
     E* At = B;                // BF16 only (same storage as B)
     E* Bt = At + rows * lda;  // BF16 only
     const bool qring = (mask & CCD_T_QRING) != 0, ring = (mask & CCD_T_RING) != 0;
-    constexpr int J = (n16 * n16 + 64 * NW - 1) / (64 * NW);  // entries of A per thread
+    constexpr int J = (nb * nb + 64 * NW - 1) / (64 * NW);  // entries of A per thread
     int32_t mp[J];
 #pragma unroll
     for (int j = 0; j < J; j++) mp[j] = -1;
-    if (live) pair_maps<n16, 64 * NW, J>(r, tid, mp);
+    if (live) pair_maps<nb, 64 * NW, J>(r, tid, mp);
     if (live) {
         pair_stage(d, memQ, memP, lo, nlut, r.nq, r.np, qs, ps, lutS, tid, 64 * NW);
         if constexpr (P == P_BF16) {
@@ -927,7 +1119,7 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
     // W(|Q|^2)/2, the first table entry of every element of the pair (member 0
     // of Q: hole qs[1], particle qs[0])
     const double wq = live ? lutS[dist2(qs[1], qs[0])] : 0.0;
-    if (live) pair_fill<E, n16, lda, 64 * NW, J, P == P_BF16>(r, mp, qs, ps, lutS, wq, A, B, At, Bt, tid, qring);
+    if (live) pair_fill<E, nb, lda, 64 * NW, J, P == P_BF16>(r, mp, qs, ps, lutS, wq, A, B, At, Bt, tid, qring);
     int32_t zsl[TPW][4];
 #pragma unroll
     for (int k = 0; k < TPW; k++) {
@@ -948,7 +1140,7 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
         if (live && qring && tile < ntt) {
             const int tx = tile / nt, ty = tile - tx * nt;
             if constexpr (P == P_BF16) xq[k] = mmbf(A, Bt, lda, tx, ty, kp, lane, xq[k]);
-            else xq[k] = mm4<P>(A, B, lda, tx, ty, kp, lane, xq[k]);
+            else xq[k] = mm4<P, rows>(A, B, lda, tx, ty, kp, lane, xq[k]);
         }
     }
     __syncthreads();  // every wave has finished reading B (Bt)
@@ -964,7 +1156,7 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
                 const int x = tx * 16 + orow<P>(lane, q), y = ty * 16 + (lane & 15);
                 double xv = (double)xq[k][q];
                 if (ring && x < r.nq && y < r.nq) xv += pair_vph(qs, lutS, wq, x, y);
-                XB[x * lda + y] = (E)xv;
+                if (nb == n16 || (x < nb && y < nb)) XB[x * lda + y] = (E)xv;
             }
         }
     }
@@ -978,7 +1170,7 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
         if (live && tile < ntt) {
             const int tu = tile / nt, ty = tile - tu * nt;
             if constexpr (P == P_BF16) acc[k] = mmbf(XB, At, lda, tu, ty, kq, lane, acc[k]);
-            else acc[k] = mm4<P>(XB, A, lda, tu, ty, kq, lane, acc[k]);
+            else acc[k] = mm4<P, rows>(XB, A, lda, tu, ty, kq, lane, acc[k]);
         }
     }
     __syncthreads();  // every wave has finished reading X
@@ -993,7 +1185,7 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
                 const int x = tx * 16 + orow<P>(lane, q), y = ty * 16 + (lane & 15);
                 const double vp = (ring && x < r.np && y < r.np) ? pair_vph(ps, lutS, wq, x, y) : 0.0;
                 if constexpr (P == P_BF16) XB[y * lda + x] = (E)(float)vp;
-                else XB[x * lda + y] = (E)vp;
+                else if (nb == n16 || (x < nb && y < nb)) XB[x * lda + y] = (E)vp;
             }
         }
     }
@@ -1005,19 +1197,20 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
         if (live && tile < ntt) {
             const int tu = tile / nt, ty = tile - tu * nt;
             if constexpr (P == P_BF16) acc[k] = mmbf(A, XB, lda, tu, ty, kp, lane, acc[k]);
-            else acc[k] = mm4<P>(A, XB, lda, tu, ty, kp, lane, acc[k]);
+            else acc[k] = mm4<P, rows>(A, XB, lda, tu, ty, kp, lane, acc[k]);
             pair_store(r, acc[k], zsl[k]);
         }
     }
 }
 
-template <int P> __host__ __device__ constexpr size_t pair_lds(int n16) {
+// n16: the padded order, m: rows and columns kept (FP64, FP32)
+template <int P> __host__ __device__ constexpr size_t pair_lds(int n16, int m = 0) {
     const size_t es = P == P_F64 ? 8 : (P == P_F32 ? 4 : 2);
     const size_t kpad = P == P_BF16 ? ((n16 + 31) & ~31) : n16;
-    const size_t lda = P == P_BF16 ? kpad + 8 : n16 + 1;
-    const size_t rows = P == P_BF16 ? kpad : n16;
+    const size_t lda = P == P_BF16 ? kpad + 8 : (m ? m : n16) + 1;
+    const size_t rows = P == P_BF16 ? kpad : (m ? m : n16);
     const size_t mats = P == P_BF16 ? 3 : 2;
-    return pair_mat_off() + mats * rows * lda * es;
+    return pair_mat_off(n16) + mats * rows * lda * es;
 }
 
 // pairs with n <= 16: one wave per item, four items per block
@@ -1044,6 +1237,80 @@ __global__ void __launch_bounds__(64 * NW) k_ringp(DevPtrs d, int cur, uint32_t 
         __syncthreads();  // the previous item's reads of LDS are done
         pair_body<P, N16, NW>(d, d.it_ring_b[base + bi], cur, mask, dyn_lds, threadIdx.x);
     }
+}
+
+// The first launch of a sweep on one stream: the chi_klij product items, every
+// ring item and the previous sweep's energy step as blocks of one grid, longest
+// items first.  A sweep of few items leaves most of the GPU idle in each of these
+// launches, and forking them over streams costs an event record, a wait and two
+// queue crossings each (about 10 us apiece); side by side in one grid they need
+// none of it.  512 threads: a product item, a pair of order 48 .. 80 on eight
+// waves, two pairs of order 32 on four each, or eight small pairs on one each; 128
+// registers and at most 80 KB of LDS (except for pairs beyond order 68), two
+// blocks per compute unit.  A sweep in us, nine launches over four streams -> three
+// launches on one: N=14, n^2<=4 94 -> 20; N=54, n^2<=36 112 -> 98; N=66, n^2<=20 115
+// -> 67 (five densities 165 -> 140, ten 248 -> 247); N=66, n^2<=36 141 -> 123 (three
+// 288 -> 266).  This launch takes 62 us at N=66, n^2<=36 and 154 us for the ten
+// densities, where the ring's gathers and scattered stores (460 MB) bound it.
+constexpr int kFrontThreads = 512;
+struct Front {
+    int nd;             // blocks of product items
+    int nb[4], lo[4];   // blocks and first item of the ring size buckets 32, 48, 64, 80
+    int n32;            // ring items of order 32
+    int ns, n_small;    // blocks and items of the small pairs
+    int ne;             // blocks of the energy step (0 or the number of problems)
+    int small80;        // the order-80 bucket holds no pair beyond order 68
+};
+constexpr int kRing80M = 68;  // two blocks of LDS matrices of this order fit one compute unit
+template <int P>
+__global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, uint32_t mask, Front f, double tol,
+                                                            double tol_rel, int rule) {
+    extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
+    __shared__ int live_s;
+    int b = blockIdx.x;
+    const int tid = threadIdx.x, w = tid >> 6;
+    if (b < f.nd) {
+        direct_block<P>(d, d.it_direct[b], cur, mask, (double*)dyn_lds, &live_s);
+        return;
+    }
+    b -= f.nd;
+    if (b < f.nb[3]) {
+        const Item it = d.it_ring_b[f.lo[3] + b];
+        if (P != P_BF16 && f.small80) pair_body<P, 80, 8, kRing80M>(d, it, cur, mask, dyn_lds, tid);
+        else pair_body<P, 80, 8>(d, it, cur, mask, dyn_lds, tid);
+        return;
+    }
+    b -= f.nb[3];
+    if (b < f.nb[2]) {
+        pair_body<P, 64, 8>(d, d.it_ring_b[f.lo[2] + b], cur, mask, dyn_lds, tid);
+        return;
+    }
+    b -= f.nb[2];
+    if (b < f.nb[1]) {
+        pair_body<P, 48, 8>(d, d.it_ring_b[f.lo[1] + b], cur, mask, dyn_lds, tid);
+        return;
+    }
+    b -= f.nb[1];
+    if (b < f.nb[0]) {
+        // items 16 (b / 8) + b % 8 and the next of the same XCD's piece
+        const int idx = 16 * (b >> 3) + (b & 7) + 8 * (w >> 2);
+        Item it = d.it_ring_b[f.lo[0] + min(idx, f.n32 - 1)];
+        if (idx >= f.n32) it.chan = -1;
+        pair_body<P, 32, 4>(d, it, cur, mask, dyn_lds + (w >> 2) * ((pair_lds<P>(32) + 15) & ~(size_t)15), tid & 255);
+        return;
+    }
+    b -= f.nb[0];
+    if (b < f.ns) {
+        constexpr size_t per = (pair_lds<P>(16) + 15) & ~(size_t)15;
+        // the four-item units 2 (b / 8) and 2 (b / 8) + 1 of XCD b % 8
+        const int unit = 16 * (b >> 3) + (b & 7) + 8 * (w >> 2), idx = 4 * unit + (w & 3);
+        Item it = d.it_ring_s[min(idx, f.n_small - 1)];
+        if (idx >= f.n_small) it.chan = -1;
+        pair_body<P, 16, 1>(d, it, cur, mask, dyn_lds + w * per, tid & 63);
+        return;
+    }
+    b -= f.ns;
+    if (b < f.ne) energy_of(d, b, tol, tol_rel, rule, (double*)dyn_lds);
 }
 
 // the ring contribution to amplitude e of problem g: its two ring slots
@@ -1091,12 +1358,42 @@ __global__ void __launch_bounds__(256) k_onebody(DevPtrs d) {
 // (|q'|^2 and A2); their delta is zero.  Padding rows carry p' = 0.
 constexpr int kKP = 128;  // momentum pairs staged per barrier
 
+// chi_klij of the item's 16 columns, [k l][16] in LDS: <kl||ij> + the product
+// items' parts in item order, as k_dsum forms it
+__device__ __forceinline__ void chi_slice(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int ct,
+                                          uint32_t mask, double* chiS) {
+    const int nhh = c.nhh, nsub = c.dsub_n;
+    const double* part = d.dpart + G.dpart_base + (int64_t)g * G.n_dpart + c.dpart_off;
+    const double* lut = d.lut + G.lut_base + g * G.nlut;
+    const int32_t* st = d.st + G.st_off;
+    for (int e = threadIdx.x; e < 16 * nhh; e += 256) {
+        const int kl = e >> 4, ij = 16 * ct + (e & 15);
+        if (ij >= nhh) continue;
+        double v = 0.0, q = 0.0;
+        if (mask & CCD_T_QHH)
+            for (int s = 0; s < nsub; s++) q += part[((int64_t)s * nhh + kl) * nhh + ij];
+        if (mask & CCD_T_HH) {
+            const int32_t p1 = d.hh[c.hh_off + kl], p2 = d.hh[c.hh_off + ij];
+            v = vas(lut, st[pa(p1)], st[pb(p1)], st[pa(p2)], st[pb(p2)]);
+        }
+        if (mask & CCD_T_QHH) v += q;
+        chiS[e] = v;
+    }
+}
+
 // the mixed modes: FP32 operands on the 16x16x4 FP32 MFMA or BF16 operands on
-// the 16x16x32 BF16 MFMA, FP32 accumulation; staging as in k_ladder64
-template <int P>
-__global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t mask, int n_items) {
+// the 16x16x32 BF16 MFMA, FP32 accumulation; staging as in k_ladder64.  Blocks nl,
+// nl + 1, ... (CHI): the one-body items, and chi_klij comes from the product
+// items' parts
+template <int P, bool CHI>
+__global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t mask, int n_items, int nl) {
     static_assert(P != P_F64, "the FP64 ladder is k_ladder64");
     constexpr int S = 4;
+    if (CHI && (int)blockIdx.x >= nl) {
+        dchi_item<true>(d, d.it_dchi[blockIdx.x - nl], mask);
+        return;
+    }
+    __shared__ double chiS[CHI ? 16 * kMaxHH : 1];
     __shared__ float lutS[kMaxLut];
     // delta chunk: [k][16] FP32, transposed [16][k] BF16
     __shared__ __attribute__((aligned(16))) char tks[P == P_F32 ? kKP * 16 * 4 : 16 * (kKP + 8) * 2];
@@ -1104,7 +1401,7 @@ __global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t 
     __shared__ int4 cvi[2][kKP];
     __shared__ int2 prs[kLadderRows];  // the two spin rows of the tile's pairs
     const char* lutB = (const char*)lutS;
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
+    for (int bi = blockIdx.x; bi < n_items; bi += nl) {
     const Item lg = d.it_lg[bi];
     if (lg.chan < 0) continue;
     const int g = lg.start;
@@ -1196,6 +1493,8 @@ __global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t 
     lutS[threadIdx.x] = lv0;
     if (threadIdx.x + 256 < kMaxLut) lutS[threadIdx.x + 256] = lv1;
     if (threadIdx.x < kLadderRows) prs[threadIdx.x] = myr;
+    if constexpr (CHI)
+        if (hh_on) chi_slice(d, c, G, g, ct, mask, chiS);
     if (pp_on) {
         if (threadIdx.x < kKP) cvi[0][threadIdx.x] = threadIdx.x < nlp ? cdesc(lpc) : cpad;
         lpc = cpad;
@@ -1291,7 +1590,8 @@ __global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t 
 #pragma unroll
             for (int s2 = 0; s2 < 4; s2++) {
                 const int kq = k0 + 4 * s2 + (lane >> 4);
-                bq[s2] = (kq < nhh && col < nhh) ? xg[kq * nhh + col] : 0.0;
+                if constexpr (CHI) bq[s2] = (kq < nhh && col < nhh) ? chiS[16 * kq + (lane & 15)] : 0.0;
+                else bq[s2] = (kq < nhh && col < nhh) ? xg[kq * nhh + col] : 0.0;
             }
 #pragma unroll
             for (int h = 0; h < 2; h++) {
@@ -1350,10 +1650,10 @@ __global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t 
 // that hold columns of the channel).  Staging is pipelined one chunk ahead: the
 // column descriptors (with the two rows of each pair) of chunk c + 1 are in LDS
 // while chunk c is multiplied, so the t loads of chunk c + 1 are in flight then.
-template <int NG>
+template <int NG, bool CHI>
 __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int cur,
                                               int r0, int ct, uint32_t mask, bool act, double* lutS,
-                                              double* tks, int4 (*cvi)[kKP], int2* prs) {
+                                              double* tks, int4 (*cvi)[kKP], int2* prs, double* chiS) {
     constexpr int S = 8;
     const char* lutB = (const char*)lutS;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1442,6 +1742,8 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
     lutS[threadIdx.x] = lv0;
     if (threadIdx.x + 256 < kMaxLut) lutS[threadIdx.x + 256] = lv1;
     if (threadIdx.x < kLadderRows) prs[threadIdx.x] = myr;
+    if constexpr (CHI)
+        if (hh_on) chi_slice(d, c, G, g, ct, mask, chiS);
     if (pp_on) {
         if (threadIdx.x < kKP) cvi[0][threadIdx.x] = threadIdx.x < nlp ? cdesc(lpc) : cpad;
         lpc = cpad;
@@ -1526,7 +1828,8 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
 #pragma unroll
             for (int q = 0; q < NG; q++) {
                 const int cc = ct * 16 + 4 * q + bj;
-                bb[q] = (kq < nhh && cc < nhh) ? xg[kq * nhh + cc] : 0.0;
+                if constexpr (CHI) bb[q] = (kq < nhh && cc < nhh) ? chiS[16 * kq + 4 * q + bj] : 0.0;
+                else bb[q] = (kq < nhh && cc < nhh) ? xg[kq * nhh + cc] : 0.0;
             }
 #pragma unroll
             for (int h = 0; h < 2; h++)
@@ -1554,12 +1857,19 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
     }
 }
 
-__global__ void __launch_bounds__(256, 3) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
+// (CHI, blocks past nl: as in k_ladder)
+template <bool CHI>
+__global__ void __launch_bounds__(256, 3) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items, int nl) {
+    if (CHI && (int)blockIdx.x >= nl) {
+        dchi_item<true>(d, d.it_dchi[blockIdx.x - nl], mask);
+        return;
+    }
     __shared__ double lutS[kMaxLut];
     __shared__ __attribute__((aligned(16))) double tks[kKP * 16];
     __shared__ int4 cvi[2][kKP];
     __shared__ int2 prs[kLadderRows];
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
+    __shared__ double chiS[CHI ? 16 * kMaxHH : 1];
+    for (int bi = blockIdx.x; bi < n_items; bi += nl) {
         const Item lg = d.it_lg[bi];
         if (lg.chan < 0) continue;
         const int g = lg.start;
@@ -1571,10 +1881,10 @@ __global__ void __launch_bounds__(256, 3) k_ladder64(DevPtrs d, int cur, uint32_
         // groups of four columns of this column tile that hold columns
         const int ng = min(4, (min(16, c.nhh - 16 * ct) + 3) >> 2);
         switch (ng) {
-            case 1: ladder64_item<1>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs); break;
-            case 2: ladder64_item<2>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs); break;
-            case 3: ladder64_item<3>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs); break;
-            default: ladder64_item<4>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs); break;
+            case 1: ladder64_item<1, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
+            case 2: ladder64_item<2, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
+            case 3: ladder64_item<3, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
+            default: ladder64_item<4, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
         }
     }
 }
@@ -1582,6 +1892,9 @@ __global__ void __launch_bounds__(256, 3) k_ladder64(DevPtrs d, int cur, uint32_
 // the update of every amplitude per (elementwise item, problem):
 // R = <ab||ij> (S_z = 0) + ladder sums (S_z = 0) + ring slots + one-body terms,
 // t_new = R / eps_ij^ab, mixing, and the energy partial of the item
+// (OB: the row's and the column's one-body intermediates are added here, as
+// k_onebody adds them, from the pair lists)
+template <bool OB>
 __global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha, uint32_t mask, int n_items) {
     __shared__ double sh[4];
     const bool ring_on = (mask & (CCD_T_RING | CCD_T_QRING)) != 0;
@@ -1601,6 +1914,7 @@ __global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha
         const double* rowX = d.rowX + G.rowa_base + g * G.n_rows_all + c.rowa_off;
         const double* colE = d.colE + G.cola_base + g * G.n_cols_all + c.cola_off;
         const double* colX = d.colX + G.cola_base + g * G.n_cols_all + c.cola_off;
+        const double* dc = d.dchi + G.eps_base + g * G.ns;
         double es = 0.0;
         for (int k = 0; k < kElemChunk / 256; k++) {
             const int e = it.start + threadIdx.x + 256 * k;
@@ -1615,7 +1929,12 @@ __global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha
                     double R = v;
                     if (lad) R += d.rmm[E];
                     if (ring_on) R += ring_term(d, G, g, c.t_off + e);
-                    R += (rowX[r] - colX[col]) * tc;
+                    if constexpr (OB) {
+                        const int32_t ab = d.pp[c.pp_off + r], ij = d.hh[c.hh_off + col];
+                        R += ((dc[pa(ab)] + dc[pb(ab)]) - (dc[pa(ij)] + dc[pb(ij)])) * tc;
+                    } else {
+                        R += (rowX[r] - colX[col]) * tc;
+                    }
                     tm = alpha * (R / (colE[col] - rowE[r])) + (1.0 - alpha) * tc;
                 }
                 d.t[cur ^ 1][E] = tm;
@@ -1671,12 +1990,13 @@ struct ccd_ctx {
     std::vector<DevChan> dchans;
     std::vector<DevPh> dph;
     std::vector<int32_t> lpinfo;
-    std::vector<int32_t> st, hh, pp, phst, phmap, zs, csr_ptr, csr_idx, pgrp, pgi, it_sz0;
+    std::vector<int32_t> st, hh, pp, phst, phmap, zs, csr_ptr, csr_idx, pgrp, pgi, it_sz0, cinfo;
     std::vector<double> eps, lut, rowE, colE, pscale;
     std::vector<Item> it_elem, it_ladder, it_dchi, it_direct, it_ring_s, it_ring_b, it_lg, it_ue, it_dsub,
         it_dsum;
     int64_t n_dpart = 0, n_dcolp = 0;
     int ring_lo[4] = {0}, ring_n[4] = {0};  // big pair items by padded size n16 = 32, 48, 64, 80
+    int max_pair = 0;                       // largest order of a pair
     std::vector<int64_t> prob_t0;  // amplitude index of each problem (caller order)
     std::vector<int> slot_of;      // caller problem -> slot (group order) of the device flags
     int64_t NT = 0;
@@ -1723,7 +2043,7 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
     X(csr_idx, int32_t) X(pgrp, int32_t) X(pgi, int32_t) X(pscale, double) \
     X(it_elem, Item) X(it_ladder, Item) X(it_sz0, int32_t) X(it_dchi, Item) \
     X(it_direct, Item) X(it_ring_s, Item) X(it_ring_b, Item) X(it_lg, Item) X(it_ue, Item) \
-    X(it_dsub, Item) X(it_dsum, Item) X(lpinfo, int32_t)
+    X(it_dsub, Item) X(it_dsum, Item) X(lpinfo, int32_t) X(cinfo, int32_t)
 
 static DevPtrs make_ptrs(ccd_ctx* c) {
     DevPtrs d;
@@ -1736,7 +2056,7 @@ static DevPtrs make_ptrs(ccd_ctx* c) {
     const void* p_it_dchi; const void* p_it_direct; const void* p_it_ring_s; const void* p_it_ring_b;
     const void* p_it_lg; const void* p_it_ue; const void* p_zs; const void* p_rowE; const void* p_colE;
     const void* p_pscale; const void* p_it_dsub; const void* p_it_dsum;
-    const void* p_lpinfo;
+    const void* p_lpinfo; const void* p_cinfo;
 #define TAKE(name, T)             \
     p_##name = base + o;          \
     o += align256(c->name.size() * sizeof(T));
@@ -1757,6 +2077,7 @@ static DevPtrs make_ptrs(ccd_ctx* c) {
     d.pscale = (const double*)p_pscale;
     d.it_dsub = (const Item*)p_it_dsub; d.it_dsum = (const Item*)p_it_dsum;
     d.lpinfo = (const int4*)p_lpinfo;
+    d.cinfo = (const int32_t*)p_cinfo;
     d.dpart = (double*)(base + c->r_dpart.off);
     d.dcolp = (double*)(base + c->r_dcolp.off);
     d.t[0] = (double*)(base + c->r_t0.off);
@@ -1932,6 +2253,7 @@ static ccd_status assemble(ccd_ctx* c) {
         for (size_t k = 0; k < H.pp.size() / 2; k++) c->pp.push_back(pack_pair(H.pp[2 * k], H.pp[2 * k + 1]));
         int rows = 0, cols = 0, chh = 0, dpart = 0, dcolp = 0;
         std::vector<std::vector<int32_t>> lists(H.ns);
+        D.cinfo_off = (int)c->cinfo.size() / 2;
         D.ladder_lo = (int)c->it_ladder.size();
         D.elem_lo = (int)c->it_elem.size();
         for (const Chan& h : H.chans) {
@@ -1978,6 +2300,10 @@ static ccd_status assemble(ccd_ctx* c) {
                     dcolp += h.nhh;
                 }
                 dc.dsub_n = (int)c->it_dsub.size() - dc.dsub_lo;
+                for (int q = 0; q < h.nhh; q++) {
+                    c->cinfo.push_back(dc.dcolp_off + q);
+                    c->cinfo.push_back(h.nhh | (dc.dsub_n << 16));
+                }
                 for (int g = 0; g < D.G; g++) dsum.push_back({slot0 + g, Item{id, g}});
                 // momentum pairs {n_a, n_b} of the rows, in order of first row;
                 // a row's pair is keyed by n_a (b follows from K and the spins)
@@ -2079,6 +2405,7 @@ static ccd_status assemble(ccd_ctx* c) {
             const int pid = (int)c->dph.size();
             if (h.zp_off >= 0) {
                 const int nb = std::max(h.n, dp.m);  // the pair's padded order
+                c->max_pair = std::max(c->max_pair, nb);
                 for (int g = 0; g < D.G; g++) {
                     if (nb <= 16) rs.push_back({slot0 + g, Item{pid, g}});
                     else {
@@ -2204,6 +2531,17 @@ static int grid_for(const ccd_ctx* c, int slot, int nb) {
     return std::min(nb, m * 256);
 }
 
+// Whether a sweep runs as three launches on the context's stream: with every
+// launch shape at its default.  It was the faster form at every size and batch
+// measured (see k_front); chosen shapes and kernel timing are those of the
+// separate launches.
+static bool one_stream(const ccd_ctx* c) {
+    if (c->timing) return false;
+    for (int k = 0; k < CCD_TUNE_LEN; k++)
+        if (c->tune[k] != 0) return false;
+    return true;
+}
+
 // the energy step left over from the previous sweep, as its own launch
 static ccd_status flush_energy(ccd_ctx* c, const DevPtrs& d) {
     if (!c->energy_pending) return CCD_OK;
@@ -2220,10 +2558,10 @@ static ccd_status L_direct(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
         if (c->energy_pending && nd > 0) {
             // the previous sweep's energy step rides on this launch (its last blocks)
             c->energy_pending = false;
-            LAUNCH(F_DIRECT, k_direct<P>, nd + (int)c->probs.size(), 256, 0, d, cur, mask, n, nd, 1, c->pend_tol,
-                   c->pend_tol_rel, c->pend_rule);
+            LAUNCH(F_DIRECT, k_direct<P>, nd + (int)c->probs.size(), dir_threads<P>(), dir_lds<P>(), d, cur, mask, n, nd,
+                   1, c->pend_tol, c->pend_tol_rel, c->pend_rule);
         } else {
-            LAUNCH(F_DIRECT, k_direct<P>, nd, 256, 0, d, cur, mask, n, nd, 0, 0.0, 0.0, 0);
+            LAUNCH(F_DIRECT, k_direct<P>, nd, dir_threads<P>(), dir_lds<P>(), d, cur, mask, n, nd, 0, 0.0, 0.0, 0);
         }
     }
     if (mask & (CCD_T_HH | CCD_T_QHH | CCD_T_QHOLE))
@@ -2279,9 +2617,11 @@ static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
     const int n = (int)c->it_lg.size();
     if (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) {
         if constexpr (P == P_F64) {
-            LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
+            LAUNCH(F_LADDER, k_ladder64<false>, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n,
+                   grid_for(c, CCD_TUNE_LADDER, n));
         } else {
-            LAUNCH(F_LADDER, k_ladder<P>, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
+            LAUNCH(F_LADDER, (k_ladder<P, false>), grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n,
+                   grid_for(c, CCD_TUNE_LADDER, n));
         }
     }
     return CCD_OK;
@@ -2289,7 +2629,57 @@ static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
 
 static ccd_status L_update(ccd_ctx* c, const DevPtrs& d, int cur, double alpha, uint32_t mask) {
     const int n = (int)c->it_ue.size();
-    LAUNCH(F_UPDATE, k_update, grid_for(c, CCD_TUNE_UPDATE, n), 256, 0, d, cur, alpha, mask, n);
+    if (one_stream(c))
+        LAUNCH(F_UPDATE, k_update<true>, n, 256, 0, d, cur, alpha, mask, n);
+    else
+        LAUNCH(F_UPDATE, k_update<false>, grid_for(c, CCD_TUNE_UPDATE, n), 256, 0, d, cur, alpha, mask, n);
+    return CCD_OK;
+}
+
+template <int P>
+static size_t front_lds(const ccd_ctx* c) {
+    size_t m = 0;
+    auto use = [&](bool on, size_t b) { if (on) m = std::max(m, b); };
+    use(!c->it_direct.empty(), dir_lds<P>());
+    use(!c->it_ring_s.empty(), 8 * ((pair_lds<P>(16) + 15) & ~(size_t)15));
+    use(c->ring_n[0] > 0, 2 * ((pair_lds<P>(32) + 15) & ~(size_t)15));
+    use(c->ring_n[1] > 0, pair_lds<P>(48));
+    use(c->ring_n[2] > 0, pair_lds<P>(64));
+    use(c->ring_n[3] > 0, c->max_pair <= kRing80M ? pair_lds<P>(80, kRing80M) : pair_lds<P>(80));
+    return std::max<size_t>(m, 64);
+}
+
+// The contractions of a sweep on the context's stream alone: two launches, the
+// update's being the third.
+template <int P>
+static ccd_status launch_one_stream(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
+    Front f;
+    std::memset(&f, 0, sizeof(f));
+    if (mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) f.nd = (int)c->it_direct.size();
+    if (mask & (CCD_T_RING | CCD_T_QRING)) {
+        for (int k = 0; k < 4; k++) {
+            f.nb[k] = c->ring_n[k];
+            f.lo[k] = c->ring_lo[k];
+        }
+        f.n32 = f.nb[0];
+        f.nb[0] = 8 * ((f.nb[0] / 8 + 1) / 2);
+        f.n_small = (int)c->it_ring_s.size();
+        f.ns = 8 * ((f.n_small / 32 + 1) / 2);
+        f.small80 = c->max_pair <= kRing80M;
+    }
+    if (c->energy_pending) {
+        c->energy_pending = false;
+        f.ne = (int)c->probs.size();
+    }
+    const int grid = f.nd + f.nb[0] + f.nb[1] + f.nb[2] + f.nb[3] + f.ns + f.ne;
+    LAUNCH(F_DIRECT, k_front<P>, grid, kFrontThreads, front_lds<P>(c), d, cur, mask, f, c->pend_tol, c->pend_tol_rel,
+           c->pend_rule);
+    const int nl = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) ? (int)c->it_lg.size() : 0;
+    const int no = (int)c->it_dchi.size();
+    if constexpr (P == P_F64)
+        LAUNCH(F_LADDER, k_ladder64<true>, nl + no, 256, 0, d, cur, mask, nl, nl);
+    else
+        LAUNCH(F_LADDER, (k_ladder<P, true>), nl + no, 256, 0, d, cur, mask, nl, nl);
     return CCD_OK;
 }
 
@@ -2313,6 +2703,7 @@ struct StreamSwap {
 // event times are not overlapped.
 template <int P>
 static ccd_status launch_contractions(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
+    if (one_stream(c)) return launch_one_stream<P>(c, d, cur, mask);
     const bool fork = c->aux_ok && !c->timing;
     ccd_status s = CCD_OK;
     // a pending energy step that no k_direct launch of this sweep can carry
@@ -2380,6 +2771,12 @@ static hipError_t set_ring_attr_pair() {
 template <int P>
 static hipError_t set_ring_attrs() {
     hipError_t e;
+    if ((e = hipFuncSetAttribute((const void*)k_front<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)std::max(dir_lds<P>(), pair_lds<P>(80)))) != hipSuccess)
+        return e;
+    if ((e = hipFuncSetAttribute((const void*)k_direct<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)dir_lds<P>())) != hipSuccess)
+        return e;
     if ((e = set_ring_attr_pair<P, 32, 4, 2>()) != hipSuccess) return e;
     if ((e = set_ring_attr_pair<P, 48, 9, 3>()) != hipSuccess) return e;
     if ((e = set_ring_attr_pair<P, 64, 16, 8>()) != hipSuccess) return e;

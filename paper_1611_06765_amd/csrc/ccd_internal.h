@@ -56,6 +56,8 @@ struct DevGroup {
     int32_t csr_off;      // one-body CSR row pointers of the group: csr_off + s
     int32_t n_dpart, n_dcolp;       // partial chi_klij / column sums per problem
     int64_t dpart_base, dcolp_base; // + g * n_dpart / n_dcolp
+    int32_t cinfo_off;    // column -> parts table of the structure (shared)
+    int32_t pad;
 };
 
 struct DevChan {

@@ -226,3 +226,29 @@ def test_extrapolated_stop_rule_bounds_the_error():
         assert np.all(ra["sweeps"] >= rb["sweeps"])
         for p in range(2):
             assert abs(a.energy(p)[2] - e_ref[p]) <= 1e-6 * abs(e_ref[p]), (scale, p)
+
+
+# sizes at the edges of the merged launches: one hole pair; small pairs only; pairs of
+# order 32, 48, 64; of order 66 (kept in 68 rows); of order above 68 (a twist)
+_EDGE = [[(2, 1, 0.1)], [(14, 4, 0.1), (14, 11, 0.07)], [(38, 12, 0.1)], [(54, 12, 0.12), (2, 9, 0.1)],
+         [(66, 20, 0.16), (66, 20, 0.08), (66, 20, 0.12)], [(66, 36, 0.16)],
+         [(66, 36, 0.16, 41.47, (0.725, 0.725, 0.725))]]
+
+
+@pytest.mark.parametrize("specs", _EDGE, ids=lambda s: "-".join(f"{x[0]}_{x[1]}" for x in s))
+@pytest.mark.parametrize("prec", [ccd.CCD_PREC_FP64, ccd.CCD_PREC_FP32, ccd.CCD_PREC_BF16])
+def test_three_launch_sweep_equals_the_separate_launches(specs, prec):
+    """The default sweep (three launches on one stream) against the families
+    as launches of their own, bit for bit, for each term alone and all
+    together: energies of every sweep and all amplitudes."""
+    probs = [ccd.problem(*x) for x in specs]
+    a, b = _ctx(probs), _ctx(probs)
+    b.set_tuning([0, 0, 0, 0, 0, 4, 0, 0, 0, 0])
+    for mask in (1, 2, 4, 8, 16, 32, 64, 127):
+        out = []
+        for c in (a, b):
+            c.reset_amplitudes()
+            out.append(c.iterate(mixing=0.5, max_iter=3, precision=prec, terms=mask, history=True, check_every=2))
+        assert np.array_equal(out[0]["history"], out[1]["history"]), mask
+        for p in range(len(probs)):
+            assert np.array_equal(a.get_amplitudes(p), b.get_amplitudes(p)), (mask, p)
