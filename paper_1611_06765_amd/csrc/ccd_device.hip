@@ -851,7 +851,7 @@ __global__ void __launch_bounds__(256) k_dsum(DevPtrs d, uint32_t mask, int n_it
 template <bool PARTS>
 __device__ __forceinline__ void dchi_item(const DevPtrs& d, const Item it, uint32_t mask) {
     const DevGroup& G = d.groups[it.chan];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
     const int s = (it.start & 0xffff) + w, g = it.start >> 16;  // state of this wave, problem
     if (s >= G.ns) return;
     const int x0 = d.csr_ptr[G.csr_off + s], x1 = d.csr_ptr[G.csr_off + s + 1];
@@ -1366,7 +1366,7 @@ __device__ __forceinline__ void chi_slice(const DevPtrs& d, const DevChan& c, co
     const double* part = d.dpart + G.dpart_base + (int64_t)g * G.n_dpart + c.dpart_off;
     const double* lut = d.lut + G.lut_base + g * G.nlut;
     const int32_t* st = d.st + G.st_off;
-    for (int e = threadIdx.x; e < 16 * nhh; e += 256) {
+    for (int e = threadIdx.x; e < 16 * nhh; e += blockDim.x) {
         const int kl = e >> 4, ij = 16 * ct + (e & 15);
         if (ij >= nhh) continue;
         double v = 0.0, q = 0.0;
@@ -1382,17 +1382,12 @@ __device__ __forceinline__ void chi_slice(const DevPtrs& d, const DevChan& c, co
 }
 
 // the mixed modes: FP32 operands on the 16x16x4 FP32 MFMA or BF16 operands on
-// the 16x16x32 BF16 MFMA, FP32 accumulation; staging as in k_ladder64.  Blocks nl,
-// nl + 1, ... (CHI): the one-body items, and chi_klij comes from the product
-// items' parts
+// the 16x16x32 BF16 MFMA, FP32 accumulation; four waves, staged with two
+// barriers per chunk
 template <int P, bool CHI>
-__global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t mask, int n_items, int nl) {
+__device__ __forceinline__ void ladder32_run(const DevPtrs& d, int cur, uint32_t mask, int n_items, int nl) {
     static_assert(P != P_F64, "the FP64 ladder is k_ladder64");
     constexpr int S = 4;
-    if (CHI && (int)blockIdx.x >= nl) {
-        dchi_item<true>(d, d.it_dchi[blockIdx.x - nl], mask);
-        return;
-    }
     __shared__ double chiS[CHI ? 16 * kMaxHH : 1];
     __shared__ float lutS[kMaxLut];
     // delta chunk: [k][16] FP32, transposed [16][k] BF16
@@ -1627,6 +1622,17 @@ __global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t 
     }
 }
 
+template <int P>
+__global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t mask, int n_items) {
+    ladder32_run<P, false>(d, cur, mask, n_items, gridDim.x);
+}
+// as k_mid64
+template <int P>
+__global__ void __launch_bounds__(256, 3) k_mid(DevPtrs d, int cur, uint32_t mask, int nl, int no) {
+    if ((int)blockIdx.x < nl) ladder32_run<P, true>(d, cur, mask, nl, nl);
+    else if ((int)blockIdx.x - nl < no) dchi_item<true>(d, d.it_dchi[blockIdx.x - nl], mask);
+}
+
 // FP64 ladder sums over momentum pairs, on the 4x4x4 MFMA.
 //
 // In an S_z = 0 block the generated <ab||cd> = s_a s_c (W(|n_a - n_c|^2) +
@@ -1647,16 +1653,26 @@ __global__ void __launch_bounds__(256, 3) k_ladder(DevPtrs d, int cur, uint32_t 
 //
 // The 16-row tiles of pairs map onto the four blocks of the instruction and the
 // 16-column tile is cut into NG groups of four columns (NG = 1 .. 4, the groups
-// that hold columns of the channel).  Staging is pipelined one chunk ahead: the
-// column descriptors (with the two rows of each pair) of chunk c + 1 are in LDS
-// while chunk c is multiplied, so the t loads of chunk c + 1 are in flight then.
+// that hold columns of the channel).  Eight waves: wave w owns pairs 32 (w % 4) ..
+// + 31 of the tile and every second 16-pair K step of a chunk (w / 4 says which),
+// since an item is a serial chain of K steps and one problem has few items; the
+// two halves are added through LDS at the end.  Staging is pipelined one chunk
+// ahead: the column descriptors (with the two rows of each pair) of chunk c + 1
+// are in LDS while chunk c is multiplied, so its t loads are in flight then, and
+// delta is double-buffered, so a chunk takes one barrier.
+constexpr int kLadThreads = 512;
+struct Lad64 {
+    double lutS[kMaxLut + 1];
+    double tks[2][kKP * 16];   // delta of two chunks; at the end the halves' sums
+    int4 cvi[3][kKP];          // column descriptors of three chunks
+    int2 prs[kLadderRows];     // the two spin rows of the tile's pairs
+};
 template <int NG, bool CHI>
 __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int cur,
-                                              int r0, int ct, uint32_t mask, bool act, double* lutS,
-                                              double* tks, int4 (*cvi)[kKP], int2* prs, double* chiS) {
+                                              int r0, int ct, uint32_t mask, bool act, Lad64& L, double* chiS) {
     constexpr int S = 8;
-    const char* lutB = (const char*)lutS;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const char* lutB = (const char*)L.lutS;
+    const int tid = threadIdx.x, lane = tid & 63, w = (tid >> 6) & 3, kh = tid >> 8;
     const int nhh = c.nhh, nlp = c.n_lp;
     const bool pp_on = act && (mask & CCD_T_PP) != 0;
     const bool hh_on = act && (mask & (CCD_T_HH | CCD_T_QHH)) != 0;
@@ -1696,17 +1712,17 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
         return make_int4(times4(li.x), S * C2, S * (C2 + D2),
                          (int)((uint32_t)(li.z + 1) | ((uint32_t)(li.w + 1) << 16)));
     };
-    constexpr int kPer = kKP * 16 / 256;
+    constexpr int kPer = kKP * 16 / kLadThreads;
     double tv[kPer];
     // delta of chunk kp from the rows in cvi[b]
     auto load_delta = [&](int kp, int b) {
         const int kn = min(kKP, nlp - kp);
 #pragma unroll
         for (int i = 0; i < kPer; i++) {
-            const int e = threadIdx.x + 256 * i, kk = e >> 4, cc = ct * 16 + (e & 15);
+            const int e = tid + kLadThreads * i, kk = e >> 4, cc = ct * 16 + (e & 15);
             double v = 0.0;
             if (kk < kn && cc < nhh) {
-                const uint32_t rr = (uint32_t)cvi[b][kk].w;
+                const uint32_t rr = (uint32_t)L.cvi[b][kk].w;
                 const int rp = (int)(rr & 0xffff) - 1, rm = (int)(rr >> 16) - 1;
                 const double tp = rp >= 0 ? tcur[(int64_t)rp * nhh + cc] : 0.0;
                 const double tm = rm >= 0 ? tcur[(int64_t)rm * nhh + cc] : 0.0;
@@ -1715,12 +1731,9 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
             tv[i] = v;
         }
     };
-    auto store_delta = [&]() {
+    auto store_delta = [&](int b) {
 #pragma unroll
-        for (int i = 0; i < kPer; i++) {
-            const int e = threadIdx.x + 256 * i;
-            tks[(e >> 4) * 16 + (e & 15)] = tv[i];
-        }
+        for (int i = 0; i < kPer; i++) L.tks[b][tid + kLadThreads * i] = tv[i];
     };
 
     double acc[2][NG][2];
@@ -1730,46 +1743,45 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
         for (int q = 0; q < NG; q++) { acc[h][q][0] = 0.0; acc[h][q][1] = 0.0; }
 
     const double* lutg = d.lut + G.lut_base + g * G.nlut;
-    const double lv0 = threadIdx.x < G.nlut ? lutg[threadIdx.x] : 0.0;
-    const double lv1 = threadIdx.x + 256 < G.nlut ? lutg[threadIdx.x + 256] : 0.0;
+    const double lv0 = tid < G.nlut ? lutg[tid] : 0.0;
     int4 lpc = cpad;
-    if (pp_on && threadIdx.x < kKP && threadIdx.x < nlp) lpc = lp[threadIdx.x];
+    if (pp_on && tid < kKP && tid < nlp) lpc = lp[tid];
     // the two spin rows of the tile's pairs, for the hh operands and the stores
     const int2* lpr = (const int2*)lp;
-    const int2 myr = (threadIdx.x < kLadderRows && r0 + threadIdx.x < nlp) ? lpr[2 * (r0 + threadIdx.x) + 1]
-                                                                           : make_int2(-1, -1);
+    const int2 myr = (tid < kLadderRows && r0 + tid < nlp) ? lpr[2 * (r0 + tid) + 1] : make_int2(-1, -1);
     __syncthreads();  // the previous item's reads of LDS are done
-    lutS[threadIdx.x] = lv0;
-    if (threadIdx.x + 256 < kMaxLut) lutS[threadIdx.x + 256] = lv1;
-    if (threadIdx.x < kLadderRows) prs[threadIdx.x] = myr;
+    if (tid < kMaxLut) L.lutS[tid] = lv0;
+    if (tid < kLadderRows) L.prs[tid] = myr;
     if constexpr (CHI)
         if (hh_on) chi_slice(d, c, G, g, ct, mask, chiS);
     if (pp_on) {
-        if (threadIdx.x < kKP) cvi[0][threadIdx.x] = threadIdx.x < nlp ? cdesc(lpc) : cpad;
+        if (tid < kKP) L.cvi[0][tid] = tid < nlp ? cdesc(lpc) : cpad;
         lpc = cpad;
-        if (threadIdx.x < kKP && kKP + threadIdx.x < nlp) lpc = lp[kKP + threadIdx.x];
+        if (tid < kKP && kKP + tid < nlp) lpc = lp[kKP + tid];
     }
     __syncthreads();
     if (pp_on) {
         load_delta(0, 0);
-        store_delta();
+        store_delta(0);
+        int b3 = 0;  // chunk index modulo 3
         for (int kp = 0; kp < nlp; kp += kKP) {
-            const int b = (kp / kKP) & 1;
+            const int b = (kp / kKP) & 1, n3 = b3 == 2 ? 0 : b3 + 1;
             const bool more = kp + kKP < nlp;
-            if (more && threadIdx.x < kKP) {
-                cvi[b ^ 1][threadIdx.x] = kp + kKP + threadIdx.x < nlp ? cdesc(lpc) : cpad;
+            if (more && tid < kKP) {
+                L.cvi[n3][tid] = kp + kKP + tid < nlp ? cdesc(lpc) : cpad;
                 lpc = cpad;
-                if (kp + 2 * kKP + threadIdx.x < nlp) lpc = lp[kp + 2 * kKP + threadIdx.x];
+                if (kp + 2 * kKP + tid < nlp) lpc = lp[kp + 2 * kKP + tid];
             }
             __syncthreads();  // this chunk's delta and the next chunk's descriptors are in LDS
-            if (more) load_delta(kp + kKP, b ^ 1);
+            if (more) load_delta(kp + kKP, n3);
             const int kn = min(kKP, nlp - kp);
             const int ksteps = (kn + 15) & ~15;
-            for (int kk = 0; kk < ksteps; kk += 16) {
+            const double* tk = L.tks[b];
+            for (int kk = 16 * kh; kk < ksteps; kk += 32) {
                 int o1[2][4], o2[2][4];
 #pragma unroll
                 for (int s2 = 0; s2 < 4; s2++) {
-                    const int4 ci = cvi[b][kk + 4 * s2 + (lane >> 4)];
+                    const int4 ci = L.cvi[b3][kk + 4 * s2 + (lane >> 4)];
 #pragma unroll
                     for (int h = 0; h < 2; h++) {
                         o1[h][s2] = __builtin_amdgcn_sdot4(apack[h], ci.x, rowA[h] + ci.y, false);
@@ -1777,29 +1789,33 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                double x1[2][4], x2[2][4], vb[4][NG];
 #pragma unroll
-                for (int s2 = 0; s2 < 4; s2++) {
+                for (int s4 = 0; s4 < 4; s4 += 2) {
+                    double x1[2][2], x2[2][2], vb[2][NG];
 #pragma unroll
-                    for (int h = 0; h < 2; h++) {
-                        x1[h][s2] = *(const double*)(lutB + o1[h][s2]);
-                        x2[h][s2] = *(const double*)(lutB + o2[h][s2]);
+                    for (int s2 = 0; s2 < 2; s2++) {
+#pragma unroll
+                        for (int h = 0; h < 2; h++) {
+                            x1[h][s2] = *(const double*)(lutB + o1[h][s4 + s2]);
+                            x2[h][s2] = *(const double*)(lutB + o2[h][s4 + s2]);
+                        }
+#pragma unroll
+                        for (int q = 0; q < NG; q++)
+                            vb[s2][q] = tk[(kk + 4 * (s4 + s2) + (lane >> 4)) * 16 + 4 * q + bj];
                     }
 #pragma unroll
-                    for (int q = 0; q < NG; q++) vb[s2][q] = tks[(kk + 4 * s2 + (lane >> 4)) * 16 + 4 * q + bj];
-                }
+                    for (int s2 = 0; s2 < 2; s2++) {
 #pragma unroll
-                for (int s2 = 0; s2 < 4; s2++) {
+                        for (int h = 0; h < 2; h++) {
+                            const double va = x1[h][s2] + x2[h][s2];
 #pragma unroll
-                    for (int h = 0; h < 2; h++) {
-                        const double va = x1[h][s2] + x2[h][s2];
-#pragma unroll
-                        for (int q = 0; q < NG; q++) acc[h][q][s2 & 1] = mfma4(va, vb[s2][q], acc[h][q][s2 & 1]);
+                            for (int q = 0; q < NG; q++) acc[h][q][s2] = mfma4(va, vb[s2][q], acc[h][q][s2]);
+                        }
                     }
                 }
             }
-            __syncthreads();  // every wave is done with this chunk
-            if (more) store_delta();
+            if (more) store_delta(b ^ 1);
+            b3 = n3;
         }
         // u of the lane's output pair: + to the (p up, q down) row, - to the other
 #pragma unroll
@@ -1811,18 +1827,16 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
                 acc[h][q][1] = -u;
             }
     }
-    // the two spin rows of the lane's A-operand pairs and of its output pairs
-    int arow[2][2], orow[2][2];
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-        const int2 ra = prs[32 * w + 16 * h + (lane & 15)], ro = prs[32 * w + 16 * h + orow4];
-        arow[h][0] = ra.x; arow[h][1] = ra.y;
-        orow[h][0] = ro.x; orow[h][1] = ro.y;
-    }
     if (hh_on) {
         // 1/2 sum_kl t_kl^ab chi_klij per spin row: A = t rows, B = chi_klij columns
+        int arow[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int2 ra = L.prs[32 * w + 16 * h + (lane & 15)];
+            arow[h][0] = ra.x; arow[h][1] = ra.y;
+        }
         const double* xg = d.chh + G.chh_base + g * G.n_chh + c.chh_off;
-        for (int k0 = 0; k0 < nhh; k0 += 4) {
+        for (int k0 = 4 * kh; k0 < nhh; k0 += 8) {
             const int kq = k0 + (lane >> 4);
             double bb[NG];
 #pragma unroll
@@ -1842,50 +1856,66 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
                 }
         }
     }
+    // add the two halves: waves of half 0 finish the + rows, of half 1 the - rows
+    double* x0 = &L.tks[0][0];
+    __syncthreads();  // the last chunk's reads are done
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int q = 0; q < NG; q++)
+            x0[kh * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane] = kh ? acc[h][q][0] : acc[h][q][1];
+    __syncthreads();
     if (act) {
 #pragma unroll
-        for (int h = 0; h < 2; h++)
+        for (int h = 0; h < 2; h++) {
+            const int2 ro = L.prs[32 * w + 16 * h + orow4];
+            const int r = kh ? ro.y : ro.x;
 #pragma unroll
-            for (int s = 0; s < 2; s++) {
-                const int r = orow[h][s];
-#pragma unroll
-                for (int q = 0; q < NG; q++) {
-                    const int cc = ct * 16 + 4 * q + bj;
-                    if (r >= 0 && cc < nhh) d.rmm[T0 + (int64_t)r * nhh + cc] = acc[h][q][s];
-                }
+            for (int q = 0; q < NG; q++) {
+                const int cc = ct * 16 + 4 * q + bj;
+                const double other = x0[(kh ^ 1) * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane];
+                // half 0's share first in both
+                const double v = kh ? other + acc[h][q][1] : acc[h][q][0] + other;
+                if (r >= 0 && cc < nhh) d.rmm[T0 + (int64_t)r * nhh + cc] = v;
             }
+        }
     }
 }
 
-// (CHI, blocks past nl: as in k_ladder)
 template <bool CHI>
-__global__ void __launch_bounds__(256, 3) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items, int nl) {
-    if (CHI && (int)blockIdx.x >= nl) {
-        dchi_item<true>(d, d.it_dchi[blockIdx.x - nl], mask);
-        return;
+__device__ __forceinline__ void ladder64_run(const DevPtrs& d, int cur, uint32_t mask, int bi, Lad64& L, double* chiS) {
+    const Item lg = uni(d.it_lg[bi]);
+    if (lg.chan < 0) return;
+    const int g = lg.start;
+    const Item it = uni(d.it_ladder[lg.chan]);
+    const int r0 = it.start & 0xfffff, ct = it.start >> 20;
+    const DevChan c = uni(d.chans[it.chan]);
+    const DevGroup G = uni(d.groups[c.group]);
+    const bool act = d.active[G.p0 + g] != 0;
+    // groups of four columns of this column tile that hold columns
+    const int ng = min(4, (min(16, c.nhh - 16 * ct) + 3) >> 2);
+    switch (ng) {
+        case 1: ladder64_item<1, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
+        case 2: ladder64_item<2, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
+        case 3: ladder64_item<3, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
+        default: ladder64_item<4, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
     }
-    __shared__ double lutS[kMaxLut];
-    __shared__ __attribute__((aligned(16))) double tks[kKP * 16];
-    __shared__ int4 cvi[2][kKP];
-    __shared__ int2 prs[kLadderRows];
-    __shared__ double chiS[CHI ? 16 * kMaxHH : 1];
-    for (int bi = blockIdx.x; bi < n_items; bi += nl) {
-        const Item lg = d.it_lg[bi];
-        if (lg.chan < 0) continue;
-        const int g = lg.start;
-        const Item it = d.it_ladder[lg.chan];
-        const int r0 = it.start & 0xfffff, ct = it.start >> 20;
-        const DevChan c = d.chans[it.chan];
-        const DevGroup G = d.groups[c.group];
-        const bool act = d.active[G.p0 + g] != 0;
-        // groups of four columns of this column tile that hold columns
-        const int ng = min(4, (min(16, c.nhh - 16 * ct) + 3) >> 2);
-        switch (ng) {
-            case 1: ladder64_item<1, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
-            case 2: ladder64_item<2, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
-            case 3: ladder64_item<3, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
-            default: ladder64_item<4, CHI>(d, c, G, g, cur, r0, ct, mask, act, lutS, tks, cvi, prs, chiS); break;
-        }
+}
+__global__ void __launch_bounds__(kLadThreads, 4) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
+    __shared__ Lad64 L;
+    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) ladder64_run<false>(d, cur, mask, bi, L, nullptr);
+}
+// the second launch of a sweep on one stream: ladder items, then (blocks nl, ...)
+// the one-body items, two per block; chi_klij comes from the product items' parts
+__global__ void __launch_bounds__(kLadThreads, 4) k_mid64(DevPtrs d, int cur, uint32_t mask, int nl, int no) {
+    __shared__ Lad64 L;
+    __shared__ double chiS[16 * kMaxHH];
+    const int b = blockIdx.x;
+    if (b < nl) {
+        ladder64_run<true>(d, cur, mask, b, L, chiS);
+    } else {
+        const int k = 2 * (b - nl) + (threadIdx.x >> 8);
+        if (k < no) dchi_item<true>(d, d.it_dchi[k], mask);
     }
 }
 
@@ -2617,11 +2647,9 @@ static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
     const int n = (int)c->it_lg.size();
     if (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) {
         if constexpr (P == P_F64) {
-            LAUNCH(F_LADDER, k_ladder64<false>, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n,
-                   grid_for(c, CCD_TUNE_LADDER, n));
+            LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), kLadThreads, 0, d, cur, mask, n);
         } else {
-            LAUNCH(F_LADDER, (k_ladder<P, false>), grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n,
-                   grid_for(c, CCD_TUNE_LADDER, n));
+            LAUNCH(F_LADDER, k_ladder<P>, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
         }
     }
     return CCD_OK;
@@ -2677,9 +2705,9 @@ static ccd_status launch_one_stream(ccd_ctx* c, const DevPtrs& d, int cur, uint3
     const int nl = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) ? (int)c->it_lg.size() : 0;
     const int no = (int)c->it_dchi.size();
     if constexpr (P == P_F64)
-        LAUNCH(F_LADDER, k_ladder64<true>, nl + no, 256, 0, d, cur, mask, nl, nl);
+        LAUNCH(F_LADDER, k_mid64, nl + (no + 1) / 2, kLadThreads, 0, d, cur, mask, nl, no);
     else
-        LAUNCH(F_LADDER, (k_ladder<P, true>), nl + no, 256, 0, d, cur, mask, nl, nl);
+        LAUNCH(F_LADDER, k_mid<P>, nl + no, 256, 0, d, cur, mask, nl, no);
     return CCD_OK;
 }
 
