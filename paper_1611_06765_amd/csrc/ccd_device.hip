@@ -1313,12 +1313,6 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
     if (b < f.ne) energy_of(d, b, tol, tol_rel, rule, (double*)dyn_lds);
 }
 
-// the ring contribution to amplitude e of problem g: its two ring slots
-__device__ __forceinline__ double ring_term(const DevPtrs& d, const DevGroup& G, int g, int64_t e) {
-    const double2 z = *(const double2*)(d.zc + 2 * (G.t_base + g * G.n_amp + e));
-    return z.x + z.y;
-}
-
 // one-body sums per row (delta chi_a + delta chi_b) and column (delta chi_i +
 // delta chi_j); grid (blocks over rows + columns, problem slot)
 __global__ void __launch_bounds__(256) k_onebody(DevPtrs d) {
@@ -1921,58 +1915,102 @@ __global__ void __launch_bounds__(kLadThreads, 4) k_mid64(DevPtrs d, int cur, ui
 
 // the update of every amplitude per (elementwise item, problem):
 // R = <ab||ij> (S_z = 0) + ladder sums (S_z = 0) + ring slots + one-body terms,
-// t_new = R / eps_ij^ab, mixing, and the energy partial of the item
-// (OB: the row's and the column's one-body intermediates are added here, as
-// k_onebody adds them, from the pair lists)
+// t_new = R / eps_ij^ab, mixing, and the energy partial of the item.  Bound by its
+// reads (48 bytes an amplitude in an S_z = 0 block, 32 elsewhere, 8 written).  The
+// item's amplitudes are loaded first; while they are on their way the energy
+// denominators and one-body intermediates of the item's rows and columns (a chunk
+// of consecutive amplitudes spans few of them) are formed in LDS.  OB: the
+// one-body intermediates come from the pair lists, else from k_onebody.
+constexpr int kUpRows = kElemChunk + 1;  // rows that a chunk of amplitudes can touch
 template <bool OB>
-__global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha, uint32_t mask, int n_items) {
-    __shared__ double sh[4];
+__device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int cur, double alpha, uint32_t mask,
+                                            double* rE, double* rX, double* cE, double* cX, double* sh) {
     const bool ring_on = (mask & (CCD_T_RING | CCD_T_QRING)) != 0;
-    const bool lad_on = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) != 0;
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
-        const Item ig = d.it_ue[bi];
-        if (ig.chan < 0) continue;
-        const int item = ig.chan, g = ig.start;
-        const Item it = d.it_elem[item];
-        const DevChan c = d.chans[it.chan];
-        const DevGroup G = d.groups[c.group];
-        const int nel = c.nhh * c.npp;
-        const bool act = d.active[G.p0 + g] != 0;
-        const bool lad = lad_on && c.sz == 0;
-        const int64_t T0 = G.t_base + g * G.n_amp + c.t_off;
+    const int item = ig.chan, g = ig.start;
+    const Item it = uni(d.it_elem[item]);
+    const DevChan c = uni(d.chans[it.chan]);
+    const DevGroup G = uni(d.groups[c.group]);
+    const int nhh = c.nhh, nel = nhh * c.npp, e1 = min(nel, it.start + kElemChunk);
+    const bool act = d.active[G.p0 + g] != 0;
+    const bool sz0 = c.sz == 0;
+    const bool lad = sz0 && (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) != 0;
+    const int64_t T0 = G.t_base + g * G.n_amp + c.t_off;
+    const double* tc = d.t[cur] + T0;
+    const double* vt = d.vt + T0;
+    const double* rm = d.rmm + T0;
+    const double2* zc = (const double2*)d.zc + T0;
+    double* tn = d.t[cur ^ 1] + T0;
+    const int r0 = it.start / nhh, nr = (e1 - 1) / nhh - r0 + 1;
+    constexpr int kPer = kElemChunk / 256;
+    double t[kPer], v[kPer], l[kPer];
+    double2 z[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        const int e = it.start + threadIdx.x + 256 * k;
+        t[k] = v[k] = l[k] = 0.0;
+        z[k] = make_double2(0.0, 0.0);
+        if (e < e1) {
+            t[k] = tc[e];
+            // <ab||ij> = 0 in S_z = +-1 blocks (two neutrons interact only in the
+            // spin singlet), so only S_z = 0 blocks read it
+            if (sz0) v[k] = vt[e];
+            if (act) {
+                if (lad) l[k] = rm[e];
+                if (ring_on) z[k] = zc[e];
+            }
+        }
+    }
+    __syncthreads();  // the previous item's reads of LDS are done
+    if (act) {
         const double* rowE = d.rowE + G.rowa_base + g * G.n_rows_all + c.rowa_off;
         const double* rowX = d.rowX + G.rowa_base + g * G.n_rows_all + c.rowa_off;
         const double* colE = d.colE + G.cola_base + g * G.n_cols_all + c.cola_off;
         const double* colX = d.colX + G.cola_base + g * G.n_cols_all + c.cola_off;
         const double* dc = d.dchi + G.eps_base + g * G.ns;
-        double es = 0.0;
-        for (int k = 0; k < kElemChunk / 256; k++) {
-            const int e = it.start + threadIdx.x + 256 * k;
-            if (e < nel && e < it.start + kElemChunk) {
-                const int64_t E = T0 + e;
-                // <ab||ij> = 0 in S_z = +-1 blocks (two neutrons interact only
-                // in the spin singlet), so only S_z = 0 blocks read it
-                const double tc = d.t[cur][E], v = c.sz == 0 ? d.vt[E] : 0.0;
-                double tm = tc;
-                if (act) {
-                    const int r = e / c.nhh, col = e - r * c.nhh;
-                    double R = v;
-                    if (lad) R += d.rmm[E];
-                    if (ring_on) R += ring_term(d, G, g, c.t_off + e);
-                    if constexpr (OB) {
-                        const int32_t ab = d.pp[c.pp_off + r], ij = d.hh[c.hh_off + col];
-                        R += ((dc[pa(ab)] + dc[pb(ab)]) - (dc[pa(ij)] + dc[pb(ij)])) * tc;
-                    } else {
-                        R += (rowX[r] - colX[col]) * tc;
-                    }
-                    tm = alpha * (R / (colE[col] - rowE[r])) + (1.0 - alpha) * tc;
-                }
-                d.t[cur ^ 1][E] = tm;
-                es += v * tm;
-            }
+        auto pair_sum = [&](int32_t p) { return dc[pa(p)] + dc[pb(p)]; };
+        for (int r = threadIdx.x; r < nr; r += 256) {
+            rE[r] = rowE[r0 + r];
+            if constexpr (OB) rX[r] = pair_sum(d.pp[c.pp_off + r0 + r]);
+            else rX[r] = rowX[r0 + r];
         }
-        const double s = block_sum256(es, sh);
-        if (threadIdx.x == 0) d.epart_elem[G.eelem_base + g * (G.elem_hi - G.elem_lo) + (item - G.elem_lo)] = s;
+        if ((int)threadIdx.x < nhh) {
+            cE[threadIdx.x] = colE[threadIdx.x];
+            if constexpr (OB) cX[threadIdx.x] = pair_sum(d.hh[c.hh_off + threadIdx.x]);
+            else cX[threadIdx.x] = colX[threadIdx.x];
+        }
+    }
+    __syncthreads();
+    double es = 0.0;
+    const float inv = 1.0f / (float)nhh;
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+        const int e = it.start + threadIdx.x + 256 * k;
+        if (e < e1) {
+            double tm = t[k];
+            if (act) {
+                // row and column of x = e - r0 nhh < kElemChunk + nhh: (x + 1/2) / nhh lies
+                // 1 / (2 nhh) >= 2^-7 from an integer
+                const int x = e - r0 * nhh, r = (int)(((float)x + 0.5f) * inv), col = x - r * nhh;
+                double R = v[k];
+                if (lad) R += l[k];
+                if (ring_on) R += z[k].x + z[k].y;
+                R += (rX[r] - cX[col]) * t[k];
+                tm = alpha * (R / (cE[col] - rE[r])) + (1.0 - alpha) * t[k];
+            }
+            tn[e] = tm;
+            es += v[k] * tm;
+        }
+    }
+    const double s = block_sum256(es, sh);
+    if (threadIdx.x == 0) d.epart_elem[G.eelem_base + g * (G.elem_hi - G.elem_lo) + (item - G.elem_lo)] = s;
+}
+template <bool OB>
+__global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha, uint32_t mask, int n_items) {
+    __shared__ double rE[kUpRows], rX[kUpRows], cE[kMaxHH], cX[kMaxHH];
+    __shared__ double sh[4];
+    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
+        const Item ig = uni(d.it_ue[bi]);
+        if (ig.chan >= 0) update_item<OB>(d, ig, cur, alpha, mask, rE, rX, cE, cX, sh);
     }
 }
 
