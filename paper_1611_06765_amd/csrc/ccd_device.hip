@@ -1260,6 +1260,7 @@ struct Front {
     int ns, n_small;    // blocks and items of the small pairs
     int ne;             // blocks of the energy step (0 or the number of problems)
     int small80;        // the order-80 bucket holds no pair beyond order 68
+    int mix;            // blocks among which the product items are spread
 };
 constexpr int kRing80M = 68;  // two blocks of LDS matrices of this order fit one compute unit
 template <int P>
@@ -1267,13 +1268,21 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
                                                             double tol_rel, int rule) {
     extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
     __shared__ int live_s;
-    int b = blockIdx.x;
     const int tid = threadIdx.x, w = tid >> 6;
-    if (b < f.nd) {
-        direct_block<P>(d, d.it_direct[b], cur, mask, (double*)dyn_lds, &live_s);
-        return;
+    // the product items spread evenly among the ring's, eight blocks (one per
+    // XCD) at a time
+    int b = blockIdx.x;
+    const int ud = f.nd >> 3, ut = f.mix >> 3, u = b >> 3;
+    if (u < ut) {
+        const int k0 = (int)((int64_t)u * ud / ut), k1 = (int)((int64_t)(u + 1) * ud / ut);
+        if (k1 > k0) {
+            direct_block<P>(d, d.it_direct[8 * k0 + (b & 7)], cur, mask, (double*)dyn_lds, &live_s);
+            return;
+        }
+        b -= 8 * k0;
+    } else {
+        b -= f.nd;
     }
-    b -= f.nd;
     if (b < f.nb[3]) {
         const Item it = d.it_ring_b[f.lo[3] + b];
         if (P != P_BF16 && f.small80) pair_body<P, 80, 8, kRing80M>(d, it, cur, mask, dyn_lds, tid);
@@ -2737,6 +2746,7 @@ static ccd_status launch_one_stream(ccd_ctx* c, const DevPtrs& d, int cur, uint3
         c->energy_pending = false;
         f.ne = (int)c->probs.size();
     }
+    f.mix = f.nd + f.nb[0] + f.nb[1] + f.nb[2] + f.nb[3] + f.ns;
     const int grid = f.nd + f.nb[0] + f.nb[1] + f.nb[2] + f.nb[3] + f.ns + f.ne;
     LAUNCH(F_DIRECT, k_front<P>, grid, kFrontThreads, front_lds<P>(c), d, cur, mask, f, c->pend_tol, c->pend_tol_rel,
            c->pend_rule);
