@@ -3,6 +3,10 @@
 //
 // One Jacobi sweep of eq. ccd3 in the intermediates form (sec. "Developing a
 // CCD code for infinite matter"), every term from the current amplitudes t:
+//   k_nm_ring     the ring over pairs {Q, -Q} of cross channels, gathered,
+//                 multiplied and stored to two ring slots per amplitude in LDS;
+//                 beyond 112 members of a cross channel the ring is channel
+//                 products instead (k_nm_gather, C_P and Z_Q below)
 //   k_nm_gather   T~_Q[(a,i)][(c,k)] = t_ik^ac for every cross channel Q
 //   k_nm_rowcol   row and column sums of t <ab||ij> per direct channel, from
 //   k_nm_colsum   chunks of whole rows (column parts added in chunk order)
@@ -173,7 +177,16 @@ struct NmLadItem {
     int32_t lad, start;            // channel entry; first momentum pair | 16-column tile << 20
 };
 
+// A pair {Q, P = -Q} of cross channels for the ring (k_nm_ring): nq and np members
+// at mem_q and mem_p, the position map [nq][np] of Q at map_off, Q's spin and
+// isospin (2 (s_p - s_h), 2 (t_p - t_h)).
+struct NmPair {
+    int64_t map_off;
+    int32_t nq, np, mem_q, mem_p, sigma, tau;
+};
+
 struct NmDev {
+    const NmPair* pairs;    // in the order of the launches, costliest first in each
     const int32_t* st;      // packed states
     const double* u;        // the four element tables
     const double* eps;
@@ -199,13 +212,14 @@ struct NmDev {
     double* tq;             // gathered T~_Q blocks
     double* cp;             // C_P blocks
     double* lad;            // ladder sums (t layout)
-    double* ring;           // four ring slots per amplitude
+    double* ring;           // ring slots per amplitude: two (pairs of cross channels) or four (channel products)
     double* rowsum;         // per global row: sum_cols t vt
     double* colsum;         // per global column: sum_rows t vt
     double* dchi;           // per state
     double* epart;
     double* ehist;          // [kNmHist]
     int32_t ns, nlut, n_items, n_tq;
+    int32_t by_pairs;       // the ring runs over pairs of cross channels
     int64_t n_amp;
 };
 
@@ -518,6 +532,271 @@ __global__ void __launch_bounds__(256) k_nm_gemm(NmDev d, int cur, uint32_t mask
     }
 }
 
+// ---- the ring over pairs of cross channels ------------------------------------
+// With A[u][x] = T~_Q = t_ik^ac ((a,i) member u of Q, (c,k) member x of P = -Q),
+// B[x][m] = <kl||cd> ((d,l) member m of Q) and V the <kb||cj> block of a channel,
+// the two ring terms of an amplitude that meet in the pair are
+//   Out = X A + A V_P,   X = A B + V_Q
+// (T~_P = A^T and the <kl||cd> block of P is B^T), three products of n^3 instead
+// of the four of the channel products, with no T~_Q, C_P or Z_Q in memory and one
+// store per position instead of two.
+//
+// All pairs are blocks of one launch of 1024 threads: a pair of order 65 .. 112 on
+// 14 waves (strip of 16 output rows w % 7, every second tile column), two pairs of
+// order 33 .. 64 on eight waves each, eight of order 17 .. 32 on two waves each, or
+// sixteen smaller ones on one wave each.  A stays in LDS; B and V_P are generated
+// in panels of 16 rows, X passes through LDS a column of tiles at a time, and the
+// accumulators of X and Out stay in registers.  The loops over panels run to the
+// size class's bound, so that the pairs of a block meet at the same barriers.
+//
+// An element needs one table entry besides the four constants of the pair (its
+// first momentum transfer is Q): an int8 dot product gives the entry's index and a
+// 16-entry table over the two holes' labels the class and sign.
+//
+// Measured (A=108, n^2<=20): 114 us, against 61 us of gathers and about 330 of the
+// 400 us of the two channel-product launches before (a sweep 551 -> 308 us).  With
+// one wave per strip and a launch per size class the same took 229 us: the 119
+// pairs beyond order 64 left half of the compute units idle for 114 us.  It is
+// bound by the scattered gathers and stores and, for the largest pairs, by the
+// chain of panels.
+constexpr int kNmRingMax = 112;    // largest order of a pair in LDS
+constexpr int kNmRingThreads = 1024;
+template <int NT> struct NmRing {
+    static constexpr int N16 = 16 * NT, ld = N16 + 1;
+    static constexpr int NW = NT == 7 ? 14 : NT == 4 ? 8 : NT == 2 ? 2 : 1;      // waves with products
+    static constexpr int groups = NT == 7 ? 1 : NT == 4 ? 2 : NT == 2 ? 8 : 16;  // pairs per block
+    static constexpr int threads = kNmRingThreads / groups;                      // threads per pair
+    static constexpr int CW = NW / NT, TPW = (NT + CW - 1) / CW;                 // waves per strip, tiles per wave
+    // doubles: A, then two panels [16][ld] or two columns of X tiles [NT][16][17]
+    static constexpr int pan = 16 * ld, xp = NT * 16 * 17;
+    static constexpr int buf = 2 * (pan > xp ? pan : xp);
+    static constexpr size_t bytes = (size_t)(N16 * ld + buf + 4) * 8 + 2 * N16 * sizeof(int4) + 3 * 16 * 4;
+    static constexpr size_t stride = (bytes + 15) & ~(size_t)15;
+};
+
+// the class code of an element from the labels of its four states: table k * nlut
+// | sign << 30, or -1
+__device__ __forceinline__ int nm_code(int nlut, int p, int q, int r, int s) {
+    int k = 0;
+    bool neg = false;
+    if (!nm_class(p, q, r, s, k, neg)) return -1;
+    return (k * nlut) | (neg ? 1 << 30 : 0);
+}
+
+template <int NT, typename Sync>
+__device__ __forceinline__ void nm_ring_pair(const NmDev& d, const NmPair& pr, bool on, int cur, uint32_t mask,
+                                             const double* u, char* lds, int tid, Sync sync) {
+    using R = NmRing<NT>;
+    constexpr int N16 = R::N16, ld = R::ld, TH = R::threads, CW = R::CW, TPW = R::TPW;
+    double* A = (double*)lds;
+    double* buf = A + N16 * ld;
+    double* uq = buf + R::buf;                  // the four tables' values at |Q|^2
+    int4* qs = (int4*)(uq + 4);                 // members of Q: hole, particle (packed n), |hole|^2 | |particle|^2 << 16, label
+    int4* ps = qs + N16;                        // members of P
+    int* code = (int*)(ps + N16);               // class codes of B, V_Q, V_P by the two holes' labels
+    const int lane = tid & 63, w = tid >> 6, c16 = lane & 15, kq = lane >> 4;
+    const int strip = w % NT, cg = w / NT;      // (waves past NW hold no strip)
+    const bool mm = w < R::NW;
+    const int nq = on ? pr.nq : 0, np = on ? pr.np : 0;
+    const bool quad = (mask & CCD_T_QRING) != 0, lin = (mask & CCD_T_RING) != 0;
+    const int32_t* map = d.pmap + pr.map_off;
+    const double* t = d.t[cur];
+    const int nlut = d.nlut;
+    // members
+    for (int e = tid; e < 2 * N16; e += TH) {
+        const int x = e < N16 ? e : e - N16;
+        const bool in = x < (e < N16 ? nq : np);
+        const int32_t m = in ? d.mem[(e < N16 ? pr.mem_q : pr.mem_p) + x] : 0;
+        const int32_t sp = in ? d.st[pr_a(m)] : 0, sh = in ? d.st[pr_b(m)] : 0;
+        const int32_t hp = sh & 0xffffff, pp = sp & 0xffffff;
+        const int h2 = __builtin_amdgcn_sdot4(hp, hp, 0, false), p2 = __builtin_amdgcn_sdot4(pp, pp, 0, false);
+        (e < N16 ? qs : ps)[x] = make_int4(hp, pp, h2 | (p2 << 16), nm_st(sh) | (nm_st(sp) << 4));
+    }
+    // A: the position map's entries, then the amplitudes, a round at a time
+    constexpr int J = (N16 * N16 + TH - 1) / TH, G = J < 16 ? J : 16;
+#pragma unroll 1
+    for (int j0 = 0; j0 < J; j0 += G) {
+        int32_t m[G];
+        double v[G];
+#pragma unroll
+        for (int j = 0; j < G; j++) {
+            const int e = tid + (j0 + j) * TH, r = e / N16, x = e - r * N16;
+            m[j] = (r < nq && x < np) ? map[r * np + x] : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < G; j++) v[j] = m[j] >= 0 ? t[m[j] >> 3] : 0.0;
+#pragma unroll
+        for (int j = 0; j < G; j++) {
+            const int e = tid + (j0 + j) * TH, r = e / N16, x = e - r * N16;
+            if (e < N16 * N16) A[r * ld + x] = (m[j] & 1) ? -v[j] : v[j];
+        }
+    }
+    // spin and isospin of a channel's particle from its hole's: the same, or the
+    // one that the channel's sigma or tau fixes
+    for (int e = tid; e < 48; e += TH) {
+        const int which = e >> 4, lx = (e >> 2) & 3, ly = e & 3;
+        auto part = [&](int h, int sg, int tu) {
+            const int sp = sg == 0 ? (h & 1) : (sg > 0), tp = tu == 0 ? (h >> 1) : (tu > 0);
+            return sp | (tp << 1);
+        };
+        const int sgn = which == 2 ? -1 : 1, sg = sgn * pr.sigma, tu = sgn * pr.tau;
+        // B: <kl||cd>, row (c, k) of P, column (d, l) of Q; V: <kb||cj> of two members
+        code[e] = which == 0 ? nm_code(nlut, lx, ly, part(lx, -pr.sigma, -pr.tau), part(ly, pr.sigma, pr.tau))
+                             : nm_code(nlut, lx, part(ly, sg, tu), part(lx, sg, tu), ly);
+    }
+    sync();
+    if (tid < 4) {
+        const int4 q0 = qs[0];
+        const int q2 = (q0.z & 0xffff) + (q0.z >> 16) - 2 * __builtin_amdgcn_sdot4(q0.x, q0.y, 0, false);
+        uq[tid] = nq > 0 ? u[tid * nlut + q2] : 0.0;
+    }
+    sync();
+    // an element: class code c, its second momentum transfer squared m
+    auto elem = [&](int c, int m) {
+        if (c < 0) return 0.0;
+        const int k = c & 0x3fffffff;
+        const int kk = (k >= nlut) + (k >= 2 * nlut) + (k >= 3 * nlut);
+        const double v = uq[kk] + u[k + m];
+        return c & (1 << 30) ? -v : v;
+    };
+    auto eB = [&](int x, int m) {  // |k - d|^2: hole of P's member, particle of Q's
+        const int4 X = ps[x], M = qs[m];
+        return elem(code[((X.w & 3) << 2) | (M.w & 3)],
+                    (X.z & 0xffff) + (M.z >> 16) - 2 * __builtin_amdgcn_sdot4(X.x, M.y, 0, false));
+    };
+    auto eV = [&](const int4* s, const int* cd, int x, int y) {  // |k - j|^2: the two holes
+        const int4 X = s[x], Y = s[y];
+        return elem(cd[((X.w & 3) << 2) | (Y.w & 3)],
+                    (X.z & 0xffff) + (Y.z & 0xffff) - 2 * __builtin_amdgcn_sdot4(X.x, Y.x, 0, false));
+    };
+    auto eVP = [&](int x, int y) { return eV(ps, code + 32, x, y); };
+    const int nt = (max(nq, np) + 15) >> 4;  // tiles in use
+    auto fill = [&](int p, auto el, int rows, int cols) {
+        double* P = buf + (p & 1) * R::pan;
+        for (int e = tid; e < 16 * N16; e += TH) {
+            const int r = e / N16, c = e - r * N16, x = 16 * p + r;
+            if (c < 16 * nt && 16 * p < rows) P[r * ld + c] = (x < rows && c < cols) ? el(x, c) : 0.0;
+        }
+    };
+    nm_d4 X[TPW], O[TPW];
+#pragma unroll
+    for (int j = 0; j < TPW; j++) X[j] = O[j] = nm_d4{0.0, 0.0, 0.0, 0.0};
+    // acc[j] += (rows of this wave's strip of A, columns of panel p) (panel, its tile column cg + CW j)
+    auto mul_panel = [&](int p, nm_d4* acc) {
+        if (!mm || strip >= nt) return;
+        const double* P = buf + (p & 1) * R::pan;
+        const int ks = min(16, np - 16 * p);
+#pragma unroll 2
+        for (int k = 0; k < ks; k += 4) {
+            const double a = A[(16 * strip + c16) * ld + 16 * p + k + kq];
+#pragma unroll
+            for (int j = 0; j < TPW; j++) {
+                const int tj = cg + CW * j;
+                if (tj < nt)
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, P[(k + kq) * ld + 16 * tj + c16], acc[j], 0, 0, 0);
+            }
+        }
+    };
+    // X = A B
+    if (quad) {
+        fill(0, eB, np, nq);
+        for (int p = 0; p < NT; p++) {
+            sync();
+            if (p + 1 < NT) fill(p + 1, eB, np, nq);
+            mul_panel(p, X);
+        }
+        sync();  // the last panel's readers are done
+    }
+    // Out = (X + V_Q) A, a column of X tiles at a time
+#pragma unroll
+    for (int j = 0; j < NT; j++) {
+        double* xp = buf + (j & 1) * R::xp;
+        if (mm && strip < nt && j < nt && j % CW == cg) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int x = 16 * strip + kq + 4 * i, y = 16 * j + c16;
+                double v = X[j / CW][i];
+                if (lin && x < nq && y < nq) v += eV(qs, code + 16, x, y);
+                xp[(strip * 16 + kq + 4 * i) * 17 + c16] = v;
+            }
+        }
+        sync();
+        if (mm && strip < nt && j < nt) {
+            const int ks = min(16, nq - 16 * j);
+            for (int k = 0; k < ks; k += 4) {
+                const double a = xp[(strip * 16 + c16) * 17 + k + kq];
+#pragma unroll
+                for (int q = 0; q < TPW; q++) {
+                    const int tj = cg + CW * q;
+                    if (tj < nt)
+                        O[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, A[(16 * j + k + kq) * ld + 16 * tj + c16], O[q], 0,
+                                                                    0, 0);
+                }
+            }
+        }
+    }
+    // Out += A V_P
+    if (lin) {
+        sync();  // the last column's readers are done
+        fill(0, eVP, np, np);
+        for (int p = 0; p < NT; p++) {
+            sync();
+            if (p + 1 < NT) fill(p + 1, eVP, np, np);
+            mul_panel(p, O);
+        }
+    }
+    // each position of the pair to its amplitude's slot: 2 e + [one pair of indices
+    // out of order], with that sign
+    if (!mm) return;
+#pragma unroll
+    for (int j = 0; j < TPW; j++) {
+        int32_t m[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int x = 16 * strip + kq + 4 * i, y = 16 * (cg + CW * j) + c16;
+            m[i] = (x < nq && y < np) ? map[x * np + y] : -1;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            if (m[i] >= 0) d.ring[2 * (int64_t)(m[i] >> 3) + (m[i] & 1)] = (m[i] & 1) ? -O[j][i] : O[j][i];
+    }
+}
+
+// blocks of a launch by size class (7, 4, 2, 1 tiles), the classes' pairs one after
+// another in the list
+struct NmRingLaunch {
+    int nb[4], n[4];
+    int u_off;  // byte offset of the element tables in LDS
+};
+template <int NT, typename Sync>
+__device__ __forceinline__ void nm_ring_block(const NmDev& d, int cur, uint32_t mask, const double* u, char* lds, int b,
+                                              int base, int n, Sync sync) {
+    using R = NmRing<NT>;
+    const int g = threadIdx.x / R::threads, k = b * R::groups + g;
+    const bool on = k < n;
+    const NmPair pr = d.pairs[base + (on ? k : n - 1)];
+    nm_ring_pair<NT>(d, pr, on, cur, mask, u, lds + g * R::stride, threadIdx.x % R::threads, sync);
+}
+__global__ void __launch_bounds__(kNmRingThreads) k_nm_ring(NmDev d, int cur, uint32_t mask, NmRingLaunch L) {
+    extern __shared__ __attribute__((aligned(16))) char nm_lds[];
+    double* u = (double*)(nm_lds + L.u_off);
+    for (int k = threadIdx.x; k < 4 * d.nlut; k += kNmRingThreads) u[k] = d.u[k];
+    __syncthreads();
+    auto block_sync = [] { __syncthreads(); };
+    // the LDS accesses of one wave complete in order; the fence keeps the compiler's order too
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    int b = blockIdx.x, base = 0;
+    if (b < L.nb[0]) return nm_ring_block<7>(d, cur, mask, u, nm_lds, b, base, L.n[0], block_sync);
+    b -= L.nb[0]; base += L.n[0];
+    if (b < L.nb[1]) return nm_ring_block<4>(d, cur, mask, u, nm_lds, b, base, L.n[1], block_sync);
+    b -= L.nb[1]; base += L.n[1];
+    if (b < L.nb[2]) return nm_ring_block<2>(d, cur, mask, u, nm_lds, b, base, L.n[2], block_sync);
+    b -= L.nb[2]; base += L.n[2];
+    nm_ring_block<1>(d, cur, mask, u, nm_lds, b, base, L.n[3], wave_sync);
+}
 
 // pp ladder over momentum pairs.  In a direct channel (K, S_z, T_z) the element
 // <ab||cd> = +-(U_k(|n_a - n_c|^2) + U_k(|n_a - n_d|^2)) depends on the row only
@@ -779,8 +1058,13 @@ __global__ void __launch_bounds__(256) k_nm_update(NmDev d, int cur, double alph
             double R = v;
             if (lad) R += d.lad[g];
             if (rng) {
-                const double* z = d.ring + 4 * g;
-                R += (z[0] + z[1]) + (z[2] + z[3]);
+                if (d.by_pairs) {
+                    const double2 z = ((const double2*)d.ring)[g];
+                    R += z.x + z.y;
+                } else {
+                    const double* z = d.ring + 4 * g;
+                    R += (z[0] + z[1]) + (z[2] + z[3]);
+                }
             }
             R += ((d.dchi[a] + d.dchi[b]) - (d.dchi[i] + d.dchi[j])) * told;
             const double den = d.eps[i] + d.eps[j] - d.eps[a] - d.eps[b];
@@ -842,6 +1126,10 @@ struct ccd_nm_ctx {
     std::vector<NmJob> jobs;
     std::vector<NmTile> tiles;
     int tiles_a = 0, tiles_b = 0;  // tiles of the first launch, then of the second
+    bool ring_pairs = false;       // the ring over pairs of cross channels (every order within LDS)
+    std::vector<NmPair> pairs;
+    NmRingLaunch ring{};           // its launch: pairs by size class
+    size_t ring_lds = 0;
     int64_t n_amp = 0, n_chh = 0, n_tq = 0, n_cp = 0;
     int n_rows = 0, n_cols = 0, max_hh = 0, max_pp = 0, max_ph = 0;
     double flops = 0.0, flops_a = 0.0;  // all products; those of the first launch
@@ -1219,14 +1507,23 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
     // {i, j}, {a, b}: (e << 3) | (slot << 1) | negative, slot = 2 [a > b] + [i > j],
     // negative when exactly one of the two pairs is out of order; -1 when
     // i = j or a = b
-    for (auto& q : c->ph) {
-        if (q.partner < 0) continue;
+    // Over pairs of cross channels only the map of the lower-numbered one is
+    // kept; the channel products keep every channel's T~_Q and C_P.
+    c->ring_pairs = c->max_ph <= kNmRingMax;
+    for (size_t qi = 0; qi < c->ph.size(); qi++) {
+        HPh& q = c->ph[qi];
+        // (a channel is never its own partner: the holes fill whole momenta, so Q != 0)
+        if (q.partner < 0 || (c->ring_pairs && q.partner <= (int)qi)) continue;
         const HPh& P = c->ph[q.partner];
-        q.tq_off = c->n_tq;
-        q.cp_off = c->n_cp;
         const int nQ = (int)q.mem.size(), nP = (int)P.mem.size();
-        c->n_tq += (int64_t)nQ * nP;
-        c->n_cp += (int64_t)nP * nP;
+        if (c->ring_pairs) {
+            c->pairs.push_back({(int64_t)c->pmap.size(), nQ, nP, q.mem_off, P.mem_off, q.sig, q.tau});
+        } else {
+            q.tq_off = c->n_tq;
+            q.cp_off = c->n_cp;
+            c->n_tq += (int64_t)nQ * nP;
+            c->n_cp += (int64_t)nP * nP;
+        }
         for (int u = 0; u < nQ; u++)
             for (int y = 0; y < nP; y++) {
                 const int a = pr_a(q.mem[u]), i = pr_b(q.mem[u]), b = pr_a(P.mem[y]), j = pr_b(P.mem[y]);
@@ -1247,6 +1544,24 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
                 const int neg = (a > b) != (i > j);
                 c->pmap.push_back((int32_t)((e << 3) | (slot << 1) | neg));
             }
+    }
+    {
+        auto cls = [](const NmPair& p) {
+            const int n = std::max(p.nq, p.np);
+            return n > 64 ? 0 : n > 32 ? 1 : n > 16 ? 2 : 3;
+        };
+        auto cost = [](const NmPair& p) { return (double)p.nq * p.np * (p.nq + p.np + 64); };
+        std::stable_sort(c->pairs.begin(), c->pairs.end(), [&](const NmPair& x, const NmPair& y) {
+            return cls(x) != cls(y) ? cls(x) < cls(y) : cost(x) > cost(y);
+        });
+        const int per[4] = {NmRing<7>::groups, NmRing<4>::groups, NmRing<2>::groups, NmRing<1>::groups};
+        const size_t lds[4] = {NmRing<7>::stride, NmRing<4>::stride, NmRing<2>::stride, NmRing<1>::stride};
+        for (const NmPair& p : c->pairs) c->ring.n[cls(p)]++;
+        for (int k = 0; k < 4; k++) {
+            c->ring.nb[k] = (c->ring.n[k] + per[k] - 1) / per[k];
+            if (c->ring.n[k] > 0) c->ring.u_off = std::max(c->ring.u_off, (int)(per[k] * lds[k]));
+        }
+        c->ring_lds = c->ring.u_off + 4 * (size_t)c->nlut * 8;
     }
     // products: launch 1 (chi_klij, C_P), launch 2 (ladders, ring Z)
     auto add_tiles = [&](const NmJob& J) {
@@ -1273,10 +1588,13 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         add_tiles(J);
         c->flops += 2.0 * C.nhh * C.nhh * C.npp;
     }
+    if (c->ring_pairs) c->flops_a = c->flops;
     for (auto& q : c->ph) {  // C_P = <kb||cj>_P + 1/2 Vbar T~_Q
         if (q.partner < 0) continue;
         const HPh& P = c->ph[q.partner];
         const int nQ = (int)q.mem.size(), nP = (int)P.mem.size();
+        c->flops += 2.0 * nP * nP * nQ;
+        if (c->ring_pairs) continue;
         NmJob J = blank();
         J.M = nP; J.N = nP; J.nseg = 1;
         J.seg[0].K = nQ; J.seg[0].amode = AM_GVBAR; J.seg[0].a_rows = P.mem_off; J.seg[0].a_cols = q.mem_off;
@@ -1285,10 +1603,9 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         J.cmode = CM_GVPH; J.cterm = CCD_T_RING; J.c_rows = P.mem_off; J.c_cols = P.mem_off;
         J.omode = OM_ROW; J.o_arr = ARR_CP; J.o_off = q.cp_off; J.ldo = nP;
         add_tiles(J);
-        c->flops += 2.0 * nP * nP * nQ;
     }
     c->tiles_a = (int)c->tiles.size();
-    c->flops_a = c->flops;
+    if (!c->ring_pairs) c->flops_a = c->flops;
     // the pp ladder over momentum pairs where the channel's elements allow it
     std::vector<std::pair<int, NmLadItem>> lit;
     std::vector<bool> by_pairs(c->ch.size(), false);
@@ -1334,6 +1651,8 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
             if (q.partner < 0) continue;
             const HPh& P = c->ph[q.partner];
             const int nQ = (int)q.mem.size(), nP = (int)P.mem.size();
+            c->flops += 2.0 * nQ * nP * nP;
+            if (c->ring_pairs) continue;
             NmJob J = blank();
             J.M = nQ; J.N = nP; J.nseg = 1;
             J.seg[0].K = nP; J.seg[0].amode = AM_ROW; J.seg[0].a_arr = ARR_TQ; J.seg[0].a_off = q.tq_off;
@@ -1342,7 +1661,6 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
             J.omode = OM_SCATTER; J.o_off = moff; J.ldo = nP;
             moff += (int64_t)nQ * nP;
             add_tiles(J);
-            c->flops += 2.0 * nQ * nP * nP;
         }
     }
     c->tiles_b = (int)c->tiles.size() - c->tiles_a;
@@ -1355,14 +1673,14 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
 
 // workspace regions, in order
 enum {
-    R_ST, R_U, R_EPS, R_HH, R_PP, R_MEM, R_PMAP, R_CH, R_ITEMS, R_JOBS, R_TILES, R_CSRP, R_CSRI, R_RCH,
+    R_PAIRS, R_ST, R_U, R_EPS, R_HH, R_PP, R_MEM, R_PMAP, R_CH, R_ITEMS, R_JOBS, R_TILES, R_CSRP, R_CSRI, R_RCH,
     R_LADD, R_LADLP, R_LADIT, R_RCIT, R_T0, R_T1, R_VT, R_CHH, R_TQ, R_CP, R_LAD, R_RING, R_ROWS, R_COLS, R_CPART,
     R_DCHI, R_EPART, R_EHIST, R_COUNT
 };
 
 void nm_layout(ccd_nm_ctx* c) {
     const size_t sz[R_COUNT] = {
-        4 * (size_t)c->ns, 8 * c->u.size(), 8 * (size_t)c->ns, 4 * c->hh_all.size(), 4 * c->pp_all.size(),
+        sizeof(NmPair) * c->pairs.size(), 4 * (size_t)c->ns, 8 * c->u.size(), 8 * (size_t)c->ns, 4 * c->hh_all.size(), 4 * c->pp_all.size(),
         4 * c->mem_all.size(), 4 * std::max<size_t>(1, c->pmap.size()), sizeof(NmChanD) * c->chd.size(),
         sizeof(NmItem) * c->items.size(), sizeof(NmJob) * c->jobs.size(), sizeof(NmTile) * c->tiles.size(),
         4 * c->csr_ptr.size(), 4 * std::max<size_t>(1, c->csr_idx.size()), 4 * c->row_chan.size(),
@@ -1370,7 +1688,7 @@ void nm_layout(ccd_nm_ctx* c) {
         sizeof(NmRcItem) * c->rcit.size(),
         8 * (size_t)c->n_amp, 8 * (size_t)c->n_amp, 8 * (size_t)c->n_amp, 8 * (size_t)std::max<int64_t>(1, c->n_chh),
         8 * (size_t)std::max<int64_t>(1, c->n_tq), 8 * (size_t)std::max<int64_t>(1, c->n_cp), 8 * (size_t)c->n_amp,
-        32 * (size_t)c->n_amp, 8 * (size_t)c->n_rows, 8 * (size_t)c->n_cols, 8 * (size_t)std::max<int64_t>(1, c->n_cpart),
+        (c->ring_pairs ? 16 : 32) * (size_t)c->n_amp, 8 * (size_t)c->n_rows, 8 * (size_t)c->n_cols, 8 * (size_t)std::max<int64_t>(1, c->n_cpart),
         8 * (size_t)c->ns,
         8 * c->items.size(), 8 * (size_t)kNmHist};
     c->region.clear();
@@ -1494,6 +1812,13 @@ ccd_status nm_harvest(ccd_nm_ctx* c) {
     return CCD_OK;
 }
 
+// LDS of a block of k_nm_ring at the largest cutoff
+constexpr int kNmRingLdsMax =
+    (int)std::max({NmRing<7>::groups * NmRing<7>::stride, NmRing<4>::groups * NmRing<4>::stride,
+                   NmRing<2>::groups * NmRing<2>::stride, NmRing<1>::groups * NmRing<1>::stride}) +
+    4 * (4 * kNmMaxNmax2 + 1) * 8;
+static_assert(kNmRingLdsMax <= 160 * 1024, "a block's pairs and tables fit the LDS of a compute unit");
+
 // one sweep from t[cur] into t[cur ^ 1]; the energy lands in ehist[slot]
 ccd_status nm_sweep(ccd_nm_ctx* c, double alpha, uint32_t mask, int slot) {
     NmDev& d = c->dev;
@@ -1520,6 +1845,11 @@ ccd_status nm_sweep(ccd_nm_ctx* c, double alpha, uint32_t mask, int slot) {
         // the pp sums of the channels with the pairs form, before the ladder jobs add the rest
         NmTimed tm(c, NF_LADPP);
         k_nm_ladpp<<<std::min<int>((int)c->ladit.size(), 4096), 256, 0, s>>>(d, cur, mask, (int)c->ladit.size());
+    }
+    if (c->ring_pairs && (mask & (CCD_T_RING | CCD_T_QRING))) {
+        const int* nb = c->ring.nb;
+        NmTimed tm(c, NF_GEMM2);
+        k_nm_ring<<<nb[0] + nb[1] + nb[2] + nb[3], kNmRingThreads, c->ring_lds, s>>>(d, cur, mask, c->ring);
     }
     if (c->tiles_b > 0) {
         NmTimed tm(c, NF_GEMM2);
@@ -1557,6 +1887,7 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
         return hipMemcpyAsync(at(r), src, c->region[r].second, hipMemcpyHostToDevice, c->stream);
     };
     const int32_t zero = -1;
+    if (!c->pairs.empty()) NM_TRY(up(R_PAIRS, c->pairs.data()));
     NM_TRY(up(R_ST, c->st.data()));
     NM_TRY(up(R_U, c->u.data()));
     NM_TRY(up(R_EPS, c->eps.data()));
@@ -1577,6 +1908,8 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
     if (!c->ladit.empty()) NM_TRY(up(R_LADIT, c->ladit.data()));
     NM_TRY(up(R_RCIT, c->rcit.data()));
     NmDev& d = c->dev;
+    d.pairs = (const NmPair*)at(R_PAIRS);
+    d.by_pairs = c->ring_pairs;
     d.st = (const int32_t*)at(R_ST);
     d.u = (const double*)at(R_U);
     d.eps = (const double*)at(R_EPS);
@@ -1615,6 +1948,8 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
     d.n_tq = (int32_t)c->n_tq;
     d.n_amp = c->n_amp;
     c->cur = 0;
+    if (c->ring_pairs)
+        NM_TRY(hipFuncSetAttribute((const void*)k_nm_ring, hipFuncAttributeMaxDynamicSharedMemorySize, kNmRingLdsMax));
     k_nm_init<<<std::min<int>((int)c->items.size(), 8192), 256, 0, c->stream>>>(d);
     NM_TRY(hipGetLastError());
     ccd_status st = nm_energy_now(c, 0, &c->emp2);

@@ -159,3 +159,20 @@ def test_snm_deterministic_bits():
     a = _ctx(28, 4, 0.1).iterate(mixing=0.7, max_iter=4)["history"]
     b = _ctx(28, 4, 0.1).iterate(mixing=0.7, max_iter=4)["history"]
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("A,n2,sweeps", [(4, 1, 2), (28, 4, 2), (76, 9, 1), (108, 9, 1), (132, 18, 1)])
+def test_ring_by_size_of_the_cross_channels(orc, A, n2, sweeps):
+    """Each size class of the ring's pairs of cross channels (up to 16, 32, 64
+    and 112 members) and the channel products beyond: the ring terms alone, both
+    and separately, then everything, against the oracle."""
+    c = _ctx(A, n2, 0.2)
+    for mask in {108: (20, 127), 132: (20,)}.get(A, (4, 16, 20, 127)):
+        c2 = _ctx(A, n2, 0.2)
+        o3 = orc.O3(orc.NM(A, n2, 0.2))
+        r = c2.iterate(mixing=0.7, max_iter=sweeps, terms=mask)
+        for s in range(sweeps):
+            assert _close(r["history"][s], o3.sweep(0.7, mask)), (mask, s)
+        assert _amplitudes_match(c2, o3), mask
+    lo, hi = {4: (1, 16), 28: (17, 32), 76: (33, 64), 108: (65, 112), 132: (113, 1000)}[A]
+    assert lo <= c.info()["max_ph"] <= hi
