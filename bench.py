@@ -68,17 +68,18 @@ def source_digest(path=KERNEL_SRC):
     removed, so that a comment-only edit keeps the counters valid and any code
     edit does not.  The set-up kernels (MBPT2 start, network warm start,
     features), which do not run in a sweep, and the host code after the device
-    code are left out."""
+    code are left out; the product item's header is put in front."""
     import hashlib
     import re
     src = open(path).read()
+    shared = open(os.path.join(os.path.dirname(path), "direct64.h")).read()
     a, b = src.find("\n// set-up kernels\n"), src.find("\n// sweep kernels\n")
     if 0 <= a < b:
         src = src[:a] + src[b:]
     h = src.find("\n// context\n")
     if h >= 0:
         src = src[:h]
-    src = re.sub(r"/\*.*?\*/", "", src, flags=re.S)
+    src = re.sub(r"/\*.*?\*/", "", shared + src, flags=re.S)
     src = re.sub(r"//[^\n]*", "", src)
     src = re.sub(r"\s+", " ", src).strip()
     return hashlib.sha256(src.encode()).hexdigest()
@@ -275,7 +276,7 @@ def snm_rate(ccd, stream, steps, warmup):
             "tflops": info["flops_per_sweep"] / (el / steps) / 1e12, "amplitudes": info["n_amplitudes"],
             "e_per_nucleon_after_mev": (er + ec) / 108, "sweeps_run": steps + warmup,
             "kernels": kernels,
-            "roofline": {"kernel": "k_nm_gemm (" + dom + ")", "bound": "mfma", "achieved": achieved,
+            "roofline": {"kernel": {"gemm_chi": "k_nm_ring", "ladder_pp": "k_nm_mid"}.get(dom, dom), "bound": "mfma", "achieved": achieved,
                          "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS,
                          "ms_per_launch": per_launch[dom], "flops_per_launch": kt[dom][2]}}
 

@@ -106,14 +106,19 @@ ccd_status ccd_nm_element(const ccd_nm_ctx* ctx, int32_t p, int32_t q, int32_t r
 ccd_status ccd_nm_last_ms(const ccd_nm_ctx* ctx, double* ms);
 /* Per-launch timing: while enabled every launch of a sweep is bracketed by two
  * HIP events on the context's stream.  ccd_nm_kernel_times returns, per kernel
- * family (CCD_NM_FAMILIES of them, named by ccd_nm_kernel_name: gather,
- * rowcol, dchi, gemm_chi (chi_klij and the ring's C_P), gemm_ladder_ring (the
- * hh ladder, the pp ladder of blocks without the momentum-pair form, and the
- * ring's Z_Q), update, energy, ladder_pp (the pp ladder as products over the
- * blocks' momentum pairs)), the summed milliseconds, the
- * launch count and the FP64 flops of one launch of that family (0 for the
- * non-product families), and optionally resets the sums.  Both synchronise the
- * stream. */
+ * family (CCD_NM_FAMILIES of them, named by ccd_nm_kernel_name), the summed
+ * milliseconds, the launch count and the FP64 flops of one launch of that family
+ * (0 for the non-product families), and optionally resets the sums.  A sweep of
+ * cross channels up to 112 members and at most 64 hole pairs per block is three
+ * launches: gemm_chi (chi_klij and the ring over pairs of cross channels; its
+ * blocks also add up the previous energy), ladder_pp (the pp ladder over the
+ * blocks' momentum pairs, to whose flops the hh ladder's, done in the same
+ * launch, are added under gemm_ladder_ring, and the one-body sums) and update.
+ * Larger systems launch gather, rowcol, dchi, gemm_chi (chi_klij and the ring's
+ * C_P, or without it the ring over pairs under gemm_ladder_ring),
+ * gemm_ladder_ring (the hh ladder, the pp ladder of blocks without the
+ * momentum-pair form, the ring's Z_Q), ladder_pp, update and energy.  Both calls
+ * synchronise the stream. */
 #define CCD_NM_FAMILIES 8
 ccd_status ccd_nm_set_timing(ccd_nm_ctx* ctx, int32_t enabled);
 ccd_status ccd_nm_kernel_times(ccd_nm_ctx* ctx, double* ms, int64_t* launches, double* flops, int32_t reset);

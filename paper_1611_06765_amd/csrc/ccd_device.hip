@@ -46,6 +46,7 @@
 #include <vector>
 
 #include "ccd_internal.h"
+#include "direct64.h"
 #include "mlp_net.h"
 #include "../../include/ccd_mlp.h"
 
@@ -199,19 +200,6 @@ __device__ __forceinline__ double vas_q(const double* __restrict__ lut, double w
     if (f == 0) return 0.0;
     double w = wr + lut[dist2(p, s)];
     return f > 0 ? w : -w;
-}
-
-// A descriptor that is the same in every lane, moved to scalar registers: a
-// kernel that loops over work items and stores in between cannot load it there
-// by itself, and then carries every field and address in vector registers.
-template <typename T>
-__device__ __forceinline__ T uni(const T& v) {
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    struct Words { int32_t w[sizeof(T) / 4]; };
-    Words x = __builtin_bit_cast(Words, v);
-#pragma unroll
-    for (size_t k = 0; k < sizeof(T) / 4; k++) x.w[k] = __builtin_amdgcn_readfirstlane(x.w[k]);
-    return __builtin_bit_cast(T, x);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -467,14 +455,6 @@ __device__ __forceinline__ void energy_of(const DevPtrs& d, int p, double tol, d
 // that product in FP64; summed from the staged chunk in the mixed modes).  Both
 // operands are amplitude-shaped blocks ([n_pp][n_hh] rows of <ab||ij> and t).
 // k_dsum adds the items' parts in item order.
-struct DirItem {
-    const double* t;
-    const double* vt;
-    double* rows;   // row sums of the channel
-    double* part;   // the item's part of chi_klij, [n_hh][n_hh]
-    double* colp;   // and of the column sums, [n_hh]
-    int nhh, k0, k1;
-};
 __device__ __forceinline__ DirItem dir_item(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int cur,
                                             int sub, int start) {
     DirItem r;
@@ -491,144 +471,8 @@ __device__ __forceinline__ DirItem dir_item(const DevPtrs& d, const DevChan& c, 
     return r;
 }
 
-// FP64, eight waves.  A chunk of whole rows (all 256 of an item where n_hh <= 16)
-// is one contiguous run of memory, at most 8 doubles of each operand per thread,
-// loaded one chunk ahead of the work and kept in LDS as it is, with row stride
-// n_hh: a product tile that reads past a row's end gets the next row's numbers,
-// which reach only outputs outside the block.  With at most four 16x16 output
-// tiles (n_hh <= 32) every wave computes all tiles over every eighth 4-row K step;
-// with more, wave w takes tiles w / 2, w / 2 + 4, ... over every second step.  The
-// partial tiles are added in LDS in wave order.  The item is a chain of loads,
-// barriers and short MFMA runs, so it is bound by latency: few and large chunks,
-// eight waves and four threads per row sum shorten that chain.
+// FP64: direct64 on eight waves
 constexpr int kDirThreads = 512;
-constexpr int kDirChunk = 4096;                      // doubles of a staged chunk
-constexpr int kDirBuf64 = kDirChunk + 64;            // and the last tile's overhang
-constexpr size_t kDirLds = 2 * (size_t)kDirBuf64 * 8;
-__device__ __forceinline__ void direct64(const DirItem& it, uint32_t mask, double* lds) {
-    double* vs = lds;
-    double* ts = lds + kDirBuf64;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int nhh = it.nhh, nt = (nhh + 15) >> 4, ntt = nt * nt;
-    const int crows = min(kDirSplit, (kDirChunk / nhh) & ~3);  // rows per staged chunk
-    const bool quad = (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0;
-    const bool split = ntt <= 4;
-    constexpr int kPer = kDirChunk / kDirThreads;
-    double vr[kPer] = {}, tr[kPer] = {};
-    auto load_chunk = [&](int r0) {
-        const int ne = min(crows, it.k1 - r0) * nhh;
-        const double* vp = it.vt + (int64_t)r0 * nhh;
-        const double* tp = it.t + (int64_t)r0 * nhh;
-#pragma unroll
-        for (int i = 0; i < kPer; i++)
-            if (kDirThreads * i < ne) {
-                const int e = min(tid + kDirThreads * i, ne - 1);
-                vr[i] = vp[e];
-                tr[i] = tp[e];
-            }
-    };
-    load_chunk(it.k0);
-    d4 acc[4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) acc[k] = d4{0, 0, 0, 0};
-    for (int r0 = it.k0; r0 < it.k1; r0 += crows) {
-        const int rc = min(crows, it.k1 - r0), rpad = (rc + 3) & ~3, ne = rc * nhh;
-        __syncthreads();  // the previous chunk's (or item's) reads are done
-#pragma unroll
-        for (int i = 0; i < kPer; i++)
-            if (kDirThreads * i < rpad * nhh) {  // zero in the rows up to the K step
-                const int e = tid + kDirThreads * i;
-                vs[e] = e < ne ? vr[i] : 0.0;
-                ts[e] = e < ne ? tr[i] : 0.0;
-            }
-        __syncthreads();
-        if (r0 + crows < it.k1) load_chunk(r0 + crows);
-        // row sums of t v (one-body particle terms): four threads per row
-        if (mask & CCD_T_QPART) {
-            for (int x = tid; x < 4 * rc; x += kDirThreads) {
-                const int o = (x >> 2) * nhh;
-                double sum = 0.0;
-#pragma unroll 2
-                for (int j = x & 3; j < nhh; j += 4) sum += ts[o + j] * vs[o + j];
-                sum += __shfl_xor(sum, 1);
-                sum += __shfl_xor(sum, 2);
-                if ((x & 3) == 0) it.rows[r0 + (x >> 2)] = sum;
-            }
-        }
-        if (quad) {
-            const int col = lane & 15, rq = lane >> 4;
-            if (nt == 1) {
-#pragma unroll 2
-                for (int kk = 4 * w; kk < rpad; kk += 32) {
-                    const int o = (kk + rq) * nhh + col;
-                    acc[0] = mfma64(vs[o], ts[o], acc[0]);
-                }
-            } else if (split) {
-#pragma unroll 2
-                for (int kk = 4 * w; kk < rpad; kk += 32) {
-                    const int o = (kk + rq) * nhh + col;
-                    const double a0 = vs[o], b0 = ts[o], a1 = vs[o + 16], b1 = ts[o + 16];
-                    acc[0] = mfma64(a0, b0, acc[0]);
-                    acc[1] = mfma64(a0, b1, acc[1]);
-                    acc[2] = mfma64(a1, b0, acc[2]);
-                    acc[3] = mfma64(a1, b1, acc[3]);
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const int tile = (w >> 1) + 4 * k;
-                    if (tile < ntt) {
-                        const double* vp = vs + rq * nhh + col + 16 * (tile / nt);
-                        const double* tp = ts + rq * nhh + col + 16 * (tile % nt);
-#pragma unroll 2
-                        for (int kk = 4 * (w & 1); kk < rpad; kk += 8)
-                            acc[k] = mfma64(vp[kk * nhh], tp[kk * nhh], acc[k]);
-                    }
-                }
-            }
-        }
-    }
-    if (!quad) return;
-    // add the waves' partial tiles in wave order: eight waves for each of at
-    // most four tiles, or two for each of up to sixteen
-    d4* red = (d4*)lds;  // split: [tile][wave][64], else [tile][64]
-    auto put = [&](const d4& sum, int ti, int tj) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int kl = ti * 16 + orow<P_F64>(lane, q), ij = tj * 16 + (lane & 15);
-            if (kl < nhh && ij < nhh) {
-                it.part[kl * nhh + ij] = sum[q];
-                if (kl == ij) it.colp[kl] = sum[q];
-            }
-        }
-    };
-    __syncthreads();
-    if (split) {
-#pragma unroll
-        for (int k = 0; k < 4; k++)
-            if (k < ntt) red[(k * 8 + w) * 64 + lane] = acc[k];
-        __syncthreads();
-        if (w < ntt) {
-            const d4* p = red + w * 8 * 64 + lane;
-            d4 sum = p[0];
-#pragma unroll 1
-            for (int q = 1; q < 8; q++) sum += p[q * 64];
-            put(sum, w / nt, w % nt);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int tile = (w >> 1) + 4 * k;
-            if (tile < ntt && (w & 1)) red[tile * 64 + lane] = acc[k];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const int tile = (w >> 1) + 4 * k;
-            if (tile < ntt && !(w & 1)) put(acc[k] + red[tile * 64 + lane], tile / nt, tile % nt);
-        }
-    }
-}
 
 // The mixed modes: FP64 in LDS, converted at the FP32 MFMA, on the first four
 // waves of the block.  The staging row stride follows the channel's tiles, so
@@ -788,7 +632,8 @@ __device__ __forceinline__ void direct_block(const DevPtrs& d, const Item it0, i
     __syncthreads();
     if (!*live_s) return;
     const DirItem di = dir_item(d, c, G, it.start, cur, it.chan, sub.start);
-    if constexpr (P == P_F64) direct64(di, mask, lds);
+    if constexpr (P == P_F64)
+        direct64<8>(di, (mask & CCD_T_QPART) != 0, (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0, lds);
     else direct32(di, mask, lds);
 }
 

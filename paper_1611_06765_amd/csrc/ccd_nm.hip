@@ -2,22 +2,27 @@
 // neutrons) on gfx950: host plan, kernels and the C ABI of include/ccd_nm.h.
 //
 // One Jacobi sweep of eq. ccd3 in the intermediates form (sec. "Developing a
-// CCD code for infinite matter"), every term from the current amplitudes t:
+// CCD code for infinite matter"), every term from the current amplitudes t, in
+// three launches:
 //   k_nm_ring     the ring over pairs {Q, -Q} of cross channels, gathered,
-//                 multiplied and stored to two ring slots per amplitude in LDS;
-//                 beyond 112 members of a cross channel the ring is channel
-//                 products instead (k_nm_gather, C_P and Z_Q below)
+//                 multiplied and stored to two ring slots per amplitude; the items
+//                 of 1/2 sum_cd <kl||cd> t_ij^cd with the row and column sums of
+//                 t <ab||ij>; the previous sweep's energy
+//   k_nm_mid      the ladders sum_{c<d} <ab||cd> t_ij^cd over momentum pairs and
+//                 sum_{k<l} t_kl^ab chi_klij, chi_klij added from the items' parts;
+//                 the one-body intermediates
+//   k_nm_update   R / eps_ij^ab with the one-body terms, mixing, energy parts
+// Beyond 112 members of a cross channel or 64 hole pairs of a block the parts are
+// launches of their own, on generic channel products:
 //   k_nm_gather   T~_Q[(a,i)][(c,k)] = t_ik^ac for every cross channel Q
 //   k_nm_rowcol   row and column sums of t <ab||ij> per direct channel, from
 //   k_nm_colsum   chunks of whole rows (column parts added in chunk order)
 //   k_nm_gemm     (launch 1) chi_klij = <kl||ij> + sum_{c<d} <kl||cd> t_ij^cd per
 //                 direct channel; C_P = <kb||cj>_P + 1/2 Vbar T~_Q per cross
 //                 channel (chi_kbcj of the ring of Q, P = -Q)
-//                 (launch 2) ladders sum_{c<d} <ab||cd> t_ij^cd +
-//                 sum_{k<l} t_kl^ab chi_klij per direct channel; the ring
-//                 Z_Q = T~_Q C_P per cross channel, scattered to the four ring
+//                 (launch 2) the hh ladder, added to k_nm_ladpp's pp ladder; the
+//                 ring Z_Q = T~_Q C_P per cross channel, scattered to the four ring
 //                 slots of the amplitudes it feeds
-//   k_nm_update   R / eps_ij^ab with the one-body terms, mixing, energy parts
 //   k_nm_energy   fixed-order energy sum
 // The products run on the FP64 16x16x4 MFMA over LDS-staged chunks; the
 // interaction is generated where a product reads it, from four tables of the
@@ -35,6 +40,7 @@
 #include <vector>
 
 #include "ccd_internal.h"
+#include "direct64.h"
 #include "../../include/ccd_nm.h"
 
 namespace {
@@ -123,6 +129,12 @@ struct NmChanD {
     int64_t t_off;
     int32_t nhh, npp, hh_off, pp_off, chh_off;
     int32_t rc_lo, rc_n;   // its row-chunk items of the row and column sums
+    int32_t part_off, colp_off, nsub;  // its product items' parts of chi_klij and of the column sums
+};
+
+// a product item: kDirSplit rows of a channel from row r0, the sub-th of it
+struct NmDirItem {
+    int32_t chan, r0, sub;
 };
 
 // a chunk of whole rows of a block for the row and column sums; its column
@@ -196,6 +208,10 @@ struct NmDev {
     const int32_t* pmap;    // ring position maps
     const NmChanD* ch;
     const NmItem* items;
+    const NmDirItem* dirit; // product items (three-launch sweep), longest first
+    const int2* cinfo;      // per global column: offset of its first part among the column parts; n_hh | parts << 16
+    double* dpart;          // the product items' parts of chi_klij
+    double* dcolp;          // and of the column sums
     const NmRcItem* rcit;   // row chunks of the row and column sums
     double* cpart;          // their column parts
     const NmJob* jobs;
@@ -284,22 +300,27 @@ __global__ void __launch_bounds__(256) k_nm_dot(NmDev d, int cur) {
 
 // energy (eq. ccdcorr with unordered pairs): the item parts in item order;
 // written to ehist[slot]
-__global__ void __launch_bounds__(256) k_nm_energy(NmDev d, int slot) {
-    __shared__ double sh[256];
-    // each thread sums a contiguous run of items in order, then a fixed tree
+__device__ __forceinline__ void nm_energy_block(const NmDev& d, int slot, double* sh) {
+    // each of 256 threads sums a contiguous run of items in order, then a fixed tree
     const int per = (d.n_items + 255) / 256;
-    double s = 0.0;
-    for (int k = 0; k < per; k++) {
-        const int w = threadIdx.x * per + k;
-        if (w < d.n_items) s += d.epart[w];
+    if (threadIdx.x < 256) {
+        double s = 0.0;
+        for (int k = 0; k < per; k++) {
+            const int w = threadIdx.x * per + k;
+            if (w < d.n_items) s += d.epart[w];
+        }
+        sh[threadIdx.x] = s;
     }
-    sh[threadIdx.x] = s;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if (threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
     if (threadIdx.x == 0) d.ehist[slot] = sh[0];
+}
+__global__ void __launch_bounds__(256) k_nm_energy(NmDev d, int slot) {
+    __shared__ double sh[256];
+    nm_energy_block(d, slot, sh);
 }
 
 // T~_Q[u][x] = t_ik^ac, (a,i) member u of Q, (c,k) member x of its partner;
@@ -381,19 +402,34 @@ __global__ void __launch_bounds__(256) k_nm_colsum(NmDev d, int n_rows, int n_co
 //   the rows holding b), chi_jj - f_jj = +1/2 sum_cdl <jl||cd> t_jl^cd = +(sum of
 //   the column sums of the columns holding j); one wave per state: lane l sums
 //   entries l, l + 64, ... of its CSR list, then a fixed butterfly over the lanes
+// (PARTS: a column's sum is added here from the product items' parts, in item order)
+template <bool PARTS>
+__device__ __forceinline__ void nm_dchi_state(const NmDev& d, uint32_t mask, int nh, int s, int lane) {
+    double acc = 0.0;
+    const bool hole = s < nh;
+    if (hole ? (mask & CCD_T_QHOLE) : (mask & CCD_T_QPART)) {
+        for (int k = d.csr_ptr[s] + lane; k < d.csr_ptr[s + 1]; k += 64) {
+            const int x = d.csr_idx[k];
+            if (!hole) {
+                acc += d.rowsum[x];
+            } else if constexpr (PARTS) {
+                const int2 ci = d.cinfo[x];
+                const int nhh = ci.y & 0xffff, n = ci.y >> 16;
+                double q = 0.0;
+                for (int i = 0; i < n; i++) q += d.dcolp[ci.x + i * nhh];
+                acc += q;
+            } else {
+                acc += d.colsum[x];
+            }
+        }
+    }
+    acc = nm_wave_sum(acc);
+    if (lane == 0) d.dchi[s] = hole ? acc : -acc;
+}
 __global__ void __launch_bounds__(256) k_nm_dchi(NmDev d, uint32_t mask, int nh) {
     const int lane = threadIdx.x & 63;
     const int wid = (blockIdx.x * 256 + threadIdx.x) >> 6, nw = (gridDim.x * 256) >> 6;
-    for (int s = wid; s < d.ns; s += nw) {
-        double acc = 0.0;
-        const bool hole = s < nh;
-        if (hole ? (mask & CCD_T_QHOLE) : (mask & CCD_T_QPART)) {
-            for (int k = d.csr_ptr[s] + lane; k < d.csr_ptr[s + 1]; k += 64)
-                acc += hole ? d.colsum[d.csr_idx[k]] : d.rowsum[d.csr_idx[k]];
-        }
-        acc = nm_wave_sum(acc);
-        if (lane == 0) d.dchi[s] = hole ? acc : -acc;
-    }
+    for (int s = wid; s < d.ns; s += nw) nm_dchi_state<false>(d, mask, nh, s, lane);
 }
 
 // ---- the channel products ---------------------------------------------------
@@ -767,6 +803,8 @@ __device__ __forceinline__ void nm_ring_pair(const NmDev& d, const NmPair& pr, b
 struct NmRingLaunch {
     int nb[4], n[4];
     int u_off;  // byte offset of the element tables in LDS
+    int nd;     // blocks of product items, after the ring's (three-launch sweep)
+    int slot;   // >= 0: one more block, the previous sweep's energy into this slot
 };
 template <int NT, typename Sync>
 __device__ __forceinline__ void nm_ring_block(const NmDev& d, int cur, uint32_t mask, const double* u, char* lds, int b,
@@ -795,7 +833,24 @@ __global__ void __launch_bounds__(kNmRingThreads) k_nm_ring(NmDev d, int cur, ui
     b -= L.nb[1]; base += L.n[1];
     if (b < L.nb[2]) return nm_ring_block<2>(d, cur, mask, u, nm_lds, b, base, L.n[2], block_sync);
     b -= L.nb[2]; base += L.n[2];
-    nm_ring_block<1>(d, cur, mask, u, nm_lds, b, base, L.n[3], wave_sync);
+    if (b < L.nb[3]) return nm_ring_block<1>(d, cur, mask, u, nm_lds, b, base, L.n[3], wave_sync);
+    b -= L.nb[3];
+    if (b < L.nd) {
+        const NmDirItem it = ccd::uni(d.dirit[b]);
+        const NmChanD C = ccd::uni(d.ch[it.chan]);
+        ccd::DirItem di;
+        di.t = d.t[cur] + C.t_off;
+        di.vt = d.vt + C.t_off;
+        di.rows = d.rowsum + C.pp_off;
+        di.part = d.dpart + C.part_off + (int64_t)it.sub * C.nhh * C.nhh;
+        di.colp = d.dcolp + C.colp_off + (int64_t)it.sub * C.nhh;
+        di.nhh = C.nhh;
+        di.k0 = it.r0;
+        di.k1 = min(C.npp, it.r0 + ccd::kDirSplit);
+        ccd::direct64<16>(di, (mask & CCD_T_QPART) != 0, (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0, (double*)nm_lds);
+        return;
+    }
+    nm_energy_block(d, L.slot, (double*)nm_lds);
 }
 
 // pp ladder over momentum pairs.  In a direct channel (K, S_z, T_z) the element
@@ -822,10 +877,12 @@ constexpr int kNmLadRows = 64;   // row momentum pairs per work item
 __device__ __forceinline__ double nm_mfma4(double a, double b, double c) {
     return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
+// chiS (three-launch sweep): the hh ladder sum_{k<l} t_kl^ab chi_klij is added
+// per row from chi_klij of the item's columns, [k l][16] in LDS
 template <int NG, int ND, int NK>
 __device__ __forceinline__ void nm_ladpp_item(const NmDev& d, const NmLadD& L, const NmChanD& C, int cur, int r0,
                                               int ct, bool pp_on, const double* lutS, double* tks,
-                                              int4 (*cvi)[kNmKP], int (*cvj)[kNmKP], int4* prs) {
+                                              int4 (*cvi)[kNmKP], int (*cvj)[kNmKP], int4* prs, const double* chiS) {
     constexpr int S = 8;  // bytes per table entry
     constexpr int NA = ND * NK == 1 ? 2 : 1;  // independent accumulators per product
     const char* lutB = (const char*)lutS;
@@ -970,15 +1027,12 @@ __device__ __forceinline__ void nm_ladpp_item(const NmDev& d, const NmLadD& L, c
     // the four rows of the lane's output pair, each with its combination
     const int4 ro = prs[16 * w + orow4];
     const int rows[4] = {ro.x, ro.y, ro.z, ro.w};
-    double* lad = d.lad + C.t_off;
+    double out[4][NG];
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-        if (rows[r] < 0) continue;
         const int rc = L.rec[r];
 #pragma unroll
         for (int q = 0; q < NG; q++) {
-            const int cc = ct * 16 + 4 * q + bj;
-            if (cc >= nhh) continue;
             double v = 0.0;
 #pragma unroll
             for (int j = 0; j < ND; j++) {
@@ -993,26 +1047,64 @@ __device__ __forceinline__ void nm_ladpp_item(const NmDev& d, const NmLadD& L, c
                 if (cf == 1) v += u;
                 else if (cf == 2) v -= u;
             }
-            lad[(int64_t)rows[r] * nhh + cc] = pp_on ? v : 0.0;
+            out[r][q] = pp_on ? v : 0.0;
         }
     }
+    if (chiS) {
+        const int4 ra = prs[16 * w + (lane & 15)];
+        const int arow[4] = {ra.x, ra.y, ra.z, ra.w};
+        for (int k0 = 0; k0 < nhh; k0 += 4) {
+            const int kl = k0 + (lane >> 4);
+            double bb[NG], a[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) a[r] = (arow[r] >= 0 && kl < nhh) ? tcur[(int64_t)arow[r] * nhh + kl] : 0.0;
+#pragma unroll
+            for (int q = 0; q < NG; q++)
+                bb[q] = (kl < nhh && ct * 16 + 4 * q + bj < nhh) ? chiS[16 * kl + 4 * q + bj] : 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+#pragma unroll
+                for (int q = 0; q < NG; q++) out[r][q] = nm_mfma4(a[r], bb[q], out[r][q]);
+        }
+    }
+    double* lad = d.lad + C.t_off;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int q = 0; q < NG; q++) {
+            const int cc = ct * 16 + 4 * q + bj;
+            if (rows[r] >= 0 && cc < nhh) lad[(int64_t)rows[r] * nhh + cc] = out[r][q];
+        }
 }
 
 template <int ND, int NK>
 __device__ __forceinline__ void nm_ladpp_ng(const NmDev& d, const NmLadD& L, const NmChanD& C, int cur, int r0,
                                             int ct, bool pp_on, double* lutS, double* tks, int4 (*cvi)[kNmKP],
-                                            int (*cvj)[kNmKP], int4* prs) {
+                                            int (*cvj)[kNmKP], int4* prs, const double* chiS) {
     const int ng = min(4, (min(16, C.nhh - 16 * ct) + 3) >> 2);
     switch (ng) {
-        case 1: nm_ladpp_item<1, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs); break;
-        case 2: nm_ladpp_item<2, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs); break;
-        case 3: nm_ladpp_item<3, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs); break;
-        default: nm_ladpp_item<4, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs); break;
+        case 1: nm_ladpp_item<1, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs, chiS); break;
+        case 2: nm_ladpp_item<2, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs, chiS); break;
+        case 3: nm_ladpp_item<3, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs, chiS); break;
+        default: nm_ladpp_item<4, ND, NK>(d, L, C, cur, r0, ct, pp_on, lutS, tks, cvi, cvj, prs, chiS); break;
     }
 }
 
-// one work item (channel, 64 row momentum pairs, 16 columns) per workgroup
-// iteration; the four class tables are staged once per workgroup
+// one work item (channel, 64 row momentum pairs, 16 columns)
+__device__ __forceinline__ void nm_lad_run(const NmDev& d, const NmLadItem it, int cur, bool pp, double* lutS,
+                                           double* tks, int4 (*cvi)[kNmKP], int (*cvj)[kNmKP], int4* prs,
+                                           const double* chiS) {
+    const NmLadD& L = d.ladd[it.lad];
+    const NmChanD C = ccd::uni(d.ch[L.chan]);
+    const int r0 = it.start & 0xfffff, ct = it.start >> 20;
+    if (L.nd == 2 && L.nk == 2) nm_ladpp_ng<2, 2>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs, chiS);
+    else if (L.nd == 2 && L.nk == 1) nm_ladpp_ng<2, 1>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs, chiS);
+    else if (L.nd == 1 && L.nk == 2) nm_ladpp_ng<1, 2>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs, chiS);
+    else if (L.nd == 1) nm_ladpp_ng<1, 1>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs, chiS);
+    else nm_ladpp_ng<1, 1>(d, L, C, cur, r0, ct, false, lutS, tks, cvi, cvj, prs, chiS);  // no element: zeros
+}
+
+// the four class tables are staged once per workgroup
 __global__ void __launch_bounds__(256, 2) k_nm_ladpp(NmDev d, int cur, uint32_t mask, int n_items) {
     __shared__ double lutS[4 * (4 * kNmMaxNmax2 + 1)];
     __shared__ __attribute__((aligned(16))) double tks[2 * kNmKP * 16];
@@ -1021,56 +1113,119 @@ __global__ void __launch_bounds__(256, 2) k_nm_ladpp(NmDev d, int cur, uint32_t 
     __shared__ int4 prs[kNmLadRows];
     for (int k = threadIdx.x; k < 4 * d.nlut; k += 256) lutS[k] = d.u[k];
     const bool pp = (mask & CCD_T_PP) != 0;
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
-        const NmLadItem it = d.ladit[bi];
-        const NmLadD& L = d.ladd[it.lad];
-        const NmChanD C = d.ch[L.chan];
-        const int r0 = it.start & 0xfffff, ct = it.start >> 20;
-        if (L.nd == 2 && L.nk == 2) nm_ladpp_ng<2, 2>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs);
-        else if (L.nd == 2 && L.nk == 1) nm_ladpp_ng<2, 1>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs);
-        else if (L.nd == 1 && L.nk == 2) nm_ladpp_ng<1, 2>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs);
-        else if (L.nd == 1) nm_ladpp_ng<1, 1>(d, L, C, cur, r0, ct, pp, lutS, tks, cvi, cvj, prs);
-        else nm_ladpp_ng<1, 1>(d, L, C, cur, r0, ct, false, lutS, tks, cvi, cvj, prs);  // no element: zeros
+    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x)
+        nm_lad_run(d, ccd::uni(d.ladit[bi]), cur, pp, lutS, tks, cvi, cvj, prs, nullptr);
+}
+
+// the second launch of the three-launch sweep: a ladder item per block, both
+// ladders, with chi_klij = <kl||ij> + the product items' parts (in item order) of
+// the item's columns formed in LDS; then (blocks nl, ...) the one-body items, four
+// states each.  In place of the chi_klij and hh products, the row and column sums,
+// the one-body launch and the energy launch (us a sweep: A=108, n^2<=20 308 -> 210,
+// n^2<=12 143 -> 94; A=28, n^2<=20 139 -> 63, n^2<=4 60 -> 33; A=4, n^2<=4 44 -> 22).
+constexpr int kNmFastHH = 64;  // hole pairs of a channel in the three-launch sweep
+__global__ void __launch_bounds__(256, 2) k_nm_mid(NmDev d, int cur, uint32_t mask, int nl, int nh) {
+    __shared__ double lutS[4 * (4 * kNmMaxNmax2 + 1)];
+    __shared__ __attribute__((aligned(16))) double tks[2 * kNmKP * 16];
+    __shared__ int4 cvi[2][kNmKP];
+    __shared__ int cvj[2][kNmKP];
+    __shared__ int4 prs[kNmLadRows];
+    __shared__ double chiS[kNmFastHH * 16];
+    if ((int)blockIdx.x >= nl) {
+        const int s = 4 * (blockIdx.x - nl) + (threadIdx.x >> 6);
+        if (s < d.ns) nm_dchi_state<true>(d, mask, nh, s, threadIdx.x & 63);
+        return;
     }
+    const NmLadItem it = ccd::uni(d.ladit[blockIdx.x]);
+    for (int k = threadIdx.x; k < 4 * d.nlut; k += 256) lutS[k] = d.u[k];
+    const bool hh = (mask & (CCD_T_HH | CCD_T_QHH)) != 0;
+    if (hh) {
+        const NmChanD C = ccd::uni(d.ch[d.ladd[it.lad].chan]);
+        const int ct = it.start >> 20;
+        for (int e = threadIdx.x; e < 16 * C.nhh; e += 256) {
+            const int kl = e >> 4, ij = 16 * ct + (e & 15);
+            if (ij >= C.nhh) continue;
+            double q = 0.0;
+            if (mask & CCD_T_QHH)
+                for (int s = 0; s < C.nsub; s++) q += d.dpart[C.part_off + ((int64_t)s * C.nhh + kl) * C.nhh + ij];
+            if (mask & CCD_T_HH) {
+                const int32_t R = d.hh[C.hh_off + kl], H = d.hh[C.hh_off + ij];
+                q += nm_vas(d.u, d.nlut, d.st[pr_a(R)], d.st[pr_b(R)], d.st[pr_a(H)], d.st[pr_b(H)]);
+            }
+            chiS[e] = q;
+        }
+    }
+    // (the item's own barriers come before its reads of lutS and chiS)
+    nm_lad_run(d, it, cur, (mask & CCD_T_PP) != 0, lutS, tks, cvi, cvj, prs, hh ? chiS : nullptr);
 }
 
 // R = <ab||ij> + ladder sums + ring slots + (dchi_a + dchi_b - dchi_i - dchi_j) t,
-// t_new = R / eps_ij^ab, t <- alpha t_new + (1 - alpha) t, energy parts
+// t_new = R / eps_ij^ab, t <- alpha t_new + (1 - alpha) t, energy parts.  The
+// item's amplitudes are loaded first; the Fock energies and one-body intermediates
+// of its rows and columns are added in LDS meanwhile.  Bound by its reads.
 __global__ void __launch_bounds__(256) k_nm_update(NmDev d, int cur, double alpha, uint32_t mask) {
     __shared__ double sh[4];
+    __shared__ double rE[kNmChunk + 1], rX[kNmChunk + 1], cE[kNmChunk], cX[kNmChunk];
     const double* t = d.t[cur];
     double* tn = d.t[cur ^ 1];
     const bool lad = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) != 0;
     const bool rng = (mask & (CCD_T_RING | CCD_T_QRING)) != 0;
+    constexpr int kPer = kNmChunk / 256;
     for (int w = blockIdx.x; w < d.n_items; w += gridDim.x) {
-        const NmItem it = d.items[w];
-        const NmChanD C = d.ch[it.chan];
-        const int64_t n = (int64_t)C.nhh * C.npp;
-        double acc = 0.0;
-        for (int k = threadIdx.x; k < kNmChunk; k += 256) {
-            const int64_t e = (int64_t)it.start + k;
-            if (e >= n) continue;
-            const int r = (int)(e / C.nhh), c = (int)(e - (int64_t)r * C.nhh);
-            const int32_t P = d.pp[C.pp_off + r], H = d.hh[C.hh_off + c];
-            const int a = pr_a(P), b = pr_b(P), i = pr_a(H), j = pr_b(H);
+        const NmItem it = ccd::uni(d.items[w]);
+        const NmChanD C = ccd::uni(d.ch[it.chan]);
+        const int nhh = C.nhh, e1 = (int)min((int64_t)nhh * C.npp, (int64_t)it.start + kNmChunk);
+        const int r0 = it.start / nhh, nr = (e1 - 1) / nhh - r0 + 1;
+        double told[kPer], v[kPer], l[kPer], z[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            const int e = it.start + threadIdx.x + 256 * k;
+            told[k] = v[k] = l[k] = z[k] = 0.0;
+            if (e >= e1) continue;
             const int64_t g = C.t_off + e;
-            const double told = t[g], v = d.vt[g];
-            double R = v;
-            if (lad) R += d.lad[g];
+            told[k] = t[g];
+            v[k] = d.vt[g];
+            if (lad) l[k] = d.lad[g];
             if (rng) {
                 if (d.by_pairs) {
-                    const double2 z = ((const double2*)d.ring)[g];
-                    R += z.x + z.y;
+                    const double2 x = ((const double2*)d.ring)[g];
+                    z[k] = x.x + x.y;
                 } else {
-                    const double* z = d.ring + 4 * g;
-                    R += (z[0] + z[1]) + (z[2] + z[3]);
+                    const double* x = d.ring + 4 * g;
+                    z[k] = (x[0] + x[1]) + (x[2] + x[3]);
                 }
             }
-            R += ((d.dchi[a] + d.dchi[b]) - (d.dchi[i] + d.dchi[j])) * told;
-            const double den = d.eps[i] + d.eps[j] - d.eps[a] - d.eps[b];
-            const double x = alpha * (R / den) + (1.0 - alpha) * told;
-            tn[g] = x;
-            acc += v * x;
+        }
+        __syncthreads();  // the previous item's reads of LDS are done
+        // columns of a block wider than the chunk: from the chunk's first column on
+        const int c0 = nhh > kNmChunk ? it.start - r0 * nhh : 0;
+        auto sum = [&](const double* x, int32_t p) { return x[pr_a(p)] + x[pr_b(p)]; };
+        for (int r = threadIdx.x; r < nr; r += 256) {
+            const int32_t P = d.pp[C.pp_off + r0 + r];
+            rE[r] = sum(d.eps, P);
+            rX[r] = sum(d.dchi, P);
+        }
+        for (int q = threadIdx.x; q < min(nhh, kNmChunk); q += 256) {
+            const int32_t H = d.hh[C.hh_off + (c0 + q) % nhh];
+            cE[q] = sum(d.eps, H);
+            cX[q] = sum(d.dchi, H);
+        }
+        __syncthreads();
+        double acc = 0.0;
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            const int e = it.start + threadIdx.x + 256 * k;
+            if (e >= e1) continue;
+            const int x = e - r0 * nhh, r = x / nhh;
+            int q = x - r * nhh - c0;
+            if (q < 0) q += nhh;
+            double R = v[k];
+            if (lad) R += l[k];
+            if (rng) R += z[k];
+            R += (rX[r] - cX[q]) * told[k];
+            const double y = alpha * (R / (cE[q] - rE[r])) + (1.0 - alpha) * told[k];
+            tn[C.t_off + e] = y;
+            acc += v[k] * y;
         }
         acc = nm_block_sum(acc, sh);
         if (threadIdx.x == 0) d.epart[w] = acc;
@@ -1120,6 +1275,14 @@ struct ccd_nm_ctx {
     std::vector<HPh> ph;
     std::vector<int32_t> hh_all, pp_all, mem_all, pmap, csr_ptr, csr_idx, row_chan;
     std::vector<NmChanD> chd;
+    // the three-launch sweep: cross channels and hole pairs within its limits and
+    // every pp ladder over momentum pairs
+    bool fast = false;
+    std::vector<NmDirItem> dirit;
+    std::vector<int32_t> cinfo;
+    int64_t n_dpart = 0, n_dcolp = 0;
+    bool energy_pending = false;   // the last sweep's energy step is left to the next first launch
+    int pend_slot = 0;
     std::vector<NmItem> items;
     std::vector<NmRcItem> rcit;
     int64_t n_cpart = 0;
@@ -1442,6 +1605,18 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
             }
         }
         d.rc_n = (int32_t)c->rcit.size() - d.rc_lo;
+        d.part_off = (int32_t)c->n_dpart;
+        d.colp_off = (int32_t)c->n_dcolp;
+        d.nsub = 0;
+        for (int r0 = 0; r0 < d.npp; r0 += ccd::kDirSplit) {
+            c->dirit.push_back({(int32_t)k, r0, d.nsub++});
+            c->n_dpart += (int64_t)d.nhh * d.nhh;
+            c->n_dcolp += d.nhh;
+        }
+        for (int q = 0; q < d.nhh; q++) {
+            c->cinfo.push_back(d.colp_off + q);
+            c->cinfo.push_back(d.nhh | (d.nsub << 16));
+        }
         c->chd.push_back(d);
         for (int64_t s0 = 0; s0 < (int64_t)d.nhh * d.npp; s0 += kNmChunk) c->items.push_back({(int32_t)k, (int32_t)s0});
     }
@@ -1588,7 +1763,7 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         add_tiles(J);
         c->flops += 2.0 * C.nhh * C.nhh * C.npp;
     }
-    if (c->ring_pairs) c->flops_a = c->flops;
+    const double flops_chi = c->flops;
     for (auto& q : c->ph) {  // C_P = <kb||cj>_P + 1/2 Vbar T~_Q
         if (q.partner < 0) continue;
         const HPh& P = c->ph[q.partner];
@@ -1605,7 +1780,7 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         add_tiles(J);
     }
     c->tiles_a = (int)c->tiles.size();
-    if (!c->ring_pairs) c->flops_a = c->flops;
+    c->flops_a = c->ring_pairs ? flops_chi : c->flops;
     // the pp ladder over momentum pairs where the channel's elements allow it
     std::vector<std::pair<int, NmLadItem>> lit;
     std::vector<bool> by_pairs(c->ch.size(), false);
@@ -1630,6 +1805,23 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
                                                const std::pair<int, NmLadItem>& y) { return x.first > y.first; });
     for (auto& e : lit) c->ladit.push_back(e.second);
     c->ladlp = std::move(lpall);
+    c->fast = c->ring_pairs && c->max_hh <= kNmFastHH && c->n_dpart < ((int64_t)1 << 31) &&
+              std::find(by_pairs.begin(), by_pairs.end(), false) == by_pairs.end();
+    if (c->fast) {
+        auto cost = [&](const NmDirItem& x) {
+            const int nt = (c->chd[x.chan].nhh + 15) / 16;
+            return std::min(ccd::kDirSplit, c->chd[x.chan].npp - x.r0) * nt * nt;
+        };
+        std::stable_sort(c->dirit.begin(), c->dirit.end(),
+                         [&](const NmDirItem& x, const NmDirItem& y) { return cost(x) > cost(y); });
+        c->ring.u_off = std::max(c->ring.u_off, (int)((ccd::kDirLds + 15) & ~(size_t)15));
+        c->ring_lds = c->ring.u_off + 4 * (size_t)c->nlut * 8;
+    } else {
+        c->dirit.clear();
+        c->cinfo.clear();
+        c->n_dpart = c->n_dcolp = 0;
+    }
+    double flops_hh = 0.0;
     for (size_t k = 0; k < c->ch.size(); k++) {  // ladders (the pp part here only without the pairs form)
         const NmChanD& C = c->chd[k];
         NmJob J = blank();
@@ -1644,6 +1836,7 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         J.omode = by_pairs[k] ? OM_ROW_ADD : OM_ROW; J.o_arr = ARR_LAD; J.o_off = C.t_off; J.ldo = C.nhh;
         add_tiles(J);
         c->flops += (by_pairs[k] ? 0.0 : 2.0 * C.npp * C.npp * C.nhh) + 2.0 * C.npp * C.nhh * C.nhh;
+        flops_hh += 2.0 * C.npp * C.nhh * C.nhh;
     }
     {
         int64_t moff = 0;
@@ -1664,6 +1857,7 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         }
     }
     c->tiles_b = (int)c->tiles.size() - c->tiles_a;
+    if (c->fast) c->flops_a = c->flops - flops_hh;  // the first launch's: chi_klij and the ring
     if (c->n_tq >= ((int64_t)1 << 31) || c->n_cp >= ((int64_t)1 << 40)) {
         ccd::set_error("ccd_nm_build: ring blocks beyond 2^31 entries");
         return CCD_EINVAL;
@@ -1673,14 +1867,15 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
 
 // workspace regions, in order
 enum {
-    R_PAIRS, R_ST, R_U, R_EPS, R_HH, R_PP, R_MEM, R_PMAP, R_CH, R_ITEMS, R_JOBS, R_TILES, R_CSRP, R_CSRI, R_RCH,
+    R_PAIRS, R_DIRIT, R_CINFO, R_DPART, R_DCOLP, R_ST, R_U, R_EPS, R_HH, R_PP, R_MEM, R_PMAP, R_CH, R_ITEMS, R_JOBS, R_TILES, R_CSRP, R_CSRI, R_RCH,
     R_LADD, R_LADLP, R_LADIT, R_RCIT, R_T0, R_T1, R_VT, R_CHH, R_TQ, R_CP, R_LAD, R_RING, R_ROWS, R_COLS, R_CPART,
     R_DCHI, R_EPART, R_EHIST, R_COUNT
 };
 
 void nm_layout(ccd_nm_ctx* c) {
     const size_t sz[R_COUNT] = {
-        sizeof(NmPair) * c->pairs.size(), 4 * (size_t)c->ns, 8 * c->u.size(), 8 * (size_t)c->ns, 4 * c->hh_all.size(), 4 * c->pp_all.size(),
+        sizeof(NmPair) * c->pairs.size(), sizeof(NmDirItem) * c->dirit.size(), 4 * c->cinfo.size(),
+        8 * (size_t)c->n_dpart, 8 * (size_t)c->n_dcolp, 4 * (size_t)c->ns, 8 * c->u.size(), 8 * (size_t)c->ns, 4 * c->hh_all.size(), 4 * c->pp_all.size(),
         4 * c->mem_all.size(), 4 * std::max<size_t>(1, c->pmap.size()), sizeof(NmChanD) * c->chd.size(),
         sizeof(NmItem) * c->items.size(), sizeof(NmJob) * c->jobs.size(), sizeof(NmTile) * c->tiles.size(),
         4 * c->csr_ptr.size(), 4 * std::max<size_t>(1, c->csr_idx.size()), 4 * c->row_chan.size(),
@@ -1819,11 +2014,52 @@ constexpr int kNmRingLdsMax =
     4 * (4 * kNmMaxNmax2 + 1) * 8;
 static_assert(kNmRingLdsMax <= 160 * 1024, "a block's pairs and tables fit the LDS of a compute unit");
 
-// one sweep from t[cur] into t[cur ^ 1]; the energy lands in ehist[slot]
+// the energy step left over from the previous sweep, as its own launch
+ccd_status nm_flush_energy(ccd_nm_ctx* c) {
+    if (!c->energy_pending) return CCD_OK;
+    c->energy_pending = false;
+    NmTimed tm(c, NF_ENERGY);
+    k_nm_energy<<<1, 256, 0, c->stream>>>(c->dev, c->pend_slot);
+    NM_TRY(hipGetLastError());
+    return CCD_OK;
+}
+
+// one sweep from t[cur] into t[cur ^ 1]; the energy lands in ehist[slot] (in the
+// three-launch sweep with the next sweep or nm_flush_energy)
 ccd_status nm_sweep(ccd_nm_ctx* c, double alpha, uint32_t mask, int slot) {
     NmDev& d = c->dev;
     hipStream_t s = c->stream;
     const int cur = c->cur;
+    if (c->fast) {
+        // three launches: the ring, the chi_klij product items and the previous
+        // sweep's energy; the ladders and the one-body items; the update
+        NmRingLaunch L = c->ring;
+        if (!(mask & (CCD_T_RING | CCD_T_QRING))) {
+            L.nb[0] = L.nb[1] = L.nb[2] = L.nb[3] = 0;
+        }
+        L.nd = (mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) ? (int)c->dirit.size() : 0;
+        L.slot = c->energy_pending ? c->pend_slot : -1;
+        const int grid = L.nb[0] + L.nb[1] + L.nb[2] + L.nb[3] + L.nd + (c->energy_pending ? 1 : 0);
+        c->energy_pending = false;
+        if (grid > 0) {
+            NmTimed tm(c, NF_GEMM1);
+            k_nm_ring<<<grid, kNmRingThreads, c->ring_lds, s>>>(d, cur, mask, L);
+        }
+        {
+            const int nl = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) ? (int)c->ladit.size() : 0;
+            NmTimed tm(c, NF_LADPP);
+            k_nm_mid<<<nl + (c->ns + 3) / 4, 256, 0, s>>>(d, cur, mask, nl, c->nh);
+        }
+        {
+            NmTimed tm(c, NF_UPDATE);
+            k_nm_update<<<std::min<int>((int)c->items.size(), 8192), 256, 0, s>>>(d, cur, alpha, mask);
+        }
+        c->energy_pending = true;
+        c->pend_slot = slot;
+        NM_TRY(hipGetLastError());
+        c->cur ^= 1;
+        return CCD_OK;
+    }
     if (d.n_tq > 0) {
         NmTimed tm(c, NF_GATHER);
         k_nm_gather<<<nm_grid(d.n_tq, 256), 256, 0, s>>>(d, cur);
@@ -1888,6 +2124,8 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
     };
     const int32_t zero = -1;
     if (!c->pairs.empty()) NM_TRY(up(R_PAIRS, c->pairs.data()));
+    if (!c->dirit.empty()) NM_TRY(up(R_DIRIT, c->dirit.data()));
+    if (!c->cinfo.empty()) NM_TRY(up(R_CINFO, c->cinfo.data()));
     NM_TRY(up(R_ST, c->st.data()));
     NM_TRY(up(R_U, c->u.data()));
     NM_TRY(up(R_EPS, c->eps.data()));
@@ -1909,6 +2147,10 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
     NM_TRY(up(R_RCIT, c->rcit.data()));
     NmDev& d = c->dev;
     d.pairs = (const NmPair*)at(R_PAIRS);
+    d.dirit = (const NmDirItem*)at(R_DIRIT);
+    d.cinfo = (const int2*)at(R_CINFO);
+    d.dpart = (double*)at(R_DPART);
+    d.dcolp = (double*)at(R_DCOLP);
     d.by_pairs = c->ring_pairs;
     d.st = (const int32_t*)at(R_ST);
     d.u = (const double*)at(R_U);
@@ -1987,6 +2229,13 @@ extern "C" ccd_status ccd_nm_iterate(ccd_nm_ctx* c, const ccd_solver_opts* o, in
         NM_TRY(hipEventRecord(c->ev0, c->stream));
         for (int k = 0; k < chunk; k++) {
             ccd_status st = nm_sweep(c, o->mixing, o->terms, k);
+            if (st != CCD_OK) {
+                c->energy_pending = false;
+                return st;
+            }
+        }
+        {
+            ccd_status st = nm_flush_energy(c);
             if (st != CCD_OK) return st;
         }
         NM_TRY(hipEventRecord(c->ev1, c->stream));
