@@ -276,11 +276,14 @@ ccd_status ccd_measure_ceilings(void* dev_buf, size_t bytes, void* hip_stream, d
  * 1/2 sum_ij <ij||ij>, the MBPT2 start (eq. ccdGuess), then Jacobi sweeps of
  * eq. ccd3 with the terms opts->terms (all eight = CCD_T_ALL), linear mixing
  * opts->mixing, stop when |dE_n - dE_(n-1)| < tol + tol_rel |dE_n| (FP64; the
- * other options are ignored).  One GPU thread per ordered amplitude: cost
- * O(n_h^4 n_p^4) per sweep, a validation path, not the fast one.  2 <= n <= 48.
+ * other options are ignored).  A sweep goes through the two-body and one-body
+ * intermediates, O(n_h^2 n_p^4 + n_h^3 n_p^3 + n_h^4 n_p^2), in one block for
+ * n <= 11: a validation path, not the fast one.  2 <= n <= 48.
  * dev_work: ccd_dense_workspace_size bytes of caller-owned device memory,
- * 256-byte aligned.  Outputs are host pointers (nullable; e_hist: max_iter
- * doubles, NAN past the last sweep).  Synchronises hip_stream once per sweep.
+ * 256-byte aligned; an area that holds the elements, two sets of amplitudes and
+ * one energy per 256 of them is enough for sweeps of O(n_h^4 n_p^4).  Outputs are
+ * host pointers (nullable; e_hist: max_iter doubles, NAN past the last sweep).
+ * Synchronises hip_stream once per launch of up to 64 sweeps.
  * Returns CCD_OK, CCD_NOT_CONVERGED, CCD_DIVERGED, CCD_EINVAL (also when a hole
  * is not below every particle in Fock energy), CCD_EHIP. */
 ccd_status ccd_dense_workspace_size(int32_t n, int32_t n_holes, size_t* bytes);
@@ -299,7 +302,7 @@ ccd_status ccd_dense_solve(const double* h, const double* v, int32_t n, int32_t 
  * every byte it reads before reading it, so no clearing is needed, but calls
  * that overlap on one GPU (other host threads, other streams) race and must
  * be serialised by the caller.  Errors: as ccd_dense_solve, and CCD_EINVAL
- * when ccd_dense_workspace_size(n, n_holes) exceeds CCD_DENSE_STATIC_BYTES
+ * when the area without intermediates exceeds CCD_DENSE_STATIC_BYTES
  * (for example n = 28 with 4 holes fits; n = 40 does not). */
 #define CCD_DENSE_STATIC_BYTES (8u << 20)
 ccd_status ccd_dense_solve_static(const double* h, const double* v, int32_t n, int32_t n_holes,

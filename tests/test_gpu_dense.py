@@ -68,3 +68,40 @@ def test_plane_waves_dense_larger_basis(orc):
     assert r["e_mbpt2"] == pytest.approx(o.emp2, rel=1e-12)
     for s in range(3):
         assert r["history"][s] == pytest.approx(o.sweep(0.8), rel=1e-11)
+
+
+def _random_hamiltonian(n, seed=5):
+    """One-body levels one apart and weak random antisymmetrised elements, without
+    any symmetry that would hide a wrong index."""
+    v = np.random.default_rng(seed).normal(size=(n,) * 4) * 0.02 / n
+    v = v - v.transpose(1, 0, 2, 3)
+    v = v - v.transpose(0, 1, 3, 2)
+    return np.arange(n, dtype=float), v + v.transpose(2, 3, 0, 1)
+
+
+@pytest.mark.parametrize("n, nh", [(2, 1), (7, 3), (8, 7), (11, 5), (12, 5), (13, 12), (17, 3)])
+@pytest.mark.parametrize("mask", [2, 9, 16, 32, 64, 127])
+def test_sweeps_in_one_block_by_launches_and_without_intermediates(orc, n, nh, mask):
+    """Model spaces on both sides of the largest that one block holds (11 states),
+    with the advertised work area and with one that has no room for intermediates:
+    every sweep's energy equals the oracle's and does not depend on the area."""
+    import ctypes as C
+    import torch
+    h, v = _random_hamiltonian(n)
+    o = orc.O1(h, v, nh)
+    ref = [o.sweep(0.8, mask) for _ in range(5)]
+    r = ccd.dense_solve(h, v, nh, mixing=0.8, tol=0.0, max_iter=5, terms=mask)
+    m = (nh * (n - nh)) ** 2
+    up = lambda x: -(-x // 256) * 256  # noqa: E731
+    small = up(8 * n ** 4) + up(8 * n) + 2 * up(8 * m) + up(8 * -(-m // 256))
+    work = torch.empty(small, dtype=torch.uint8, device="cuda")
+    hist = np.zeros(5)
+    opt = ccd.ccd_solver_opts()
+    opt.mixing, opt.tol, opt.max_iter, opt.terms = 0.8, 0.0, 5, mask
+    st = ccd._lib.ccd_dense_solve(ccd._dptr(h), ccd._dptr(v), n, nh, C.byref(opt), C.c_void_p(work.data_ptr()), small,
+                                  C.c_void_p(torch.cuda.current_stream().cuda_stream), None, None, None, None,
+                                  ccd._dptr(hist))
+    assert st == ccd.CCD_OK
+    for s in range(5):
+        assert r["history"][s] == pytest.approx(ref[s], rel=RTOL, abs=1e-15), s
+        assert hist[s] == pytest.approx(ref[s], rel=RTOL, abs=1e-15), s
