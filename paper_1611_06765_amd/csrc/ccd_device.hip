@@ -141,6 +141,9 @@ struct DevPtrs {
     const int4* lpinfo;      // per momentum pair {p, q} of an S_z = 0 block: (p as int8 x, y, z, 0;
                              // |p|^2 | |q|^2 << 10; row of (p up, q down); row of (p down, q up)), -1 = none
     const Item* it_ue;       // (elementwise item, problem in group): the update
+    const Item* cl_items;    // the lists by problem, their runs (ccd_ctx), and those of the live problems
+    const int32_t* cl_run;
+    Item* lists;
     double* t[2];
     double* vt;              // <ab||ij>
     double* chh;
@@ -156,11 +159,18 @@ struct DevPtrs {
     double* epart_elem;
     double* ecorr;
     double* eprev;
-    int32_t* active;
+    int32_t* active;         // per problem: 1 iterating; 0 stopped; -1 stopped, and both amplitude buffers hold t
     int32_t* sweeps;
     double* ehist;           // per problem: energies of the last kHistCap sweeps (ring)
     double* dprev;           // per problem: |dE| of the previous sweep (0 = none yet)
     int32_t* streak;         // per problem: consecutive sweeps that passed the tail test
+};
+
+// lists of a sweep on one stream; kListRing + b: ring items of size bucket b
+enum { kListDirect = 0, kListSmall, kListRing, kListLadder = kListRing + 4, kListOneBody, kListUpdate, kLists };
+struct SweepLists {
+    int n[kLists] = {0};
+    int ring_lo[4] = {0};
 };
 
 constexpr int kHistCap = 64;  // sweeps between two host reads of the energy history
@@ -422,11 +432,17 @@ __device__ __forceinline__ void energy_of(const DevPtrs& d, int p, double tol, d
     const DevGroup G = d.groups[d.pgrp[p]];
     const int g = d.pgi[p], n = G.elem_hi - G.elem_lo;
     const double* part = d.epart_elem + G.eelem_base + g * n;
+    // (only this block writes the flag, after the barriers of block_sum256)
+    if (d.active[p] <= 0) {
+        // stopped: the update of the sweep just run copied t to the other buffer
+        if (threadIdx.x == 0) d.active[p] = -1;
+        return;
+    }
     double s = 0.0;
     if (threadIdx.x < 256)
         for (int x = threadIdx.x; x < n; x += 256) s += part[x];
     double e = block_sum256(s, sh);
-    if (threadIdx.x == 0 && d.active[p]) {
+    if (threadIdx.x == 0) {
         double old = d.ecorr[p];
         d.eprev[p] = old;
         d.ecorr[p] = e;
@@ -628,7 +644,7 @@ __device__ __forceinline__ void direct_block(const DevPtrs& d, const Item it0, i
     // launch may clear it meanwhile, and waves that read it at different
     // times would otherwise take different paths through the barriers below
     __syncthreads();  // the previous item's readers of live_s are done
-    if (threadIdx.x == 0) *live_s = d.active[G.p0 + it.start];
+    if (threadIdx.x == 0) *live_s = d.active[G.p0 + it.start] > 0;
     __syncthreads();
     if (!*live_s) return;
     const DirItem di = dir_item(d, c, G, it.start, cur, it.chan, sub.start);
@@ -660,7 +676,7 @@ __global__ void __launch_bounds__(256) k_dsum(DevPtrs d, uint32_t mask, int n_it
         const DevChan c = d.chans[it.chan];
         const DevGroup G = d.groups[c.group];
         const int g = it.start;
-        if (!d.active[G.p0 + g]) continue;
+        if (d.active[G.p0 + g] <= 0) continue;
         const int nhh = c.nhh, nsub = c.dsub_n;
         const double* part = d.dpart + G.dpart_base + (int64_t)g * G.n_dpart + c.dpart_off;
         const double* colp = d.dcolp + G.dcolp_base + (int64_t)g * G.n_dcolp + c.dcolp_off;
@@ -700,7 +716,7 @@ __device__ __forceinline__ void dchi_item(const DevPtrs& d, const Item it, uint3
     const int s = (it.start & 0xffff) + w, g = it.start >> 16;  // state of this wave, problem
     if (s >= G.ns) return;
     const int x0 = d.csr_ptr[G.csr_off + s], x1 = d.csr_ptr[G.csr_off + s + 1];
-    if (!d.active[G.p0 + g]) return;
+    if (d.active[G.p0 + g] <= 0) return;
     const double* rows = d.rowsum + G.rows_base + g * G.n_rows;
     const double* cols = d.colsum + G.cols_base + g * G.n_cols;
     double acc = 0.0;
@@ -772,7 +788,7 @@ __device__ __forceinline__ bool pair_ctx(const DevPtrs& d, const Item it, int cu
     memP = q.pmem_off;
     lut_off = G.lut_base + g * G.nlut;
     nlut = G.nlut;
-    return d.active[G.p0 + g] != 0;
+    return d.active[G.p0 + g] > 0;
 }
 
 // stage the (p, h) states of both member lists and the problem's W/2 table
@@ -924,7 +940,7 @@ __host__ __device__ constexpr size_t pair_mat_off(int n16) {
 // kept in LDS, M a multiple of 4 and no smaller than either size of the pair.
 template <int P, int N16, int NW, int M = N16>
 __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int cur, uint32_t mask, char* lds,
-                                          int tid) {
+                                          int tid, int* live_s, int waves) {
     using E = typename std::conditional<P == P_F64, double, typename std::conditional<P == P_F32, float, __bf16>::type>::type;
     using AT = typename AccT<P>::T;
     constexpr int n16 = N16, nt = N16 / 16, ntt = nt * nt, TPW = (ntt + NW - 1) / NW;
@@ -935,9 +951,12 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
     PairCtx r;
     r.nq = 0; r.np = 0; r.self = false; r.map = nullptr; r.t = nullptr; r.zc = nullptr; r.zs = nullptr;
     int32_t memQ = 0, memP = 0, lo = 0, nlut = 0;
-    // every wave reaches every barrier below; only the work is guarded by live
+    // every wave reaches every barrier below; only the work is guarded by live.  An
+    // energy block of this launch may clear the flag meanwhile: waves that read it
+    // at different times leave values that the update of a stopped problem skips
     const bool live = it.chan >= 0 && pair_ctx(d, it, cur, r, memQ, memP, lo, nlut);
     const int lane = tid & 63, w = tid >> 6;
+    if (lane == 0) live_s[threadIdx.x >> 6] = live;
     double* lutS = (double*)lds;
     int32_t* qs = (int32_t*)(lutS + kMaxLut);
     int32_t* ps = qs + 2 * N16;
@@ -961,6 +980,9 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
         }
     }
     __syncthreads();
+    int any = 0;
+    for (int k = 0; k < waves; k++) any |= live_s[k];
+    if (!any) return;  // all of the block's items belong to stopped problems
     // W(|Q|^2)/2, the first table entry of every element of the pair (member 0
     // of Q: hole qs[1], particle qs[0])
     const double wq = live ? lutS[dist2(qs[1], qs[0])] : 0.0;
@@ -1063,6 +1085,7 @@ template <int P>
 __global__ void __launch_bounds__(256) k_ringp_small(DevPtrs d, int cur, uint32_t mask, int n_items) {
     constexpr size_t per = (pair_lds<P>(16) + 15) & ~(size_t)15;
     __shared__ __attribute__((aligned(16))) char lds[4 * per];
+    __shared__ int live_s[4];
     const int w = threadIdx.x >> 6;
     const int nb = (n_items + 3) / 4;
     for (int bi = blockIdx.x; bi < nb; bi += gridDim.x) {
@@ -1070,7 +1093,7 @@ __global__ void __launch_bounds__(256) k_ringp_small(DevPtrs d, int cur, uint32_
         Item it = d.it_ring_s[min(idx, n_items - 1)];
         if (idx >= n_items) it.chan = -1;
         __syncthreads();  // the previous item's reads of LDS are done
-        pair_body<P, 16, 1>(d, it, cur, mask, lds + w * per, threadIdx.x & 63);
+        pair_body<P, 16, 1>(d, it, cur, mask, lds + w * per, threadIdx.x & 63, live_s, 4);
     }
 }
 
@@ -1078,9 +1101,10 @@ __global__ void __launch_bounds__(256) k_ringp_small(DevPtrs d, int cur, uint32_
 template <int P, int N16, int NW>
 __global__ void __launch_bounds__(64 * NW) k_ringp(DevPtrs d, int cur, uint32_t mask, int base, int n_items) {
     extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
+    __shared__ int live_s[NW];
     for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
         __syncthreads();  // the previous item's reads of LDS are done
-        pair_body<P, N16, NW>(d, d.it_ring_b[base + bi], cur, mask, dyn_lds, threadIdx.x);
+        pair_body<P, N16, NW>(d, d.it_ring_b[base + bi], cur, mask, dyn_lds, threadIdx.x, live_s, NW);
     }
 }
 
@@ -1112,7 +1136,8 @@ template <int P>
 __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, uint32_t mask, Front f, double tol,
                                                             double tol_rel, int rule) {
     extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
-    __shared__ int live_s;
+    constexpr int kW = kFrontThreads / 64;
+    __shared__ __attribute__((aligned(16))) int live_s[kW];
     const int tid = threadIdx.x, w = tid >> 6;
     // the product items spread evenly among the ring's, eight blocks (one per
     // XCD) at a time
@@ -1121,7 +1146,7 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
     if (u < ut) {
         const int k0 = (int)((int64_t)u * ud / ut), k1 = (int)((int64_t)(u + 1) * ud / ut);
         if (k1 > k0) {
-            direct_block<P>(d, d.it_direct[8 * k0 + (b & 7)], cur, mask, (double*)dyn_lds, &live_s);
+            direct_block<P>(d, d.it_direct[8 * k0 + (b & 7)], cur, mask, (double*)dyn_lds, live_s);
             return;
         }
         b -= 8 * k0;
@@ -1130,18 +1155,18 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
     }
     if (b < f.nb[3]) {
         const Item it = d.it_ring_b[f.lo[3] + b];
-        if (P != P_BF16 && f.small80) pair_body<P, 80, 8, kRing80M>(d, it, cur, mask, dyn_lds, tid);
-        else pair_body<P, 80, 8>(d, it, cur, mask, dyn_lds, tid);
+        if (P != P_BF16 && f.small80) pair_body<P, 80, 8, kRing80M>(d, it, cur, mask, dyn_lds, tid, live_s, kW);
+        else pair_body<P, 80, 8>(d, it, cur, mask, dyn_lds, tid, live_s, kW);
         return;
     }
     b -= f.nb[3];
     if (b < f.nb[2]) {
-        pair_body<P, 64, 8>(d, d.it_ring_b[f.lo[2] + b], cur, mask, dyn_lds, tid);
+        pair_body<P, 64, 8>(d, d.it_ring_b[f.lo[2] + b], cur, mask, dyn_lds, tid, live_s, kW);
         return;
     }
     b -= f.nb[2];
     if (b < f.nb[1]) {
-        pair_body<P, 48, 8>(d, d.it_ring_b[f.lo[1] + b], cur, mask, dyn_lds, tid);
+        pair_body<P, 48, 8>(d, d.it_ring_b[f.lo[1] + b], cur, mask, dyn_lds, tid, live_s, kW);
         return;
     }
     b -= f.nb[1];
@@ -1150,7 +1175,8 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
         const int idx = 16 * (b >> 3) + (b & 7) + 8 * (w >> 2);
         Item it = d.it_ring_b[f.lo[0] + min(idx, f.n32 - 1)];
         if (idx >= f.n32) it.chan = -1;
-        pair_body<P, 32, 4>(d, it, cur, mask, dyn_lds + (w >> 2) * ((pair_lds<P>(32) + 15) & ~(size_t)15), tid & 255);
+        pair_body<P, 32, 4>(d, it, cur, mask, dyn_lds + (w >> 2) * ((pair_lds<P>(32) + 15) & ~(size_t)15), tid & 255,
+                            live_s, kW);
         return;
     }
     b -= f.nb[0];
@@ -1160,7 +1186,7 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
         const int unit = 16 * (b >> 3) + (b & 7) + 8 * (w >> 2), idx = 4 * unit + (w & 3);
         Item it = d.it_ring_s[min(idx, f.n_small - 1)];
         if (idx >= f.n_small) it.chan = -1;
-        pair_body<P, 16, 1>(d, it, cur, mask, dyn_lds + w * per, tid & 63);
+        pair_body<P, 16, 1>(d, it, cur, mask, dyn_lds + w * per, tid & 63, live_s, kW);
         return;
     }
     b -= f.ns;
@@ -1173,7 +1199,7 @@ __global__ void __launch_bounds__(256) k_onebody(DevPtrs d) {
     const int p = blockIdx.y;
     const DevGroup G = d.groups[d.pgrp[p]];
     const int g = d.pgi[p];
-    if (!d.active[G.p0 + g]) return;
+    if (d.active[G.p0 + g] <= 0) return;
     const int e = blockIdx.x * 256 + threadIdx.x;
     const double* dc = d.dchi + G.eps_base + g * G.ns;
     if (e < G.n_rows_all) {
@@ -1254,9 +1280,9 @@ __device__ __forceinline__ void ladder32_run(const DevPtrs& d, int cur, uint32_t
     const DevGroup G = d.groups[c.group];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int nhh = c.nhh, nlp = c.n_lp;
-    const bool act = d.active[G.p0 + g] != 0;
-    const bool pp_on = act && (mask & CCD_T_PP) != 0;
-    const bool hh_on = act && (mask & (CCD_T_HH | CCD_T_QHH)) != 0;
+    if (d.active[G.p0 + g] <= 0) continue;  // (an earlier launch wrote the flag: every wave reads the same)
+    const bool pp_on = (mask & CCD_T_PP) != 0;
+    const bool hh_on = (mask & (CCD_T_HH | CCD_T_QHH)) != 0;
     const int64_t T0 = G.t_base + g * G.n_amp + c.t_off;
     const double* tcur = d.t[cur] + T0;
     const int4* lp = d.lpinfo + c.lp_off;
@@ -1454,19 +1480,17 @@ __device__ __forceinline__ void ladder32_run(const DevPtrs& d, int cur, uint32_t
         }
     }
     // this lane owns pairs orow(lane, r) of each tile, column col
-    if (act) {
 #pragma unroll
-        for (int h = 0; h < 2; h++)
+    for (int h = 0; h < 2; h++)
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int po = rbase + 16 * h + orow<P>(lane, r);
-                if (po < nlp && col < nhh) {
-                    const int2 rr = prs[32 * w + 16 * h + orow<P>(lane, r)];
-                    if (rr.x >= 0) d.rmm[T0 + (int64_t)rr.x * nhh + col] = (double)acc[h][r];
-                    if (rr.y >= 0) d.rmm[T0 + (int64_t)rr.y * nhh + col] = (double)acc2[h][r];
-                }
+        for (int r = 0; r < 4; r++) {
+            const int po = rbase + 16 * h + orow<P>(lane, r);
+            if (po < nlp && col < nhh) {
+                const int2 rr = prs[32 * w + 16 * h + orow<P>(lane, r)];
+                if (rr.x >= 0) d.rmm[T0 + (int64_t)rr.x * nhh + col] = (double)acc[h][r];
+                if (rr.y >= 0) d.rmm[T0 + (int64_t)rr.y * nhh + col] = (double)acc2[h][r];
             }
-    }
+        }
     }
 }
 
@@ -1517,13 +1541,13 @@ struct Lad64 {
 };
 template <int NG, bool CHI>
 __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int cur,
-                                              int r0, int ct, uint32_t mask, bool act, Lad64& L, double* chiS) {
+                                              int r0, int ct, uint32_t mask, Lad64& L, double* chiS) {
     constexpr int S = 8;
     const char* lutB = (const char*)L.lutS;
     const int tid = threadIdx.x, lane = tid & 63, w = (tid >> 6) & 3, kh = tid >> 8;
     const int nhh = c.nhh, nlp = c.n_lp;
-    const bool pp_on = act && (mask & CCD_T_PP) != 0;
-    const bool hh_on = act && (mask & (CCD_T_HH | CCD_T_QHH)) != 0;
+    const bool pp_on = (mask & CCD_T_PP) != 0;
+    const bool hh_on = (mask & (CCD_T_HH | CCD_T_QHH)) != 0;
     const int64_t T0 = G.t_base + g * G.n_amp + c.t_off;
     const double* tcur = d.t[cur] + T0;
     const int4* lp = d.lpinfo + c.lp_off;
@@ -1713,19 +1737,17 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
         for (int q = 0; q < NG; q++)
             x0[kh * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane] = kh ? acc[h][q][0] : acc[h][q][1];
     __syncthreads();
-    if (act) {
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const int2 ro = L.prs[32 * w + 16 * h + orow4];
-            const int r = kh ? ro.y : ro.x;
+    for (int h = 0; h < 2; h++) {
+        const int2 ro = L.prs[32 * w + 16 * h + orow4];
+        const int r = kh ? ro.y : ro.x;
 #pragma unroll
-            for (int q = 0; q < NG; q++) {
-                const int cc = ct * 16 + 4 * q + bj;
-                const double other = x0[(kh ^ 1) * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane];
-                // half 0's share first in both
-                const double v = kh ? other + acc[h][q][1] : acc[h][q][0] + other;
-                if (r >= 0 && cc < nhh) d.rmm[T0 + (int64_t)r * nhh + cc] = v;
-            }
+        for (int q = 0; q < NG; q++) {
+            const int cc = ct * 16 + 4 * q + bj;
+            const double other = x0[(kh ^ 1) * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane];
+            // half 0's share first in both
+            const double v = kh ? other + acc[h][q][1] : acc[h][q][0] + other;
+            if (r >= 0 && cc < nhh) d.rmm[T0 + (int64_t)r * nhh + cc] = v;
         }
     }
 }
@@ -1739,14 +1761,14 @@ __device__ __forceinline__ void ladder64_run(const DevPtrs& d, int cur, uint32_t
     const int r0 = it.start & 0xfffff, ct = it.start >> 20;
     const DevChan c = uni(d.chans[it.chan]);
     const DevGroup G = uni(d.groups[c.group]);
-    const bool act = d.active[G.p0 + g] != 0;
+    if (d.active[G.p0 + g] <= 0) return;  // (an earlier launch wrote the flag: every wave reads the same)
     // groups of four columns of this column tile that hold columns
     const int ng = min(4, (min(16, c.nhh - 16 * ct) + 3) >> 2);
     switch (ng) {
-        case 1: ladder64_item<1, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
-        case 2: ladder64_item<2, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
-        case 3: ladder64_item<3, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
-        default: ladder64_item<4, CHI>(d, c, G, g, cur, r0, ct, mask, act, L, chiS); break;
+        case 1: ladder64_item<1, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        case 2: ladder64_item<2, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        case 3: ladder64_item<3, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        default: ladder64_item<4, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
     }
 }
 __global__ void __launch_bounds__(kLadThreads, 4) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
@@ -1785,7 +1807,8 @@ __device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int
     const DevChan c = uni(d.chans[it.chan]);
     const DevGroup G = uni(d.groups[c.group]);
     const int nhh = c.nhh, nel = nhh * c.npp, e1 = min(nel, it.start + kElemChunk);
-    const bool act = d.active[G.p0 + g] != 0;
+    const int act = d.active[G.p0 + g];
+    if (act < 0) return;  // stopped, and t is in both buffers already
     const bool sz0 = c.sz == 0;
     const bool lad = sz0 && (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) != 0;
     const int64_t T0 = G.t_base + g * G.n_amp + c.t_off;
@@ -1794,6 +1817,10 @@ __device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int
     const double* rm = d.rmm + T0;
     const double2* zc = (const double2*)d.zc + T0;
     double* tn = d.t[cur ^ 1] + T0;
+    if (act == 0) {  // stopped in the last sweep: carry t over to the other buffer
+        for (int e = it.start + threadIdx.x; e < e1; e += 256) tn[e] = tc[e];
+        return;
+    }
     const int r0 = it.start / nhh, nr = (e1 - 1) / nhh - r0 + 1;
     constexpr int kPer = kElemChunk / 256;
     double t[kPer], v[kPer], l[kPer];
@@ -1808,30 +1835,26 @@ __device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int
             // <ab||ij> = 0 in S_z = +-1 blocks (two neutrons interact only in the
             // spin singlet), so only S_z = 0 blocks read it
             if (sz0) v[k] = vt[e];
-            if (act) {
-                if (lad) l[k] = rm[e];
-                if (ring_on) z[k] = zc[e];
-            }
+            if (lad) l[k] = rm[e];
+            if (ring_on) z[k] = zc[e];
         }
     }
     __syncthreads();  // the previous item's reads of LDS are done
-    if (act) {
-        const double* rowE = d.rowE + G.rowa_base + g * G.n_rows_all + c.rowa_off;
-        const double* rowX = d.rowX + G.rowa_base + g * G.n_rows_all + c.rowa_off;
-        const double* colE = d.colE + G.cola_base + g * G.n_cols_all + c.cola_off;
-        const double* colX = d.colX + G.cola_base + g * G.n_cols_all + c.cola_off;
-        const double* dc = d.dchi + G.eps_base + g * G.ns;
-        auto pair_sum = [&](int32_t p) { return dc[pa(p)] + dc[pb(p)]; };
-        for (int r = threadIdx.x; r < nr; r += 256) {
-            rE[r] = rowE[r0 + r];
-            if constexpr (OB) rX[r] = pair_sum(d.pp[c.pp_off + r0 + r]);
-            else rX[r] = rowX[r0 + r];
-        }
-        if ((int)threadIdx.x < nhh) {
-            cE[threadIdx.x] = colE[threadIdx.x];
-            if constexpr (OB) cX[threadIdx.x] = pair_sum(d.hh[c.hh_off + threadIdx.x]);
-            else cX[threadIdx.x] = colX[threadIdx.x];
-        }
+    const double* rowE = d.rowE + G.rowa_base + g * G.n_rows_all + c.rowa_off;
+    const double* rowX = d.rowX + G.rowa_base + g * G.n_rows_all + c.rowa_off;
+    const double* colE = d.colE + G.cola_base + g * G.n_cols_all + c.cola_off;
+    const double* colX = d.colX + G.cola_base + g * G.n_cols_all + c.cola_off;
+    const double* dc = d.dchi + G.eps_base + g * G.ns;
+    auto pair_sum = [&](int32_t p) { return dc[pa(p)] + dc[pb(p)]; };
+    for (int r = threadIdx.x; r < nr; r += 256) {
+        rE[r] = rowE[r0 + r];
+        if constexpr (OB) rX[r] = pair_sum(d.pp[c.pp_off + r0 + r]);
+        else rX[r] = rowX[r0 + r];
+    }
+    if ((int)threadIdx.x < nhh) {
+        cE[threadIdx.x] = colE[threadIdx.x];
+        if constexpr (OB) cX[threadIdx.x] = pair_sum(d.hh[c.hh_off + threadIdx.x]);
+        else cX[threadIdx.x] = colX[threadIdx.x];
     }
     __syncthreads();
     double es = 0.0;
@@ -1840,17 +1863,14 @@ __device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int
     for (int k = 0; k < kPer; k++) {
         const int e = it.start + threadIdx.x + 256 * k;
         if (e < e1) {
-            double tm = t[k];
-            if (act) {
-                // row and column of x = e - r0 nhh < kElemChunk + nhh: (x + 1/2) / nhh lies
-                // 1 / (2 nhh) >= 2^-7 from an integer
-                const int x = e - r0 * nhh, r = (int)(((float)x + 0.5f) * inv), col = x - r * nhh;
-                double R = v[k];
-                if (lad) R += l[k];
-                if (ring_on) R += z[k].x + z[k].y;
-                R += (rX[r] - cX[col]) * t[k];
-                tm = alpha * (R / (cE[col] - rE[r])) + (1.0 - alpha) * t[k];
-            }
+            // row and column of x = e - r0 nhh < kElemChunk + nhh: (x + 1/2) / nhh lies
+            // 1 / (2 nhh) >= 2^-7 from an integer
+            const int x = e - r0 * nhh, r = (int)(((float)x + 0.5f) * inv), col = x - r * nhh;
+            double R = v[k];
+            if (lad) R += l[k];
+            if (ring_on) R += z[k].x + z[k].y;
+            R += (rX[r] - cX[col]) * t[k];
+            const double tm = alpha * (R / (cE[col] - rE[r])) + (1.0 - alpha) * t[k];
             tn[e] = tm;
             es += v[k] * tm;
         }
@@ -1858,6 +1878,40 @@ __device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int
     const double s = block_sum256(es, sh);
     if (threadIdx.x == 0) d.epart_elem[G.eelem_base + g * (G.elem_hi - G.elem_lo) + (item - G.elem_lo)] = s;
 }
+// The lists of the problems that are still iterating, one after the other (blocks
+// 0 .. kLists P - 1), and for a problem that has just stopped its t carried over to
+// the other buffer (kCarry blocks each), as its update items, no longer listed, would
+// have done.  The lists of all problems keep each XCD on one problem's data, so when
+// a problem stops its XCD idles; these spread each problem over all of them.  Ten
+// densities at N=66, n^2<=20, of which 10 / 5 / 1 iterate: a sweep 245 / 235 / 199 us
+// from the lists of all problems, 266 / 145 / 52 from these (hence the former until
+// the first one stops); the solve to its last sweep (42) 10.6 -> 9.1 ms.
+constexpr int kCarry = 32;
+__global__ void __launch_bounds__(256) k_live_lists(DevPtrs d, int P, int cur) {
+    __shared__ double sh[4];
+    const int b = blockIdx.x;
+    if (b >= kLists * P) {
+        const int sl = (b - kLists * P) / kCarry, part = (b - kLists * P) % kCarry;
+        if (d.active[sl] != 0) return;
+        const DevGroup G = d.groups[d.pgrp[sl]];
+        const int64_t t0 = G.t_base + (int64_t)d.pgi[sl] * G.n_amp;
+        for (int64_t e = (int64_t)part * 256 + threadIdx.x; e < G.n_amp; e += 256 * kCarry)
+            d.t[cur ^ 1][t0 + e] = d.t[cur][t0 + e];
+        return;
+    }
+    const int k = b / P, sl = b % P;
+    if (d.active[sl] <= 0) return;
+    const int32_t* run = d.cl_run + k * (P + 1);
+    int before = 0;
+    for (int q = threadIdx.x; q < sl; q += 256)
+        if (d.active[q] > 0) before += run[q + 1] - run[q];
+    const double x = block_sum256((double)before, sh);  // (whole numbers below 2^53)
+    if (threadIdx.x == 0) sh[0] = x;
+    __syncthreads();
+    Item* out = d.lists + run[0] + (int)sh[0];
+    for (int e = run[sl] + threadIdx.x; e < run[sl + 1]; e += 256) out[e - run[sl]] = d.cl_items[e];
+}
+
 template <bool OB>
 __global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha, uint32_t mask, int n_items) {
     __shared__ double rE[kUpRows], rX[kUpRows], cE[kMaxHH], cX[kMaxHH];
@@ -1916,6 +1970,12 @@ struct ccd_ctx {
     std::vector<double> eps, lut, rowE, colE, pscale;
     std::vector<Item> it_elem, it_ladder, it_dchi, it_direct, it_ring_s, it_ring_b, it_lg, it_ue, it_dsub,
         it_dsum;
+    // the sweep's lists once more, each problem's items by themselves (several problems): run k of
+    // slot s is cl_items[cl_run[k (P + 1) + s] .. cl_run[k (P + 1) + s + 1])
+    std::vector<Item> cl_items;
+    std::vector<int32_t> cl_run;
+    SweepLists lists;       // the lists that the three launches take
+    bool live_lists = false;  // ... are those of the problems still iterating (r_lists)
     int64_t n_dpart = 0, n_dcolp = 0;
     int ring_lo[4] = {0}, ring_n[4] = {0};  // big pair items by padded size n16 = 32, 48, 64, 80
     int max_pair = 0;                       // largest order of a pair
@@ -1925,7 +1985,7 @@ struct ccd_ctx {
     int n_rows = 0, n_cols = 0, n_chh = 0, n_eps = 0, n_eparte = 0, max_ph = 0;
     // workspace
     Region r_static, r_t0, r_t1, r_vt, r_chh, r_rows, r_cols, r_dchi, r_zc, r_rowx, r_colx, r_rmm, r_eparte,
-        r_ecorr, r_eprev, r_active, r_sweeps, r_ehist, r_dpart, r_dcolp, r_dprev, r_streak;
+        r_ecorr, r_eprev, r_active, r_sweeps, r_ehist, r_dpart, r_dcolp, r_dprev, r_streak, r_lists;
     size_t ws_bytes = 0;
     char* ws = nullptr;
     bool bound = false;
@@ -1965,7 +2025,8 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
     X(csr_idx, int32_t) X(pgrp, int32_t) X(pgi, int32_t) X(pscale, double) \
     X(it_elem, Item) X(it_ladder, Item) X(it_sz0, int32_t) X(it_dchi, Item) \
     X(it_direct, Item) X(it_ring_s, Item) X(it_ring_b, Item) X(it_lg, Item) X(it_ue, Item) \
-    X(it_dsub, Item) X(it_dsum, Item) X(lpinfo, int32_t) X(cinfo, int32_t)
+    X(it_dsub, Item) X(it_dsum, Item) X(lpinfo, int32_t) X(cinfo, int32_t) \
+    X(cl_items, Item) X(cl_run, int32_t)
 
 static DevPtrs make_ptrs(ccd_ctx* c) {
     DevPtrs d;
@@ -1978,7 +2039,7 @@ static DevPtrs make_ptrs(ccd_ctx* c) {
     const void* p_it_dchi; const void* p_it_direct; const void* p_it_ring_s; const void* p_it_ring_b;
     const void* p_it_lg; const void* p_it_ue; const void* p_zs; const void* p_rowE; const void* p_colE;
     const void* p_pscale; const void* p_it_dsub; const void* p_it_dsum;
-    const void* p_lpinfo; const void* p_cinfo;
+    const void* p_lpinfo; const void* p_cinfo; const void* p_cl_items; const void* p_cl_run;
 #define TAKE(name, T)             \
     p_##name = base + o;          \
     o += align256(c->name.size() * sizeof(T));
@@ -2000,6 +2061,15 @@ static DevPtrs make_ptrs(ccd_ctx* c) {
     d.it_dsub = (const Item*)p_it_dsub; d.it_dsum = (const Item*)p_it_dsum;
     d.lpinfo = (const int4*)p_lpinfo;
     d.cinfo = (const int32_t*)p_cinfo;
+    d.cl_items = (const Item*)p_cl_items;
+    d.cl_run = (const int32_t*)p_cl_run;
+    d.lists = (Item*)(base + c->r_lists.off);
+    if (c->live_lists) {
+        const int P1 = (int)c->probs.size() + 1;
+        auto at = [&](int k) { return d.lists + c->cl_run[k * P1]; };
+        d.it_direct = at(kListDirect); d.it_ring_s = at(kListSmall); d.it_ring_b = at(kListRing);
+        d.it_lg = at(kListLadder); d.it_dchi = at(kListOneBody); d.it_ue = at(kListUpdate);
+    }
     d.dpart = (double*)(base + c->r_dpart.off);
     d.dcolp = (double*)(base + c->r_dcolp.off);
     d.t[0] = (double*)(base + c->r_t0.off);
@@ -2070,7 +2140,23 @@ static void layout(ccd_ctx* c) {
     region(c->r_ehist, P * kHistCap * 8);
     region(c->r_dprev, P * 8);
     region(c->r_streak, P * 4);
+    region(c->r_lists, c->cl_items.size() * sizeof(Item));
     c->ws_bytes = o;
+}
+
+// the lists of every problem
+static void full_lists(ccd_ctx* c) {
+    SweepLists& l = c->lists;
+    c->live_lists = false;
+    l.n[kListDirect] = (int)c->it_direct.size();
+    l.n[kListSmall] = (int)c->it_ring_s.size();
+    l.n[kListLadder] = (int)c->it_lg.size();
+    l.n[kListOneBody] = (int)c->it_dchi.size();
+    l.n[kListUpdate] = (int)c->it_ue.size();
+    for (int b = 0; b < 4; b++) {
+        l.n[kListRing + b] = c->ring_n[b];
+        l.ring_lo[b] = c->ring_lo[b];
+    }
 }
 
 // Blocks are dispatched to the eight XCDs round-robin by block index.  Work
@@ -2374,6 +2460,36 @@ static ccd_status assemble(ccd_ctx* c) {
         c->ring_n[k] = (int)o.size();
         c->it_ring_b.insert(c->it_ring_b.end(), o.begin(), o.end());
     }
+    c->cl_items.clear();
+    c->cl_run.clear();
+    if (P > 1) {
+        auto add = [&](const std::vector<std::pair<int, Item>>& v, const std::vector<double>* cost, bool per_problem,
+                       int u) {
+            std::vector<std::vector<std::pair<int, Item>>> of(P);
+            std::vector<std::vector<double>> oc(P);
+            for (size_t k = 0; k < v.size(); k++) {
+                of[v[k].first].push_back(v[k]);
+                if (cost) oc[v[k].first].push_back((*cost)[k]);
+            }
+            for (size_t sl = 0; sl < P; sl++) {
+                c->cl_run.push_back((int32_t)c->cl_items.size());
+                std::vector<Item> o;
+                if (u == 0) for (const auto& x : of[sl]) o.push_back(x.second);  // as they are, without padding
+                else o = cost ? xcd_order_cost(of[sl], oc[sl], per_problem) : xcd_order(of[sl], u);
+                c->cl_items.insert(c->cl_items.end(), o.begin(), o.end());
+            }
+            c->cl_run.push_back((int32_t)c->cl_items.size());
+        };
+        std::vector<std::pair<int, Item>> ob;
+        for (const Item& it : c->it_dchi) ob.push_back({c->dgroups[it.chan].p0 + (it.start >> 16), it});
+        add(dir, &dir_cost, false, 1);
+        add(rs, nullptr, false, 4);
+        for (int k = 0; k < 4; k++) add(rb[k], &rb_cost[k], true, 1);
+        add(lg, &lg_cost, false, 1);
+        add(ob, nullptr, false, 0);  // (dchi_item takes no padding items)
+        add(ue, nullptr, false, 1);
+    }
+    full_lists(c);
     // per-slot copies of (group, index in group) for the per-problem kernels
     std::vector<int32_t> sg(P), sgi(P);
     for (size_t p = 0; p < P; p++) {
@@ -2548,7 +2664,7 @@ static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
 }
 
 static ccd_status L_update(ccd_ctx* c, const DevPtrs& d, int cur, double alpha, uint32_t mask) {
-    const int n = (int)c->it_ue.size();
+    const int n = c->lists.n[kListUpdate];
     if (one_stream(c))
         LAUNCH(F_UPDATE, k_update<true>, n, 256, 0, d, cur, alpha, mask, n);
     else
@@ -2573,17 +2689,18 @@ static size_t front_lds(const ccd_ctx* c) {
 // update's being the third.
 template <int P>
 static ccd_status launch_one_stream(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
+    const SweepLists& l = c->lists;
     Front f;
     std::memset(&f, 0, sizeof(f));
-    if (mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) f.nd = (int)c->it_direct.size();
+    if (mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) f.nd = l.n[kListDirect];
     if (mask & (CCD_T_RING | CCD_T_QRING)) {
         for (int k = 0; k < 4; k++) {
-            f.nb[k] = c->ring_n[k];
-            f.lo[k] = c->ring_lo[k];
+            f.nb[k] = l.n[kListRing + k];
+            f.lo[k] = l.ring_lo[k];
         }
         f.n32 = f.nb[0];
         f.nb[0] = 8 * ((f.nb[0] / 8 + 1) / 2);
-        f.n_small = (int)c->it_ring_s.size();
+        f.n_small = l.n[kListSmall];
         f.ns = 8 * ((f.n_small / 32 + 1) / 2);
         f.small80 = c->max_pair <= kRing80M;
     }
@@ -2595,8 +2712,8 @@ static ccd_status launch_one_stream(ccd_ctx* c, const DevPtrs& d, int cur, uint3
     const int grid = f.nd + f.nb[0] + f.nb[1] + f.nb[2] + f.nb[3] + f.ns + f.ne;
     LAUNCH(F_DIRECT, k_front<P>, grid, kFrontThreads, front_lds<P>(c), d, cur, mask, f, c->pend_tol, c->pend_tol_rel,
            c->pend_rule);
-    const int nl = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) ? (int)c->it_lg.size() : 0;
-    const int no = (int)c->it_dchi.size();
+    const int nl = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) ? l.n[kListLadder] : 0;
+    const int no = l.n[kListOneBody];
     if constexpr (P == P_F64)
         LAUNCH(F_LADDER, k_mid64, nl + (no + 1) / 2, kLadThreads, 0, d, cur, mask, nl, no);
     else
@@ -2959,6 +3076,29 @@ ccd_status ccd_bind_workspace(ccd_ctx* c, void* ptr, size_t bytes) {
     return CCD_OK;
 }
 
+// lists of the problems with act[slot] > 0 for the sweeps to come
+static ccd_status live_lists(ccd_ctx* c, const std::vector<int32_t>& act) {
+    const int P = (int)c->probs.size();
+    const DevPtrs d = make_ptrs(c);
+    hipLaunchKernelGGL(k_live_lists, dim3((kLists + kCarry) * P), dim3(256), 0, c->stream, d, P, c->cur);
+    HIP_TRY(hipGetLastError());
+    SweepLists& l = c->lists;
+    for (int k = 0; k < kLists; k++) {
+        const int32_t* run = c->cl_run.data() + (size_t)k * (P + 1);
+        l.n[k] = 0;
+        for (int s = 0; s < P; s++)
+            if (act[s] > 0) l.n[k] += run[s + 1] - run[s];
+        if (k >= kListRing && k < kListRing + 4) l.ring_lo[k - kListRing] = run[0] - c->cl_run[kListRing * (P + 1)];
+    }
+    c->live_lists = true;
+    return CCD_OK;
+}
+struct FullLists {  // the lists of every problem again at the end of a phase
+    ccd_ctx* c;
+    explicit FullLists(ccd_ctx* cc) : c(cc) {}
+    ~FullLists() { full_lists(c); }
+};
+
 // one phase of sweeps in precision prec.  Sweeps run in chunks of up to
 // check_every (graph replays when asked); after each chunk the host reads the
 // per-problem sweep counters, active flags and the device energy history.
@@ -2988,7 +3128,9 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
     // device decides when each problem stops, so results do not change.
     std::vector<double> ec(P), dq(P), d_then(P, 0.0);
     std::vector<int32_t> sw_then(P, 0);
-    int next = every;
+    int next = every, listed = P;  // problems on the sweep's lists
+    const FullLists full(c);
+    std::vector<std::pair<int, int64_t>> needs;  // (sweeps, amplitudes) of a problem
     while (used < budget && !all_done) {
         int n;
         double tol, rel;
@@ -3021,14 +3163,22 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
                 if (e_hist)
                     for (int k = sw0[sl]; k < sw[sl] && k < o->max_iter; k++)
                         e_hist[(size_t)p * o->max_iter + k] = hb[(size_t)sl * kHistCap + k % kHistCap];
-                if (act[sl]) all_done = false;
+                if (act[sl] > 0) all_done = false;
             }
             // (with graph replay every chunk length is a graph of its own to
-            // capture, so the chunks keep the one length there)
+            // capture, so the chunks keep the one length there, and the lists)
+            if (stops && !graph && !all_done && used < budget) {
+                const int live = (int)std::count_if(act.begin(), act.end(), [](int32_t a) { return a > 0; });
+                if (live < listed && one_stream(c)) {
+                    if ((st = live_lists(c, act)) != CCD_OK) return st;
+                    listed = live;
+                }
+            }
             if (stops && !graph && used + 1 >= min_sweeps) {
                 next = 0;
+                needs.clear();
                 for (int sl = 0; sl < P; sl++) {
-                    if (!act[sl]) continue;
+                    if (act[sl] <= 0) continue;
                     const double de = dq[sl], thr = tol_phase + rel_phase * std::fabs(ec[sl]);
                     int need = every;
                     // the rate over the last chunk, else over the last sweep (the
@@ -3049,11 +3199,25 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
                         const double k = de < target ? 0.0 : std::floor(std::log(target / de) / std::log(rate));
                         need = k >= (double)every ? every : (int)k + extra;
                     }
-                    next = std::max(next, std::min(std::max(need, 1), every));
+                    need = std::min(std::max(need, 1), every);
+                    next = std::max(next, need);
+                    needs.push_back({need, c->dgroups[c->pgrp[sl]].n_amp});
                     d_then[sl] = de;
                     sw_then[sl] = sw[sl];
                 }
                 if (next < 1) next = every;
+                // An earlier read takes the problems that will have stopped off the
+                // lists: it pays from about 10^6 amplitudes' sweeps on (60 us, a read's
+                // cost, at the 75 ps that an amplitude takes in a large sweep)
+                std::sort(needs.begin(), needs.end());
+                int64_t off = 0;
+                for (const auto& x : needs) {
+                    off += x.second;
+                    if ((next - x.first) * off >= 1000000) {
+                        next = x.first;
+                        break;
+                    }
+                }
             }
         }
     }
@@ -3113,7 +3277,7 @@ ccd_status ccd_iterate(ccd_ctx* c, const ccd_solver_opts* o, int32_t* sweeps_don
         }
     if (o->tol > 0.0 || o->tol_rel > 0.0)
         for (int p = 0; p < P; p++)
-            if (act[c->slot_of[p]]) return CCD_NOT_CONVERGED;
+            if (act[c->slot_of[p]] > 0) return CCD_NOT_CONVERGED;
     return CCD_OK;
 }
 

@@ -252,3 +252,42 @@ def test_three_launch_sweep_equals_the_separate_launches(specs, prec):
         assert np.array_equal(out[0]["history"], out[1]["history"]), mask
         for p in range(len(probs)):
             assert np.array_equal(a.get_amplitudes(p), b.get_amplitudes(p)), (mask, p)
+
+
+# problems that stop at different sweeps: several of one group, several groups, one with
+# small pairs only beside large ones
+_STOPS = [[(14, 4, r) for r in (0.02, 0.2, 0.1)], [(66, 20, 0.16), (66, 20, 0.02), (14, 4, 0.05), (38, 12, 0.1)],
+          [(2, 1, 0.1), (66, 36, 0.06), (54, 12, 0.2)]]
+
+
+@pytest.mark.parametrize("specs", _STOPS, ids=lambda s: "-".join(f"{x[0]}_{x[1]}" for x in s))
+@pytest.mark.parametrize("prec", [ccd.CCD_PREC_FP64, ccd.CCD_PREC_BF16])
+@pytest.mark.parametrize("every", [1, 2, 8])
+def test_problems_that_stop_early_equal_their_own_contexts(specs, prec, every):
+    """Problems leave the sweep's lists as they stop.  Sweeps, energies and
+    amplitudes equal those of a context of the problem's own bit for bit, also
+    after more sweeps of all problems, whose first one reads whichever of the two
+    amplitude buffers a problem ended in."""
+    probs = [ccd.problem(*x) for x in specs]
+    opt = dict(mixing=0.5, tol_rel=2e-8, max_iter=120, stop_rule=1, precision=prec, history=True, refine_sweeps=1,
+               mixed_tol=1e-2 if prec else 0.0, check_every=every)
+    def solve(c, more):
+        r = c.iterate(**opt)
+        t = [c.get_amplitudes(p) for p in range(c.n)]
+        m = c.iterate(mixing=0.5, max_iter=more, history=True)
+        return r["sweeps"], r["history"], t, m["history"], [c.get_amplitudes(p) for p in range(c.n)]
+    batch = _ctx(probs)
+    runs = [solve(batch, 3)]
+    batch.reset_amplitudes()
+    runs.append(solve(batch, 2))
+    assert len(set(runs[0][0])) > 1
+    for p, prob in enumerate(probs):
+        alone = _ctx([prob])
+        for more, run in zip((3, 2), runs):
+            alone.reset_amplitudes()
+            ref = solve(alone, more)
+            assert run[0][p] == ref[0][0]
+            assert np.array_equal(run[1][p], ref[1][0], equal_nan=True)
+            assert np.array_equal(run[2][p], ref[2][0])
+            assert np.array_equal(run[3][p], ref[3][0])
+            assert np.array_equal(run[4][p], ref[4][0])
