@@ -357,7 +357,7 @@ class Context:
 
     def get_amplitudes(self, p=0):
         n = self.info(p)["n_amplitudes"]
-        out = np.zeros(n)
+        out = np.empty(n)
         _check(_lib.ccd_get_amplitudes(self._h, p, _dptr(out), n), "ccd_get_amplitudes")
         return out
 
@@ -582,7 +582,7 @@ class NMContext:
         return a.value, b.value, c.value
 
     def get_amplitudes(self):
-        out = np.zeros(self.info()["n_amplitudes"])
+        out = np.empty(self.info()["n_amplitudes"])
         _check(_lib.ccd_nm_get_amplitudes(self._h, _dptr(out), out.size), "ccd_nm_get_amplitudes")
         return out
 

@@ -47,6 +47,7 @@
 
 #include "ccd_internal.h"
 #include "direct64.h"
+#include "host_io.h"
 #include "mlp_net.h"
 #include "../../include/ccd_mlp.h"
 
@@ -1912,6 +1913,18 @@ __global__ void __launch_bounds__(256) k_live_lists(DevPtrs d, int P, int cur) {
     for (int e = run[sl] + threadIdx.x; e < run[sl + 1]; e += 256) out[e - run[sl]] = d.cl_items[e];
 }
 
+// all problems iterate; fresh: from sweep 0
+__global__ void __launch_bounds__(256) k_start(DevPtrs d, int P, int fresh) {
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= P) return;
+    d.active[p] = 1;
+    if (fresh) {
+        d.sweeps[p] = 0;
+        d.streak[p] = 0;
+        d.dprev[p] = 0.0;
+    }
+}
+
 template <bool OB>
 __global__ void __launch_bounds__(256) k_update(DevPtrs d, int cur, double alpha, uint32_t mask, int n_items) {
     __shared__ double rE[kUpRows], rX[kUpRows], cE[kMaxHH], cX[kMaxHH];
@@ -1991,6 +2004,7 @@ struct ccd_ctx {
     bool bound = false;
     int cur = 0;
     std::vector<double> emp2;
+    HostIO io;
     // timing
     bool timing = false;
     std::vector<hipEvent_t> ev_pool;
@@ -2133,13 +2147,14 @@ static void layout(ccd_ctx* c) {
     region(c->r_colx, c->colE.size() * 8);
     region(c->r_rmm, (size_t)c->NT * 8);
     region(c->r_eparte, (size_t)c->n_eparte * 8);
-    region(c->r_ecorr, P * 8);
     region(c->r_eprev, P * 8);
-    region(c->r_active, P * 4);
-    region(c->r_sweeps, P * 4);
-    region(c->r_ehist, P * kHistCap * 8);
+    // the state words: read by the host as one block (read_state)
+    region(c->r_ecorr, P * 8);
     region(c->r_dprev, P * 8);
+    region(c->r_sweeps, P * 4);
     region(c->r_streak, P * 4);
+    region(c->r_active, P * 4);
+    region(c->r_ehist, P * kHistCap * 8);
     region(c->r_lists, c->cl_items.size() * sizeof(Item));
     c->ws_bytes = o;
 }
@@ -2463,30 +2478,38 @@ static ccd_status assemble(ccd_ctx* c) {
     c->cl_items.clear();
     c->cl_run.clear();
     if (P > 1) {
+        // the problems of a group have the same items: ordered for the first, copied for the rest
         auto add = [&](const std::vector<std::pair<int, Item>>& v, const std::vector<double>* cost, bool per_problem,
                        int u) {
             std::vector<std::vector<std::pair<int, Item>>> of(P);
             std::vector<std::vector<double>> oc(P);
             for (size_t k = 0; k < v.size(); k++) {
+                if (v[k].second.start != 0) continue;
                 of[v[k].first].push_back(v[k]);
                 if (cost) oc[v[k].first].push_back((*cost)[k]);
             }
-            for (size_t sl = 0; sl < P; sl++) {
-                c->cl_run.push_back((int32_t)c->cl_items.size());
-                std::vector<Item> o;
-                if (u == 0) for (const auto& x : of[sl]) o.push_back(x.second);  // as they are, without padding
-                else o = cost ? xcd_order_cost(of[sl], oc[sl], per_problem) : xcd_order(of[sl], u);
-                c->cl_items.insert(c->cl_items.end(), o.begin(), o.end());
+            for (const DevGroup& D : c->dgroups) {
+                std::vector<Item> o = cost ? xcd_order_cost(of[D.p0], oc[D.p0], per_problem) : xcd_order(of[D.p0], u);
+                for (int g = 0; g < D.G; g++) {
+                    for (Item& it : o) it.start = g;
+                    c->cl_run.push_back((int32_t)c->cl_items.size());
+                    c->cl_items.insert(c->cl_items.end(), o.begin(), o.end());
+                }
             }
             c->cl_run.push_back((int32_t)c->cl_items.size());
         };
-        std::vector<std::pair<int, Item>> ob;
-        for (const Item& it : c->it_dchi) ob.push_back({c->dgroups[it.chan].p0 + (it.start >> 16), it});
         add(dir, &dir_cost, false, 1);
         add(rs, nullptr, false, 4);
         for (int k = 0; k < 4; k++) add(rb[k], &rb_cost[k], true, 1);
         add(lg, &lg_cost, false, 1);
-        add(ob, nullptr, false, 0);  // (dchi_item takes no padding items)
+        // the one-body items are listed by problem already, and take no padding
+        int last = -1;
+        for (const Item& it : c->it_dchi) {
+            const int sl = c->dgroups[it.chan].p0 + (it.start >> 16);
+            for (; last < sl; last++) c->cl_run.push_back((int32_t)c->cl_items.size());
+            c->cl_items.push_back(it);
+        }
+        for (; last < (int)P; last++) c->cl_run.push_back((int32_t)c->cl_items.size());
         add(ue, nullptr, false, 1);
     }
     full_lists(c);
@@ -2552,6 +2575,23 @@ static ccd_status harvest(ccd_ctx* c) {
         }                                                                               \
     } while (0)
 
+
+// the state words up to the end of region r to the host
+static ccd_status read_state(ccd_ctx* c, const Region& r) {
+    HIP_TRY(c->io.read_words(c->ws + c->r_ecorr.off, (r.off + r.bytes + 7 - c->r_ecorr.off) / 8, c->stream));
+    return CCD_OK;
+}
+// region r in the host's copy
+template <typename T>
+static const T* state(const ccd_ctx* c, const Region& r) {
+    return (const T*)(c->io.words + (r.off - c->r_ecorr.off));
+}
+static ccd_status start_sweeps(ccd_ctx* c, bool fresh) {
+    const int P = (int)c->probs.size();
+    hipLaunchKernelGGL(k_start, dim3((P + 255) / 256), dim3(256), 0, c->stream, make_ptrs(c), P, (int)fresh);
+    HIP_TRY(hipGetLastError());
+    return CCD_OK;
+}
 
 static ccd_status refresh_energy(ccd_ctx* c) {
     DevPtrs d = make_ptrs(c);
@@ -3065,14 +3105,16 @@ ccd_status ccd_bind_workspace(ccd_ctx* c, void* ptr, size_t bytes) {
     HIP_TRY(hipMemcpyAsync(c->ws + c->r_static.off, img.data(), img.size(), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipMemsetAsync(c->ws + c->r_t0.off, 0, c->ws_bytes - c->r_t0.off, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    if (!c->io.words && !c->io.init((c->r_ehist.off + c->r_ehist.bytes + 7 - c->r_ecorr.off) / 8)) {
+        set_error("ccd_bind_workspace: no host memory");
+        return CCD_EHIP;
+    }
     c->bound = true;
     ccd_status s = ccd_reset_amplitudes(c);
+    if (s == CCD_OK) s = read_state(c, c->r_ecorr);
     if (s != CCD_OK) return s;
     const int P = (int)c->probs.size();
-    std::vector<double> e(P);
-    HIP_TRY(hipMemcpyAsync(e.data(), c->ws + c->r_ecorr.off, P * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    for (int p = 0; p < P; p++) c->emp2[p] = e[c->slot_of[p]];
+    for (int p = 0; p < P; p++) c->emp2[p] = state<double>(c, c->r_ecorr)[c->slot_of[p]];
     return CCD_OK;
 }
 
@@ -3102,22 +3144,20 @@ struct FullLists {  // the lists of every problem again at the end of a phase
 // one phase of sweeps in precision prec.  Sweeps run in chunks of up to
 // check_every (graph replays when asked); after each chunk the host reads the
 // per-problem sweep counters, active flags and the device energy history.
-// min_sweeps: sweeps run before the convergence test may stop a problem.
+// min_sweeps: sweeps run before the convergence test may stop a problem; fresh: the
+// first phase of a call.  With a tolerance or an energy history wanted, the host's
+// copy of the state is that after the last sweep.
 static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, double tol_phase, double rel_phase,
-                            int rule, int budget, int min_sweeps, double* e_hist, int& used) {
+                            int rule, int budget, int min_sweeps, double* e_hist, int& used, bool fresh) {
     const int P = (int)c->probs.size();
-    std::vector<int32_t> ones(P, 1);
-    HIP_TRY(hipMemcpyAsync(c->ws + c->r_active.off, ones.data(), P * 4, hipMemcpyHostToDevice, c->stream));
     const bool stops = tol_phase > 0.0 || rel_phase > 0.0;
     const bool check = stops || e_hist;
     const int every = check ? std::max(1, std::min(o->check_every > 0 ? o->check_every : 1, kHistCap)) : kHistCap;
     const bool graph = o->use_graph != 0;
     std::vector<int32_t> sw(P, 0), sw0(P, 0), act(P, 1);
-    std::vector<double> hb((size_t)P * kHistCap);
-    if (e_hist) {
-        HIP_TRY(hipMemcpyAsync(sw.data(), c->ws + c->r_sweeps.off, P * 4, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-    }
+    ccd_status st = start_sweeps(c, fresh);
+    if (st != CCD_OK) return st;
+    if (e_hist && !fresh) sw.assign(state<int32_t>(c, c->r_sweeps), state<int32_t>(c, c->r_sweeps) + P);
     bool all_done = false;
     used = 0;
     // Chunk length: `every` sweeps, or fewer once the sweeps that the slowest
@@ -3126,7 +3166,8 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
     // most of a live sweep (launches, barriers, the update's copy of t), while
     // a short chunk costs one more host read.  Only the host's reads move; the
     // device decides when each problem stops, so results do not change.
-    std::vector<double> ec(P), dq(P), d_then(P, 0.0);
+    const double *hb = state<double>(c, c->r_ehist), *ec = state<double>(c, c->r_ecorr), *dq = state<double>(c, c->r_dprev);
+    std::vector<double> d_then(P, 0.0);
     std::vector<int32_t> sw_then(P, 0);
     int next = every, listed = P;  // problems on the sweep's lists
     const FullLists full(c);
@@ -3142,21 +3183,13 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
             tol = tol_phase;
             rel = rel_phase;
         }
-        ccd_status st = run_sweeps(c, n, o->mixing, tol, rel, rule, o->terms, prec, graph);
-        if (st != CCD_OK) return st;
+        if ((st = run_sweeps(c, n, o->mixing, tol, rel, rule, o->terms, prec, graph)) != CCD_OK) return st;
         used += n;
         if (check) {
             sw0 = sw;
-            HIP_TRY(hipMemcpyAsync(sw.data(), c->ws + c->r_sweeps.off, P * 4, hipMemcpyDeviceToHost, c->stream));
-            HIP_TRY(hipMemcpyAsync(act.data(), c->ws + c->r_active.off, P * 4, hipMemcpyDeviceToHost, c->stream));
-            if (e_hist || stops)
-                HIP_TRY(hipMemcpyAsync(hb.data(), c->ws + c->r_ehist.off, hb.size() * 8, hipMemcpyDeviceToHost,
-                                       c->stream));
-            if (stops) {
-                HIP_TRY(hipMemcpyAsync(ec.data(), c->ws + c->r_ecorr.off, P * 8, hipMemcpyDeviceToHost, c->stream));
-                HIP_TRY(hipMemcpyAsync(dq.data(), c->ws + c->r_dprev.off, P * 8, hipMemcpyDeviceToHost, c->stream));
-            }
-            HIP_TRY(hipStreamSynchronize(c->stream));
+            if ((st = read_state(c, c->r_ehist)) != CCD_OK) return st;
+            sw.assign(state<int32_t>(c, c->r_sweeps), state<int32_t>(c, c->r_sweeps) + P);
+            act.assign(state<int32_t>(c, c->r_active), state<int32_t>(c, c->r_active) + P);
             all_done = stops;
             for (int p = 0; p < P; p++) {
                 const int sl = c->slot_of[p];
@@ -3187,7 +3220,7 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
                     if (sw[sl] > sw_then[sl] && d_then[sl] > 0.0 && de > 0.0) {
                         rate = std::pow(de / d_then[sl], 1.0 / (sw[sl] - sw_then[sl]));
                     } else if (sw[sl] >= 3 && de > 0.0) {
-                        const double* h = hb.data() + (size_t)sl * kHistCap;
+                        const double* h = hb + (size_t)sl * kHistCap;
                         const double d1 = std::fabs(h[(sw[sl] - 2) % kHistCap] - h[(sw[sl] - 3) % kHistCap]);
                         if (d1 > 0.0) rate = de / d1;
                     }
@@ -3240,11 +3273,6 @@ ccd_status ccd_iterate(ccd_ctx* c, const ccd_solver_opts* o, int32_t* sweeps_don
         return CCD_EINVAL;
     }
     const int P = (int)c->probs.size();
-    std::vector<int32_t> zeros(P, 0);
-    std::vector<double> dzero(P, 0.0);
-    HIP_TRY(hipMemcpyAsync(c->ws + c->r_sweeps.off, zeros.data(), P * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(c->ws + c->r_dprev.off, dzero.data(), P * 8, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(c->ws + c->r_streak.off, zeros.data(), P * 4, hipMemcpyHostToDevice, c->stream));
     if (e_hist)
         for (size_t k = 0; k < (size_t)P * o->max_iter; k++) e_hist[k] = NAN;
     int used = 0;
@@ -3253,21 +3281,19 @@ ccd_status ccd_iterate(ccd_ctx* c, const ccd_solver_opts* o, int32_t* sweeps_don
     // a mixed phase with its own criterion uses the plain |dE| test: near its
     // rounding floor the ratio of successive changes hovers around 1
     ccd_status st = run_phase(c, o, o->precision, own ? o->mixed_tol : o->tol, own ? 0.0 : o->tol_rel,
-                              own ? 0 : o->stop_rule, o->max_iter, 1, e_hist, used);
+                              own ? 0 : o->stop_rule, o->max_iter, 1, e_hist, used, true);
     if (st != CCD_OK) return st;
     if (mixed && used < o->max_iter) {
         // FP64 refinement: continue the FP64 iteration from the mixed-precision iterate
         int used2 = 0;
         st = run_phase(c, o, CCD_PREC_FP64, o->tol, o->tol_rel, o->stop_rule, o->max_iter - used,
-                       std::max(1, o->refine_sweeps), e_hist, used2);
+                       std::max(1, o->refine_sweeps), e_hist, used2, false);
         if (st != CCD_OK) return st;
     }
-    std::vector<int32_t> sw(P), act(P);
-    std::vector<double> e(P);
-    HIP_TRY(hipMemcpyAsync(sw.data(), c->ws + c->r_sweeps.off, P * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(e.data(), c->ws + c->r_ecorr.off, P * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(act.data(), c->ws + c->r_active.off, P * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    // (without a history or a tolerance of the last phase nothing has been read yet)
+    if (!e_hist && !(o->tol > 0.0 || o->tol_rel > 0.0) && (st = read_state(c, c->r_active)) != CCD_OK) return st;
+    const int32_t *sw = state<int32_t>(c, c->r_sweeps), *act = state<int32_t>(c, c->r_active);
+    const double* e = state<double>(c, c->r_ecorr);
     if (sweeps_done)
         for (int p = 0; p < P; p++) sweeps_done[p] = sw[c->slot_of[p]];
     for (int p = 0; p < P; p++)
@@ -3292,7 +3318,6 @@ ccd_status ccd_mbpt3(ccd_ctx* c, double* out) {
     o.max_iter = 1;
     o.precision = CCD_PREC_FP64;
     o.check_every = 1;
-    std::vector<double> e(P);
     for (int k = 0; k < 4; k++) {
         ccd_status s = ccd_reset_amplitudes(c);
         if (s != CCD_OK) return s;
@@ -3302,9 +3327,8 @@ ccd_status ccd_mbpt3(ccd_ctx* c, double* out) {
             (void)ccd_reset_amplitudes(c);
             return s;
         }
-        HIP_TRY(hipMemcpyAsync(e.data(), c->ws + c->r_ecorr.off, 8 * P, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        for (int p = 0; p < P; p++) out[4 * p + k] = e[c->slot_of[p]] - c->emp2[p];
+        if ((s = read_state(c, c->r_ecorr)) != CCD_OK) return s;
+        for (int p = 0; p < P; p++) out[4 * p + k] = state<double>(c, c->r_ecorr)[c->slot_of[p]] - c->emp2[p];
     }
     return ccd_reset_amplitudes(c);
 }
@@ -3315,11 +3339,10 @@ ccd_status ccd_energy(const ccd_ctx* cc, int32_t p, double* eref, double* emp2, 
     if (eref) *eref = c->probs[p].eref;
     if (emp2 || ecorr) {
         if (!c->bound) { set_error("ccd_energy: no workspace bound"); return CCD_ESTATE; }
-        double e = 0;
-        HIP_TRY(hipMemcpyAsync(&e, c->ws + c->r_ecorr.off + 8 * c->slot_of[p], 8, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
+        const ccd_status s = read_state(c, c->r_ecorr);
+        if (s != CCD_OK) return s;
         if (emp2) *emp2 = c->emp2[p];
-        if (ecorr) *ecorr = e;
+        if (ecorr) *ecorr = state<double>(c, c->r_ecorr)[c->slot_of[p]];
     }
     return CCD_OK;
 }
@@ -3336,9 +3359,9 @@ ccd_status ccd_twist_average(const ccd_ctx* cc, const double* weight, double* ou
     if (!c || !weight || !out) { set_error("ccd_twist_average: NULL argument"); return CCD_EINVAL; }
     if (!c->bound) { set_error("ccd_twist_average: no workspace bound"); return CCD_ESTATE; }
     const size_t P = c->probs.size();
-    std::vector<double> ec(P);
-    HIP_TRY(hipMemcpyAsync(ec.data(), c->ws + c->r_ecorr.off, 8 * P, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    const ccd_status s = read_state(c, c->r_ecorr);
+    if (s != CCD_OK) return s;
+    const double* ec = state<double>(c, c->r_ecorr);
     double acc[5] = {0, 0, 0, 0, 0};
     for (size_t p = 0; p < P; p++) {
         const HostProblem& H = c->probs[p];
@@ -3374,8 +3397,7 @@ ccd_status ccd_get_amplitudes(const ccd_ctx* c, int32_t p, double* dst, size_t n
     if (!c->bound) { set_error("no workspace bound"); return CCD_ESTATE; }
     if (n != (size_t)c->probs[p].n_amp) { set_error("ccd_get_amplitudes: n != n_amplitudes"); return CCD_EINVAL; }
     const Region& r = c->cur ? c->r_t1 : c->r_t0;
-    HIP_TRY(hipMemcpyAsync(dst, c->ws + r.off + 8 * c->prob_t0[p], n * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(((ccd_ctx*)c)->io.download(dst, c->ws + r.off + 8 * c->prob_t0[p], n * 8, c->stream));
     return CCD_OK;
 }
 

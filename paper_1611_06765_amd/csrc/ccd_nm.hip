@@ -41,6 +41,7 @@
 
 #include "ccd_internal.h"
 #include "direct64.h"
+#include "host_io.h"
 #include "../../include/ccd_nm.h"
 
 namespace {
@@ -1307,6 +1308,7 @@ struct ccd_nm_ctx {
     NmDev dev{};
     int cur = 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    mutable ccd::HostIO io;
 };
 
 namespace {
@@ -1965,8 +1967,8 @@ int nm_grid(int64_t work, int per) {
 ccd_status nm_energy_now(ccd_nm_ctx* c, int slot, double* e) {
     k_nm_energy<<<1, 256, 0, c->stream>>>(c->dev, slot);
     NM_TRY(hipGetLastError());
-    NM_TRY(hipMemcpyAsync(e, c->dev.ehist + slot, 8, hipMemcpyDeviceToHost, c->stream));
-    NM_TRY(hipStreamSynchronize(c->stream));
+    NM_TRY(c->io.read_words(c->dev.ehist + slot, 1, c->stream));
+    *e = ((const double*)c->io.words)[0];
     return CCD_OK;
 }
 
@@ -2115,6 +2117,10 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
         ccd::set_error("ccd_nm_bind_workspace: already bound");
         return CCD_ESTATE;
     }
+    if (!c->io.words && !c->io.init(kNmHist)) {
+        ccd::set_error("ccd_nm_bind_workspace: no host memory");
+        return CCD_EHIP;
+    }
     c->ws = (char*)ptr;
     char* b = c->ws;
     auto at = [&](int r) { return (void*)(b + c->region[r].first); };
@@ -2222,7 +2228,7 @@ extern "C" ccd_status ccd_nm_iterate(ccd_nm_ctx* c, const ccd_solver_opts* o, in
     double e = c->ecorr;
     int done = 0;
     bool conv = false, bad = false;
-    std::vector<double> h(kNmHist);
+    const double* h = (const double*)c->io.words;
     float ms_total = 0.0f;
     while (done < o->max_iter && !conv && !bad) {
         const int chunk = test ? 1 : std::min(kNmHist, o->max_iter - done);
@@ -2239,8 +2245,7 @@ extern "C" ccd_status ccd_nm_iterate(ccd_nm_ctx* c, const ccd_solver_opts* o, in
             if (st != CCD_OK) return st;
         }
         NM_TRY(hipEventRecord(c->ev1, c->stream));
-        NM_TRY(hipMemcpyAsync(h.data(), c->dev.ehist, 8 * (size_t)chunk, hipMemcpyDeviceToHost, c->stream));
-        NM_TRY(hipStreamSynchronize(c->stream));
+        NM_TRY(c->io.read_words(c->dev.ehist, (size_t)chunk, c->stream));
         float ms = 0.0f;
         NM_TRY(hipEventElapsedTime(&ms, c->ev0, c->ev1));
         ms_total += ms;
@@ -2291,8 +2296,7 @@ extern "C" ccd_status ccd_nm_get_amplitudes(const ccd_nm_ctx* c, double* dst, si
         ccd::set_error("ccd_nm_get_amplitudes: no workspace");
         return CCD_ESTATE;
     }
-    NM_TRY(hipMemcpyAsync(dst, c->dev.t[c->cur], 8 * n, hipMemcpyDeviceToHost, c->stream));
-    NM_TRY(hipStreamSynchronize(c->stream));
+    NM_TRY(c->io.download(dst, c->dev.t[c->cur], 8 * n, c->stream));
     return CCD_OK;
 }
 
