@@ -372,6 +372,7 @@ template <bool BF16> __host__ __device__ constexpr size_t warm_lds() {
 template <bool BF16>
 __global__ void __launch_bounds__(256, 3) k_warm(DevPtrs d, int cur, const float* __restrict__ P, int n_items,
                                                 int max_g) {
+    constexpr int kNT = 2;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const mlp::Lds s = mlp::lds_carve<BF16>(lds);
     float* Fs = (float*)(lds + mlp::lds_bytes<BF16>());    // [kWarmChunk][kPack] features
@@ -406,15 +407,24 @@ __global__ void __launch_bounds__(256, 3) k_warm(DevPtrs d, int cur, const float
                 Vs[threadIdx.x] = v;
             }
             __syncthreads();
-            // wave w: amplitudes 64 w .. 64 w + 63 of the chunk, four per tile
-            for (int a0 = 64 * w; a0 < min(n, 64 * w + 64); a0 += 4) {
-                const float4* fr = (const float4*)&Fs[(a0 + ((lane & 15) >> 2)) * mlp::kPack];
-                const float4 f0 = fr[0], f1 = fr[1];
-                const float f[mlp::kPack] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-                const float y = mlp::tile_predict<BF16>(f, s, lane);
+            // wave w: amplitudes 64 w .. 64 w + 63 of the chunk, four per tile, kNT tiles
+            // at a time (Fs holds zeros beyond n)
+            for (int a0 = 64 * w; a0 < min(n, 64 * w + 64); a0 += 4 * kNT) {
+                float f[kNT][mlp::kPack], y[kNT];
+#pragma unroll
+                for (int k = 0; k < kNT; k++) {
+                    const float4* fr = (const float4*)&Fs[(a0 + 4 * k + ((lane & 15) >> 2)) * mlp::kPack];
+                    const float4 f0 = fr[0], f1 = fr[1];
+                    f[k][0] = f0.x; f[k][1] = f0.y; f[k][2] = f0.z; f[k][3] = f0.w;
+                    f[k][4] = f1.x; f[k][5] = f1.y; f[k][6] = f1.z; f[k][7] = f1.w;
+                }
+                mlp::tile_predict<BF16, kNT>(f, s, lane, y);
                 // lane 20 kq: A-operand row 4 kq, i.e. amplitude kq of the tile, variant 0
-                const int o = a0 + kq;
-                if ((lane & 15) == 4 * kq && o < n) tout[c0 + o] = (Vs[o] + (double)y / sc) / Ds[o];
+#pragma unroll
+                for (int k = 0; k < kNT; k++) {
+                    const int o = a0 + 4 * k + kq;
+                    if ((lane & 15) == 4 * kq && o < n) tout[c0 + o] = (Vs[o] + (double)y[k] / sc) / Ds[o];
+                }
             }
         }
     }

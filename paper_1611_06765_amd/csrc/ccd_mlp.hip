@@ -27,24 +27,54 @@ namespace {
     } while (0)
 
 // ---- forward on a buffer of packed features -----------------------------------
-// wave tiles of four amplitudes (16 rows); grid-stride over tiles
-template <bool BF16>
-__global__ void __launch_bounds__(256) k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ feat,
+// A wave takes NT tiles of four amplitudes (16 rows) at a time, the next ones'
+// features on their way meanwhile, and a grid of the blocks that fit the chip at
+// once (three per compute unit in BF16 at 168 registers, two in FP32) strides over
+// them, so W2 is staged once per resident block.  1 037 776 amplitudes in BF16: 275
+// us with one tile at a time, 2048 blocks and the accumulators in the AGPR file, 225
+// with two, 208 with 168 plain registers (four tiles 226, at two waves a SIMD; the
+// next step's layer 1 issued among this step's MFMAs 220); 60 000 amplitudes 33 ->
+// 22 us.  FP32 1336 -> 1205.  What is left is the activations' VALU time beside the
+// MFMAs (see tile_predict).
+template <bool BF16, int NT>
+__global__ void __launch_bounds__(256, 3) k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ feat,
                                                  int64_t n, float* __restrict__ y) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const Lds s = lds_carve<BF16>(lds);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int kAmps = 4 * NT;
+    const int64_t ngrp = (n + kAmps - 1) / kAmps, step = (int64_t)gridDim.x * 4;
+    float4 nx[NT][2];
+    auto fetch = [&](int64_t t) {
+#pragma unroll
+        for (int k = 0; k < NT; k++) {
+            const int64_t e = kAmps * t + 4 * k + ((lane & 15) >> 2);
+            nx[k][0] = nx[k][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (e < n) {
+                nx[k][0] = *(const float4*)&feat[e * kPack];
+                nx[k][1] = *(const float4*)&feat[e * kPack + 4];
+            }
+        }
+    };
+    int64_t t = (int64_t)blockIdx.x * 4 + w;
+    fetch(t);
     lds_load<BF16>(P, s, threadIdx.x, 256);
     __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t ntile = (n + 3) / 4;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + w; t < ntile; t += (int64_t)gridDim.x * 4) {
-        const int64_t e = 4 * t + ((lane & 15) >> 2);
-        float f[kPack];
+    for (; t < ngrp; t += step) {
+        float f[NT][kPack], yp[NT];
 #pragma unroll
-        for (int q = 0; q < kPack; q++) f[q] = e < n ? feat[e * kPack + q] : 0.0f;
-        const float yp = tile_predict<BF16>(f, s, lane);
-        const int64_t eo = 4 * t + (lane >> 4);
-        if ((lane & 15) == 0 && eo < n) y[eo] = yp;
+        for (int k = 0; k < NT; k++) {
+            const float4 a = nx[k][0], b = nx[k][1];
+            f[k][0] = a.x; f[k][1] = a.y; f[k][2] = a.z; f[k][3] = a.w;
+            f[k][4] = b.x; f[k][5] = b.y; f[k][6] = b.z; f[k][7] = b.w;
+        }
+        fetch(t + step);
+        tile_predict<BF16, NT>(f, s, lane, yp);
+#pragma unroll
+        for (int k = 0; k < NT; k++) {
+            const int64_t eo = kAmps * t + 4 * k + (lane >> 4);
+            if ((lane & 15) == 0 && eo < n) y[eo] = yp[k];
+        }
     }
 }
 
@@ -440,7 +470,9 @@ ccd_status grad_attrs() {
     if (done) return CCD_OK;
     MLP_TRY(hipFuncSetAttribute((const void*)k_mlp_grad, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)grad_lds_bytes()));
-    MLP_TRY(hipFuncSetAttribute((const void*)k_mlp_fwd<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    MLP_TRY(hipFuncSetAttribute((const void*)k_mlp_fwd<false, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds_bytes<false>()));
+    MLP_TRY(hipFuncSetAttribute((const void*)k_mlp_fwd<false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds_bytes<false>()));
     done = true;
     return CCD_OK;
@@ -466,14 +498,16 @@ ccd_status ccd_mlp_forward(const float* params, const float* feat, int64_t n, in
     if (n == 0) return CCD_OK;
     ccd_status s = grad_attrs();
     if (s != CCD_OK) return s;
+    // two tiles a wave once one each would give every wave of the chip two to four: below
+    // that half as many waves would only be slower (100 amplitudes in FP32 16.6 -> 20.4 us)
     const int64_t ntile = (n + 3) / 4;
-    const int grid = (int)std::min<int64_t>((ntile + 3) / 4, 2048);
-    if (precision == CCD_PREC_BF16)
-        hipLaunchKernelGGL(k_mlp_fwd<true>, dim3(grid), dim3(256), lds_bytes<true>(), (hipStream_t)stream, params,
-                           feat, n, y);
-    else
-        hipLaunchKernelGGL(k_mlp_fwd<false>, dim3(grid), dim3(256), lds_bytes<false>(), (hipStream_t)stream, params,
-                           feat, n, y);
+    const bool bf16 = precision == CCD_PREC_BF16, two = ntile > 4096;
+    const int64_t waves = two ? (ntile + 1) / 2 : ntile;
+    const int grid = (int)std::min<int64_t>((waves + 3) / 4, bf16 ? 768 : 512);
+    const auto k = bf16 ? (two ? k_mlp_fwd<true, 2> : k_mlp_fwd<true, 1>)
+                        : (two ? k_mlp_fwd<false, 2> : k_mlp_fwd<false, 1>);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), bf16 ? lds_bytes<true>() : lds_bytes<false>(), (hipStream_t)stream,
+                       params, feat, n, y);
     MLP_TRY(hipGetLastError());
     return CCD_OK;
 }

@@ -136,75 +136,121 @@ __device__ __forceinline__ void lds_load(const float* __restrict__ P, const Lds&
     }
 }
 
-// Prediction y of amplitude (lane >> 4) of a 16-row tile.  f: packed features
-// of the amplitude of this lane's A-operand row, i.e. amplitude (lane & 15) >> 2.
-// The result is valid in every lane of the 16-lane group.
-template <bool BF16>
-__device__ __forceinline__ float tile_predict(const float* f, const Lds& s, int lane) {
+// the value of the lane that a DPP control names (0xB1, 0x4E: lane ^ 1, lane ^ 2;
+// 0x141, 0x140: the mirror of a half row of eight, of a row of sixteen lanes)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+// sum over a row of sixteen lanes, valid in each: partners lane ^ 1, ^ 2, then, as
+// four and eight lanes agree by then, the mirror lane for ^ 4 and ^ 8
+__device__ __forceinline__ float row_sum(float x) {
+    x += dpp<0xB1>(x);
+    x += dpp<0x4E>(x);
+    x += dpp<0x141>(x);
+    x += dpp<0x140>(x);
+    return x;
+}
+
+// Predictions y[n] of amplitude (lane >> 4) of NT 16-row tiles.  f[n]: packed
+// features of the amplitude of this lane's A-operand row in tile n, i.e. amplitude
+// (lane & 15) >> 2.  The results are valid in every lane of the 16-lane group.
+//
+// BF16: a tile's 40 MFMAs take 640 cycles of a SIMD, the activations about 220 VALU
+// instructions (880 cycles), and W2 read from LDS for one tile at a time 1024 cycles
+// of the LDS that four SIMDs share; so NT tiles go through each operand read, and
+// the last layer's row sums use DPP instead of LDS permutes.
+template <bool BF16, int NT>
+__device__ __forceinline__ void tile_predict(const float (&f)[NT][kPack], const Lds& s, int lane, float (&y)[NT]) {
     const int row = lane & 15, kq = lane >> 4;
-    float x[7];
-    variant_inputs(f, row & 3, x);
-    f4v acc[8];
+    f4v acc[NT][8];
 #pragma unroll
-    for (int ct = 0; ct < 8; ct++) acc[ct] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < NT; n++)
+#pragma unroll
+        for (int ct = 0; ct < 8; ct++) acc[n][ct] = f4v{0.f, 0.f, 0.f, 0.f};
     if constexpr (BF16) {
         // layer 1, transposed: D[unit][row] = sum_k W1[unit][k] x_row[k].  Every
         // lane supplies W1's row 16 ct + row as A[row][8 kq .. 8 kq + 7]; the B
         // operand B[8 kq + j][row] is input j of this lane's own row in the
         // lanes of group 0 and zero in the others, so only K = 0..7 counts.
         // The lane receives units 16 ct + 4 (lane / 16) + i.
-        h8v xb;
+        h8v xb[NT];
 #pragma unroll
-        for (int j = 0; j < 7; j++) xb[j] = kq == 0 ? (_Float16)x[j] : (_Float16)0.f;
-        xb[7] = (_Float16)0.f;
-        const _Float16* W1h = (const _Float16*)s.W1;
-        bf8v a[4];
+        for (int n = 0; n < NT; n++) {
+            float x[7];
+            variant_inputs(f[n], row & 3, x);
 #pragma unroll
-        for (int ct = 0; ct < 8; ct++) {
-            const h8v wa = *(const h8v*)&W1h[(16 * ct + row) * kPack];
-            const f4v z = mfma_f16(wa, xb, f4v{0.f, 0.f, 0.f, 0.f});
-            const float4 bb = *(const float4*)&s.b1[16 * ct + 4 * kq];
-            // unit 16 ct + 4 kq + i is logical K index 8 kq + 4 (ct % 2) + i of step ct / 2
-            a[ct >> 1][4 * (ct & 1) + 0] = (__bf16)act(z[0] + bb.x);
-            a[ct >> 1][4 * (ct & 1) + 1] = (__bf16)act(z[1] + bb.y);
-            a[ct >> 1][4 * (ct & 1) + 2] = (__bf16)act(z[2] + bb.z);
-            a[ct >> 1][4 * (ct & 1) + 3] = (__bf16)act(z[3] + bb.w);
+            for (int j = 0; j < 7; j++) xb[n][j] = kq == 0 ? (_Float16)x[j] : (_Float16)0.f;
+            xb[n][7] = (_Float16)0.f;
         }
+        const _Float16* W1h = (const _Float16*)s.W1;
         const __bf16* W2 = (const __bf16*)s.W2;
 #pragma unroll
         for (int st = 0; st < 4; st++) {
+            bf8v a[NT];
+#pragma unroll
+            for (int c2 = 0; c2 < 2; c2++) {
+                const int ct = 2 * st + c2;
+                const h8v wa = *(const h8v*)&W1h[(16 * ct + row) * kPack];
+                const float4 bb = *(const float4*)&s.b1[16 * ct + 4 * kq];
+#pragma unroll
+                for (int n = 0; n < NT; n++) {
+                    const f4v z = mfma_f16(wa, xb[n], f4v{0.f, 0.f, 0.f, 0.f});
+                    // unit 16 ct + 4 kq + i is logical K index 8 kq + 4 (ct % 2) + i of step ct / 2
+                    a[n][4 * c2 + 0] = (__bf16)act(z[0] + bb.x);
+                    a[n][4 * c2 + 1] = (__bf16)act(z[1] + bb.y);
+                    a[n][4 * c2 + 2] = (__bf16)act(z[2] + bb.z);
+                    a[n][4 * c2 + 3] = (__bf16)act(z[3] + bb.w);
+                }
+            }
 #pragma unroll
             for (int ct = 0; ct < 8; ct++) {
                 const bf8v b = *(const bf8v*)&W2[(ct * 16 + row) * kLd16 + 32 * st + 8 * kq];
-                acc[ct] = mfma_bf16(a[st], b, acc[ct]);
+#pragma unroll
+                for (int n = 0; n < NT; n++) acc[n][ct] = mfma_bf16(a[n], b, acc[n][ct]);
             }
-            // keep the next step's W2 loads below this point (register pressure)
+            // keep the next step's loads below this point (register pressure)
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
+        float x[NT][7];
+#pragma unroll
+        for (int n = 0; n < NT; n++) variant_inputs(f[n], row & 3, x[n]);
         const float* W2 = (const float*)s.W2;
         for (int st = 0; st < 32; st++) {
             const int c = 4 * st + kq;
-            const float a = act(layer1(s.W1, s.b1, c, x));
+            float a[NT];
 #pragma unroll
-            for (int ct = 0; ct < 8; ct++) acc[ct] = mfma_f32(a, W2[(ct * 16 + row) * kLd32 + c], acc[ct]);
+            for (int n = 0; n < NT; n++) a[n] = act(layer1(s.W1, s.b1, c, x[n]));
+#pragma unroll
+            for (int ct = 0; ct < 8; ct++) {
+                const float b = W2[(ct * 16 + row) * kLd32 + c];
+#pragma unroll
+                for (int n = 0; n < NT; n++) acc[n][ct] = mfma_f32(a[n], b, acc[n][ct]);
+            }
         }
     }
     // accumulator lane layout: rows 4 kq + i (amplitude kq, variant i), column ct*16 + row
-    float gp[4] = {0.f, 0.f, 0.f, 0.f};
+    float gp[NT][4];
+#pragma unroll
+    for (int n = 0; n < NT; n++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) gp[n][i] = 0.f;
 #pragma unroll
     for (int ct = 0; ct < 8; ct++) {
         const int col = ct * 16 + row;
         const float b2 = s.b2[col], w3 = s.W3[col];
 #pragma unroll
-        for (int i = 0; i < 4; i++) gp[i] += act(acc[ct][i] + b2) * w3;
+        for (int n = 0; n < NT; n++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) gp[n][i] += act(acc[n][ct][i] + b2) * w3;
     }
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
+    for (int n = 0; n < NT; n++) {
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1) gp[i] += __shfl_xor(gp[i], o);
+        for (int i = 0; i < 4; i++) gp[n][i] = row_sum(gp[n][i]);
+        y[n] = 0.25f * ((gp[n][0] - gp[n][1]) - (gp[n][2] - gp[n][3]));
     }
-    return 0.25f * ((gp[0] - gp[1]) - (gp[2] - gp[3]));
 }
 
 }  // namespace mlp

@@ -259,3 +259,18 @@ def test_gradient_at_chunk_and_block_edges(n, area):
                    (inputs.OFF_B2, inputs.OFF_W3), (inputs.OFF_W3, inputs.OFF_B3)]:
         assert np.linalg.norm(g[lo:hi] - gw[lo:hi]) <= 1e-4 * np.linalg.norm(gw[lo:hi]), (lo, hi)
     assert np.all(g[inputs.OFF_B3:] == 0.0)
+
+
+@pytest.mark.parametrize("prec", [ccd.CCD_PREC_FP32, ccd.CCD_PREC_BF16])
+@pytest.mark.parametrize("n", [1, 4, 5, 16384, 16385, 16389, 16392, 70001])
+def test_forward_does_not_depend_on_the_tiles_per_wave(prec, n):
+    """Amplitudes are independent: one call over n of them (two tiles a wave above
+    16384) equals calls over pieces of 4000 (one tile a wave), bit for bit."""
+    torch = _torch()
+    g = torch.Generator().manual_seed(n)
+    feat = (2 * torch.rand(n, 8, generator=g) - 1).cuda()
+    p = _dev(_params())
+    y = ccd.mlp_forward(p, feat, prec)
+    ref = torch.cat([ccd.mlp_forward(p, feat[k:k + 4000].contiguous(), prec) for k in range(0, n, 4000)])
+    assert y.shape == (n,) and bool(torch.isfinite(y).all())
+    assert torch.equal(y, ref)
