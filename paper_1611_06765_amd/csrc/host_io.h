@@ -49,7 +49,7 @@ struct HostIO {
     bool init(size_t nwords) {
         words_cap = 8 * std::max<size_t>(nwords, 1);
         void* p = nullptr;
-        if (hipHostMalloc(&p, words_cap, hipHostMallocMapped) == hipSuccess) {
+        if (hipHostMalloc(&p, words_cap, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
             void* q = nullptr;
             if (hipHostGetDevicePointer(&q, p, 0) == hipSuccess) {
                 words = (char*)p;
@@ -62,7 +62,7 @@ struct HostIO {
         bool ok = true;
         for (hipEvent_t& e : ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
         p = nullptr;
-        if (ok && hipHostMalloc(&p, kSlot * kSlots, hipHostMallocMapped) == hipSuccess) {
+        if (ok && hipHostMalloc(&p, kSlot * kSlots, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
             void* q = nullptr;
             if (hipHostGetDevicePointer(&q, p, 0) == hipSuccess) {
                 stage = (char*)p;
