@@ -1536,21 +1536,27 @@ __global__ void __launch_bounds__(256, 3) k_mid(DevPtrs d, int cur, uint32_t mas
 //
 // The 16-row tiles of pairs map onto the four blocks of the instruction and the
 // 16-column tile is cut into NG groups of four columns (NG = 1 .. 4, the groups
-// that hold columns of the channel).  Eight waves: wave w owns pairs 32 (w % 4) ..
-// + 31 of the tile and every second 16-pair K step of a chunk (w / 4 says which),
-// since an item is a serial chain of K steps and one problem has few items; the
+// that hold columns of the channel).  T = 512, eight waves: wave w owns pairs
+// 32 (w % 4) .. + 31 of the tile and every second 16-pair K step of a chunk (w / 4
+// says which), since an item is a serial chain of K steps and one problem has few
+// items; with more of them than two rounds of the chip (kLadSplit) the waves come
+// from other items, and T = 256, four waves with both halves' sums in registers, has
+// half the staging and one epilogue (the sums are the same bits).  N=66, n^2<=36 (570
+// items) this launch 33 us with eight waves, 45 with four; a whole sweep of ten
+// densities at n^2<=20 (2120 items) 244.5 and 240, of the 40 solves 1121 and 1094.
+// With eight, the
 // two halves are added through LDS at the end.  Staging is pipelined one chunk
 // ahead: the column descriptors (with the two rows of each pair) of chunk c + 1
 // are in LDS while chunk c is multiplied, so its t loads are in flight then, and
 // delta is double-buffered, so a chunk takes one barrier.
-constexpr int kLadThreads = 512;
+constexpr int kLadW = 3;  // waves a SIMD of the 256-thread form
 struct Lad64 {
     double lutS[kMaxLut + 1];
     double tks[2][kKP * 16];   // delta of two chunks; at the end the halves' sums
     int4 cvi[3][kKP];          // column descriptors of three chunks
     int2 prs[kLadderRows];     // the two spin rows of the tile's pairs
 };
-template <int NG, bool CHI>
+template <int T, int NG, bool CHI>
 __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c, const DevGroup& G, int g, int cur,
                                               int r0, int ct, uint32_t mask, Lad64& L, double* chiS) {
     constexpr int S = 8;
@@ -1595,14 +1601,14 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
         return make_int4(times4(li.x), S * C2, S * (C2 + D2),
                          (int)((uint32_t)(li.z + 1) | ((uint32_t)(li.w + 1) << 16)));
     };
-    constexpr int kPer = kKP * 16 / kLadThreads;
+    constexpr int kPer = kKP * 16 / T;
     double tv[kPer];
     // delta of chunk kp from the rows in cvi[b]
     auto load_delta = [&](int kp, int b) {
         const int kn = min(kKP, nlp - kp);
 #pragma unroll
         for (int i = 0; i < kPer; i++) {
-            const int e = tid + kLadThreads * i, kk = e >> 4, cc = ct * 16 + (e & 15);
+            const int e = tid + T * i, kk = e >> 4, cc = ct * 16 + (e & 15);
             double v = 0.0;
             if (kk < kn && cc < nhh) {
                 const uint32_t rr = (uint32_t)L.cvi[b][kk].w;
@@ -1616,17 +1622,21 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
     };
     auto store_delta = [&](int b) {
 #pragma unroll
-        for (int i = 0; i < kPer; i++) L.tks[b][tid + kLadThreads * i] = tv[i];
+        for (int i = 0; i < kPer; i++) L.tks[b][tid + T * i] = tv[i];
     };
 
-    double acc[2][NG][2];
+    constexpr int HW = 512 / T;  // K halves of a wave
+    double acc[HW][2][NG][2];
 #pragma unroll
-    for (int h = 0; h < 2; h++)
+    for (int f = 0; f < HW; f++)
 #pragma unroll
-        for (int q = 0; q < NG; q++) { acc[h][q][0] = 0.0; acc[h][q][1] = 0.0; }
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int q = 0; q < NG; q++) { acc[f][h][q][0] = 0.0; acc[f][h][q][1] = 0.0; }
 
     const double* lutg = d.lut + G.lut_base + g * G.nlut;
     const double lv0 = tid < G.nlut ? lutg[tid] : 0.0;
+    const double lv1 = T < kMaxLut && tid < G.nlut - T ? lutg[T + tid] : 0.0;  // (n^2<=64 has 257 entries)
     int4 lpc = cpad;
     if (pp_on && tid < kKP && tid < nlp) lpc = lp[tid];
     // the two spin rows of the tile's pairs, for the hh operands and the stores
@@ -1634,6 +1644,7 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
     const int2 myr = (tid < kLadderRows && r0 + tid < nlp) ? lpr[2 * (r0 + tid) + 1] : make_int2(-1, -1);
     __syncthreads();  // the previous item's reads of LDS are done
     if (tid < kMaxLut) L.lutS[tid] = lv0;
+    if (T < kMaxLut && tid < kMaxLut - T) L.lutS[T + tid] = lv1;
     if (tid < kLadderRows) L.prs[tid] = myr;
     if constexpr (CHI)
         if (hh_on) chi_slice(d, c, G, g, ct, mask, chiS);
@@ -1661,38 +1672,43 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
             const int ksteps = (kn + 15) & ~15;
             const double* tk = L.tks[b];
             for (int kk = 16 * kh; kk < ksteps; kk += 32) {
-                int o1[2][4], o2[2][4];
 #pragma unroll
-                for (int s2 = 0; s2 < 4; s2++) {
-                    const int4 ci = L.cvi[b3][kk + 4 * s2 + (lane >> 4)];
+                for (int f = 0; f < HW; f++) {
+                    const int ks = kk + 16 * f;
+                    if (f && ks >= ksteps) break;
+                    int o1[2][4], o2[2][4];
 #pragma unroll
-                    for (int h = 0; h < 2; h++) {
-                        o1[h][s2] = __builtin_amdgcn_sdot4(apack[h], ci.x, rowA[h] + ci.y, false);
-                        o2[h][s2] = rowS[h] + ci.z - o1[h][s2];
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int s4 = 0; s4 < 4; s4 += 2) {
-                    double x1[2][2], x2[2][2], vb[2][NG];
-#pragma unroll
-                    for (int s2 = 0; s2 < 2; s2++) {
+                    for (int s2 = 0; s2 < 4; s2++) {
+                        const int4 ci = L.cvi[b3][ks + 4 * s2 + (lane >> 4)];
 #pragma unroll
                         for (int h = 0; h < 2; h++) {
-                            x1[h][s2] = *(const double*)(lutB + o1[h][s4 + s2]);
-                            x2[h][s2] = *(const double*)(lutB + o2[h][s4 + s2]);
+                            o1[h][s2] = __builtin_amdgcn_sdot4(apack[h], ci.x, rowA[h] + ci.y, false);
+                            o2[h][s2] = rowS[h] + ci.z - o1[h][s2];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int s4 = 0; s4 < 4; s4 += 2) {
+                        double x1[2][2], x2[2][2], vb[2][NG];
+#pragma unroll
+                        for (int s2 = 0; s2 < 2; s2++) {
+#pragma unroll
+                            for (int h = 0; h < 2; h++) {
+                                x1[h][s2] = *(const double*)(lutB + o1[h][s4 + s2]);
+                                x2[h][s2] = *(const double*)(lutB + o2[h][s4 + s2]);
+                            }
+#pragma unroll
+                            for (int q = 0; q < NG; q++)
+                                vb[s2][q] = tk[(ks + 4 * (s4 + s2) + (lane >> 4)) * 16 + 4 * q + bj];
                         }
 #pragma unroll
-                        for (int q = 0; q < NG; q++)
-                            vb[s2][q] = tk[(kk + 4 * (s4 + s2) + (lane >> 4)) * 16 + 4 * q + bj];
-                    }
+                        for (int s2 = 0; s2 < 2; s2++) {
 #pragma unroll
-                    for (int s2 = 0; s2 < 2; s2++) {
+                            for (int h = 0; h < 2; h++) {
+                                const double va = x1[h][s2] + x2[h][s2];
 #pragma unroll
-                        for (int h = 0; h < 2; h++) {
-                            const double va = x1[h][s2] + x2[h][s2];
-#pragma unroll
-                            for (int q = 0; q < NG; q++) acc[h][q][s2] = mfma4(va, vb[s2][q], acc[h][q][s2]);
+                                for (int q = 0; q < NG; q++) acc[f][h][q][s2] = mfma4(va, vb[s2][q], acc[f][h][q][s2]);
+                            }
                         }
                     }
                 }
@@ -1705,9 +1721,12 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
         for (int h = 0; h < 2; h++)
 #pragma unroll
             for (int q = 0; q < NG; q++) {
-                const double u = acc[h][q][0] + acc[h][q][1];
-                acc[h][q][0] = u;
-                acc[h][q][1] = -u;
+#pragma unroll
+                for (int f = 0; f < HW; f++) {
+                    const double u = acc[f][h][q][0] + acc[f][h][q][1];
+                    acc[f][h][q][0] = u;
+                    acc[f][h][q][1] = -u;
+                }
             }
     }
     if (hh_on) {
@@ -1720,24 +1739,42 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
         }
         const double* xg = d.chh + G.chh_base + g * G.n_chh + c.chh_off;
         for (int k0 = 4 * kh; k0 < nhh; k0 += 8) {
-            const int kq = k0 + (lane >> 4);
-            double bb[NG];
+#pragma unroll
+            for (int f = 0; f < HW; f++) {
+                if (f && k0 + 4 >= nhh) break;
+                const int kq = k0 + 4 * f + (lane >> 4);
+                double bb[NG];
+#pragma unroll
+                for (int q = 0; q < NG; q++) {
+                    const int cc = ct * 16 + 4 * q + bj;
+                    if constexpr (CHI) bb[q] = (kq < nhh && cc < nhh) ? chiS[16 * kq + 4 * q + bj] : 0.0;
+                    else bb[q] = (kq < nhh && cc < nhh) ? xg[kq * nhh + cc] : 0.0;
+                }
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int s = 0; s < 2; s++) {
+                        const int r = arow[h][s];
+                        const double a = (r >= 0 && kq < nhh) ? tcur[(int64_t)r * nhh + kq] : 0.0;
+#pragma unroll
+                        for (int q = 0; q < NG; q++) acc[f][h][q][s] = mfma4(a, bb[q], acc[f][h][q][s]);
+                    }
+            }
+        }
+    }
+    if constexpr (HW == 2) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int2 ro = L.prs[32 * w + 16 * h + orow4];
 #pragma unroll
             for (int q = 0; q < NG; q++) {
                 const int cc = ct * 16 + 4 * q + bj;
-                if constexpr (CHI) bb[q] = (kq < nhh && cc < nhh) ? chiS[16 * kq + 4 * q + bj] : 0.0;
-                else bb[q] = (kq < nhh && cc < nhh) ? xg[kq * nhh + cc] : 0.0;
+                if (cc >= nhh) continue;
+                if (ro.x >= 0) d.rmm[T0 + (int64_t)ro.x * nhh + cc] = acc[0][h][q][0] + acc[HW - 1][h][q][0];
+                if (ro.y >= 0) d.rmm[T0 + (int64_t)ro.y * nhh + cc] = acc[0][h][q][1] + acc[HW - 1][h][q][1];
             }
-#pragma unroll
-            for (int h = 0; h < 2; h++)
-#pragma unroll
-                for (int s = 0; s < 2; s++) {
-                    const int r = arow[h][s];
-                    const double a = (r >= 0 && kq < nhh) ? tcur[(int64_t)r * nhh + kq] : 0.0;
-#pragma unroll
-                    for (int q = 0; q < NG; q++) acc[h][q][s] = mfma4(a, bb[q], acc[h][q][s]);
-                }
         }
+        return;
     }
     // add the two halves: waves of half 0 finish the + rows, of half 1 the - rows
     double* x0 = &L.tks[0][0];
@@ -1746,7 +1783,7 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
     for (int h = 0; h < 2; h++)
 #pragma unroll
         for (int q = 0; q < NG; q++)
-            x0[kh * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane] = kh ? acc[h][q][0] : acc[h][q][1];
+            x0[kh * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane] = kh ? acc[0][h][q][0] : acc[0][h][q][1];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; h++) {
@@ -1757,13 +1794,13 @@ __device__ __forceinline__ void ladder64_item(const DevPtrs& d, const DevChan& c
             const int cc = ct * 16 + 4 * q + bj;
             const double other = x0[(kh ^ 1) * kKP * 16 + ((w * 2 + h) * 4 + q) * 64 + lane];
             // half 0's share first in both
-            const double v = kh ? other + acc[h][q][1] : acc[h][q][0] + other;
+            const double v = kh ? other + acc[0][h][q][1] : acc[0][h][q][0] + other;
             if (r >= 0 && cc < nhh) d.rmm[T0 + (int64_t)r * nhh + cc] = v;
         }
     }
 }
 
-template <bool CHI>
+template <int T, bool CHI>
 __device__ __forceinline__ void ladder64_run(const DevPtrs& d, int cur, uint32_t mask, int bi, Lad64& L, double* chiS) {
     const Item lg = uni(d.it_lg[bi]);
     if (lg.chan < 0) return;
@@ -1776,26 +1813,31 @@ __device__ __forceinline__ void ladder64_run(const DevPtrs& d, int cur, uint32_t
     // groups of four columns of this column tile that hold columns
     const int ng = min(4, (min(16, c.nhh - 16 * ct) + 3) >> 2);
     switch (ng) {
-        case 1: ladder64_item<1, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
-        case 2: ladder64_item<2, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
-        case 3: ladder64_item<3, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
-        default: ladder64_item<4, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        case 1: ladder64_item<T, 1, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        case 2: ladder64_item<T, 2, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        case 3: ladder64_item<T, 3, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
+        default: ladder64_item<T, 4, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
     }
 }
-__global__ void __launch_bounds__(kLadThreads, 4) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
+__global__ void __launch_bounds__(512, 4) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
     __shared__ Lad64 L;
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) ladder64_run<false>(d, cur, mask, bi, L, nullptr);
+    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) ladder64_run<512, false>(d, cur, mask, bi, L, nullptr);
+}
+__global__ void __launch_bounds__(256, kLadW) k_ladder64_w4(DevPtrs d, int cur, uint32_t mask, int n_items) {
+    __shared__ Lad64 L;
+    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) ladder64_run<256, false>(d, cur, mask, bi, L, nullptr);
 }
 // the second launch of a sweep on one stream: ladder items, then (blocks nl, ...)
-// the one-body items, two per block; chi_klij comes from the product items' parts
-__global__ void __launch_bounds__(kLadThreads, 4) k_mid64(DevPtrs d, int cur, uint32_t mask, int nl, int no) {
+// the one-body items, one per 256 threads; chi_klij comes from the product items' parts
+template <int T>
+__global__ void __launch_bounds__(T, T == 512 ? 4 : kLadW) k_mid64(DevPtrs d, int cur, uint32_t mask, int nl, int no) {
     __shared__ Lad64 L;
     __shared__ double chiS[16 * kMaxHH];
     const int b = blockIdx.x;
     if (b < nl) {
-        ladder64_run<true>(d, cur, mask, b, L, chiS);
+        ladder64_run<T, true>(d, cur, mask, b, L, chiS);
     } else {
-        const int k = 2 * (b - nl) + (threadIdx.x >> 8);
+        const int k = T / 256 * (b - nl) + (threadIdx.x >> 8);
         if (k < no) dchi_item<true>(d, d.it_dchi[k], mask);
     }
 }
@@ -2700,12 +2742,16 @@ static ccd_status L_ring(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask, i
     return s;
 }
 
+constexpr int kLadSplit = 1024;  // ladder items above which four waves take one (see ladder64_item)
 template <int P>
 static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
     const int n = (int)c->it_lg.size();
     if (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) {
         if constexpr (P == P_F64) {
-            LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), kLadThreads, 0, d, cur, mask, n);
+            if (n <= kLadSplit)
+                LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), 512, 0, d, cur, mask, n);
+            else
+                LAUNCH(F_LADDER, k_ladder64_w4, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
         } else {
             LAUNCH(F_LADDER, k_ladder<P>, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
         }
@@ -2765,7 +2811,10 @@ static ccd_status launch_one_stream(ccd_ctx* c, const DevPtrs& d, int cur, uint3
     const int nl = (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) ? l.n[kListLadder] : 0;
     const int no = l.n[kListOneBody];
     if constexpr (P == P_F64)
-        LAUNCH(F_LADDER, k_mid64, nl + (no + 1) / 2, kLadThreads, 0, d, cur, mask, nl, no);
+        if (nl <= kLadSplit)
+            LAUNCH(F_LADDER, k_mid64<512>, nl + (no + 1) / 2, 512, 0, d, cur, mask, nl, no);
+        else
+            LAUNCH(F_LADDER, k_mid64<256>, nl + no, 256, 0, d, cur, mask, nl, no);
     else
         LAUNCH(F_LADDER, k_mid<P>, nl + no, 256, 0, d, cur, mask, nl, no);
     return CCD_OK;

@@ -291,3 +291,22 @@ def test_problems_that_stop_early_equal_their_own_contexts(specs, prec, every):
             assert np.array_equal(run[2][p], ref[2][0])
             assert np.array_equal(run[3][p], ref[3][0])
             assert np.array_equal(run[4][p], ref[4][0])
+
+
+@pytest.mark.parametrize("specs", [[(14, 64, r) for r in np.linspace(0.05, 0.2, 14)],
+                                   [(38, 12, r) for r in np.linspace(0.05, 0.2, 12)] + [(2, 64, 0.1)]],
+                         ids=["14_64", "38_12"])
+def test_ladder_on_four_waves_equals_eight(specs):
+    """Batches with more than 1024 ladder items (four waves an item) against each
+    problem alone (eight), bit for bit, also at the largest cutoff's table of 257
+    entries: the pp ladder, the hh ladder and all terms."""
+    probs = [ccd.problem(*x) for x in specs]
+    batch = _ctx(probs)
+    for mask in (1, 18, 127):
+        batch.reset_amplitudes()
+        e = batch.iterate(mixing=0.5, max_iter=3, terms=mask, history=True)["history"]
+        for p in (0, len(probs) // 2, len(probs) - 1):
+            alone = _ctx([probs[p]])
+            r = alone.iterate(mixing=0.5, max_iter=3, terms=mask, history=True)
+            assert np.array_equal(e[p], r["history"][0]), (mask, p)
+            assert np.array_equal(batch.get_amplitudes(p), alone.get_amplitudes(0)), (mask, p)
