@@ -1127,11 +1127,12 @@ __global__ void __launch_bounds__(64 * NW) k_ringp(DevPtrs d, int cur, uint32_t 
 // none of it.  512 threads: a product item, a pair of order 48 .. 80 on eight
 // waves, two pairs of order 32 on four each, or eight small pairs on one each; 128
 // registers and at most 80 KB of LDS (except for pairs beyond order 68), two
-// blocks per compute unit.  A sweep in us, nine launches over four streams -> three
-// launches on one: N=14, n^2<=4 94 -> 20; N=54, n^2<=36 112 -> 98; N=66, n^2<=20 115
-// -> 67 (five densities 165 -> 140, ten 248 -> 247); N=66, n^2<=36 141 -> 123 (three
-// 288 -> 266).  This launch takes 62 us at N=66, n^2<=36 and 154 us for the ten
-// densities, where the ring's gathers and scattered stores (460 MB) bound it.
+// blocks per compute unit.  A sweep in us, nine launches over four streams -> these
+// three with the ladder and update below: N=14, n^2<=4 94 -> 19; N=54, n^2<=36 112 ->
+// 84; N=66, n^2<=20 115 -> 52 (five densities 165 -> 137, ten 248 -> 240); N=66,
+// n^2<=36 141 -> 104 (three 288 -> 256).  This launch takes 61 us at N=66, n^2<=36 and
+// 162 us for the ten densities, where the ring's gathers and scattered stores (521 MB)
+// bound it.
 constexpr int kFrontThreads = 512;
 struct Front {
     int nd;             // blocks of product items
