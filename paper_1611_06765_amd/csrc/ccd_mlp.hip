@@ -186,7 +186,8 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(
     for (int j = 0; j < 4; j++)
 #pragma unroll
         for (int q = 0; q < 7; q++) aW1[j][q] = 0.f;
-    float loss = 0.f;
+    // in 64 bits: a lane adds a term per chunk, and a block's run of chunks grows with the batch
+    double loss = 0.0;
 
     for (int64_t e = e0; e < e1; e += kCh) {
         __syncthreads();  // previous chunk done with Fs, H1, DZ2, Gs
@@ -251,7 +252,7 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(
         for (int i = 0; i < 4; i++) g[i] = Gs[4 * el + i] + Gs[4 * kCh + 4 * el + i];
         const float yp = 0.25f * ((g[0] - g[1]) - (g[2] - g[3]));
         const float res = Vs[el] != 0.f ? yp - Ys[el] : 0.f;
-        if (ch == 0 && r16 == 0) loss += 0.5f * res * res * inv_m;
+        if (ch == 0 && r16 == 0) loss += (double)(0.5f * res * res * inv_m);
         float dg[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) dg[i] = variant_sign(i) * 0.25f * res * inv_m;
@@ -364,9 +365,10 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(
     // loss: lanes r16 == 0 of waves ch == 0 hold it
     loss += __shfl_xor(loss, 16);
     loss += __shfl_xor(loss, 32);
-    if (ch == 0 && lane == 0) Gs[rt] = loss;
+    double* Ls = (double*)Gs;
+    if (ch == 0 && lane == 0) Ls[rt] = loss;
     __syncthreads();
-    if (tid == 0) work_loss[blockIdx.x] = (Gs[0] + Gs[1]) + (Gs[2] + Gs[3]);
+    if (tid == 0) work_loss[blockIdx.x] = (float)((Ls[0] + Ls[1]) + (Ls[2] + Ls[3]));
 }
 
 // sum of the block partials (fixed order: four quarters of the rows, each in

@@ -274,3 +274,24 @@ def test_forward_does_not_depend_on_the_tiles_per_wave(prec, n):
     ref = torch.cat([ccd.mlp_forward(p, feat[k:k + 4000].contiguous(), prec) for k in range(0, n, 4000)])
     assert y.shape == (n,) and bool(torch.isfinite(y).all())
     assert torch.equal(y, ref)
+
+
+@pytest.mark.parametrize("entry", ["loss_grad", "train"])
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_loss_of_many_equal_rows_is_that_of_a_chunk(entry, seed):
+    """2^22 copies of one row: every term is a power of two times that of 16
+    copies, so all sums in 64 bits are exact, and a block's sum, rounded to 32
+    bits once, is the same up to 2^-23."""
+    torch = _torch()
+    p = _params(seed=31, scale=1.5)
+    f1 = _rand_feats(1, seed=seed)
+    loss = []
+    for n in (16, 1 << 22):
+        P, F = _dev(p), _dev(f1).expand(n, 8).contiguous()
+        Y = torch.full((n,), 0.317, device="cuda")
+        if entry == "loss_grad":
+            loss.append(ccd.mlp_loss_grad(P, F, Y)[0])
+        else:
+            order = torch.arange(n, dtype=torch.int32, device="cuda")
+            loss.append(ccd.mlp_train(P, ccd.AdamState(P), F, Y, order, n, 1e-3))
+    assert loss[0] > 0.0 and abs(loss[1] - loss[0]) <= 2.0 ** -23 * loss[0]
