@@ -962,10 +962,8 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
     PairCtx r;
     r.nq = 0; r.np = 0; r.self = false; r.map = nullptr; r.t = nullptr; r.zc = nullptr; r.zs = nullptr;
     int32_t memQ = 0, memP = 0, lo = 0, nlut = 0;
-    // every wave reaches every barrier below; only the work is guarded by live.  An
-    // energy block of this launch may clear the flag meanwhile: waves that read it
-    // at different times leave values that the update of a stopped problem skips
-    const bool live = it.chan >= 0 && pair_ctx(d, it, cur, r, memQ, memP, lo, nlut);
+    // every wave reaches every barrier below; only the work is guarded by live
+    bool live = it.chan >= 0 && pair_ctx(d, it, cur, r, memQ, memP, lo, nlut);
     const int lane = tid & 63, w = tid >> 6;
     if (lane == 0) live_s[threadIdx.x >> 6] = live;
     double* lutS = (double*)lds;
@@ -991,9 +989,16 @@ __device__ __forceinline__ void pair_body(const DevPtrs& d, const Item it, int c
         }
     }
     __syncthreads();
-    int any = 0;
-    for (int k = 0; k < waves; k++) any |= live_s[k];
-    if (!any) return;  // all of the block's items belong to stopped problems
+    int seen = 0;  // bit k: wave k of the block saw its problem iterating
+    for (int k = 0; k < waves; k++) seen |= live_s[k] << k;
+    seen = __builtin_amdgcn_readfirstlane(seen);
+    if (!seen) return;  // all of the block's items belong to stopped problems
+    // An energy block of this launch may have cleared the flag between two waves'
+    // reads of it.  A wave that saw it cleared has staged nothing, so the item's
+    // waves all go by the same answer: stopped if one of them saw that (the update
+    // skips a stopped problem's values).
+    constexpr int kAll = (1 << NW) - 1;
+    live = ((seen >> __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) - w)) & kAll) == kAll;
     // W(|Q|^2)/2, the first table entry of every element of the pair (member 0
     // of Q: hole qs[1], particle qs[0])
     const double wq = live ? lutS[dist2(qs[1], qs[0])] : 0.0;
