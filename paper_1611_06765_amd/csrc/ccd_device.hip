@@ -3170,7 +3170,7 @@ ccd_status ccd_bind_workspace(ccd_ctx* c, void* ptr, size_t bytes) {
     HIP_TRY(hipMemcpyAsync(c->ws + c->r_static.off, img.data(), img.size(), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipMemsetAsync(c->ws + c->r_t0.off, 0, c->ws_bytes - c->r_t0.off, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (!c->io.words && !c->io.init((c->r_ehist.off + c->r_ehist.bytes + 7 - c->r_ecorr.off) / 8)) {
+    if (!c->io.words && !c->io.init((c->r_ehist.off + c->r_ehist.bytes + 7 - c->r_ecorr.off) / 8, c->ws)) {
         set_error("ccd_bind_workspace: no host memory");
         return CCD_EHIP;
     }
@@ -3404,10 +3404,10 @@ ccd_status ccd_energy(const ccd_ctx* cc, int32_t p, double* eref, double* emp2, 
     if (eref) *eref = c->probs[p].eref;
     if (emp2 || ecorr) {
         if (!c->bound) { set_error("ccd_energy: no workspace bound"); return CCD_ESTATE; }
-        const ccd_status s = read_state(c, c->r_ecorr);
-        if (s != CCD_OK) return s;
+        std::vector<double> e(c->probs.size());
+        HIP_TRY(c->io.read_words(c->ws + c->r_ecorr.off, e.size(), c->stream, e.data()));
         if (emp2) *emp2 = c->emp2[p];
-        if (ecorr) *ecorr = state<double>(c, c->r_ecorr)[c->slot_of[p]];
+        if (ecorr) *ecorr = e[c->slot_of[p]];
     }
     return CCD_OK;
 }
@@ -3424,9 +3424,8 @@ ccd_status ccd_twist_average(const ccd_ctx* cc, const double* weight, double* ou
     if (!c || !weight || !out) { set_error("ccd_twist_average: NULL argument"); return CCD_EINVAL; }
     if (!c->bound) { set_error("ccd_twist_average: no workspace bound"); return CCD_ESTATE; }
     const size_t P = c->probs.size();
-    const ccd_status s = read_state(c, c->r_ecorr);
-    if (s != CCD_OK) return s;
-    const double* ec = state<double>(c, c->r_ecorr);
+    std::vector<double> ec(P);
+    HIP_TRY(c->io.read_words(c->ws + c->r_ecorr.off, P, c->stream, ec.data()));
     double acc[5] = {0, 0, 0, 0, 0};
     for (size_t p = 0; p < P; p++) {
         const HostProblem& H = c->probs[p];

@@ -32,7 +32,8 @@ struct HostIO {
     char* stage = nullptr;  // kSlots pinned slots, or null: none to be had
     char* stage_d = nullptr;
     hipEvent_t ev[kSlots] = {};
-    std::mutex mu;  // several threads may read one context
+    int device = -1;  // of the memory that is read
+    std::mutex mu;    // of the slots and of `words` until they are copied out
 
     HostIO() = default;
     HostIO(const HostIO&) = delete;
@@ -45,8 +46,11 @@ struct HostIO {
         if (stage) (void)hipHostFree(stage);
     }
 
-    // without pinned memory or events the plain copies stay; false: no memory at all
-    bool init(size_t nwords) {
+    // without pinned memory or events the plain copies stay; false: no memory at all.
+    // mem: the device memory that will be read
+    bool init(size_t nwords, const void* mem) {
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, mem) == hipSuccess) device = at.device;
         words_cap = 8 * std::max<size_t>(nwords, 1);
         void* p = nullptr;
         if (hipHostMalloc(&p, words_cap, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
@@ -75,10 +79,17 @@ struct HostIO {
         return words != nullptr;
     }
 
-    // the first n words at src into `words`, after all work on s
-    hipError_t read_words(const void* src, size_t n, hipStream_t s) {
+    // A caller may read a context while another GPU is current.  The null stream is
+    // then that GPU's, and a kernel there cannot reach this memory; a copy can.
+    bool here() const {
+        int d = -1;
+        return hipGetDevice(&d) == hipSuccess && d == device;
+    }
+
+    // the first n words at src into `words` (and to out), after all work on s
+    hipError_t read_words(const void* src, size_t n, hipStream_t s, void* out = nullptr) {
         std::lock_guard<std::mutex> lock(mu);
-        if (words_d) {
+        if (words_d && here()) {
             k_words_out<<<dim3((unsigned)std::min<size_t>((n + 1023) / 1024, 64)), 256, 0, s>>>(
                 (double*)words_d, (const double*)src, (int)n);
             hipError_t e = hipGetLastError();
@@ -87,13 +98,15 @@ struct HostIO {
             hipError_t e = hipMemcpyAsync(words, src, 8 * n, hipMemcpyDeviceToHost, s);
             if (e != hipSuccess) return e;
         }
-        return hipStreamSynchronize(s);
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e == hipSuccess && out) std::memcpy(out, words, 8 * n);
+        return e;
     }
 
     // bytes (a multiple of 8) from device memory to dst, after all work on s
     hipError_t download(void* dst, const void* src, size_t bytes, hipStream_t s) {
         std::lock_guard<std::mutex> lock(mu);
-        if (!stage) {
+        if (!stage || !here()) {
             hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
             return e == hipSuccess ? hipStreamSynchronize(s) : e;
         }
