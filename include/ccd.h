@@ -163,9 +163,11 @@ ccd_status ccd_workspace_size(const ccd_ctx* ctx, size_t* bytes);
  * by the caller (e.g. a torch uint8 tensor) and kept alive until ccd_destroy.
  * Uploads the tables, then on the device builds <ab||ij>, the MBPT2 amplitudes
  * t0 = <ab||ij>/eps_ij^ab and the MBPT2 energy (eq. ccdGuess).  The library
- * itself allocates no device memory; the context holds 2 MiB of pinned host
- * memory for its transfers until ccd_destroy.  Errors: CCD_EINVAL (NULL / too small /
- * misaligned: 256-byte alignment required), CCD_EHIP, CCD_ESTATE (bound twice). */
+ * itself allocates no device memory; the context holds pinned host memory for its
+ * transfers until ccd_destroy (the size of its largest problem's amplitudes, at most
+ * 2 MiB, and that of its energies and flags).  Errors:
+ * CCD_EINVAL (NULL / too small / misaligned: 256-byte alignment required),
+ * CCD_EHIP, CCD_ESTATE (bound twice). */
 ccd_status ccd_bind_workspace(ccd_ctx* ctx, void* device_ptr, size_t bytes);
 
 /* Jacobi sweeps of eq. ccd3 in the intermediates form on the GPU (every term

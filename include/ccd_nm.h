@@ -74,7 +74,9 @@ ccd_status ccd_nm_info_get(const ccd_nm_ctx* ctx, ccd_nm_info* info);
 ccd_status ccd_nm_workspace_size(const ccd_nm_ctx* ctx, size_t* bytes);
 /* Caller-owned device memory of ccd_nm_workspace_size bytes, 256-byte aligned,
  * kept alive until ccd_nm_destroy.  Uploads the tables and builds <ab||ij>, the
- * MBPT2 amplitudes and energy (eq. ccdGuess) on the device. */
+ * MBPT2 amplitudes and energy (eq. ccdGuess) on the device.  Until ccd_nm_destroy
+ * the context holds pinned host memory for its transfers (the size of the
+ * amplitudes, at most 2 MiB). */
 ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* ctx, void* device_ptr, size_t bytes);
 /* Jacobi sweeps of eq. ccd3 in the intermediates form (FP64; opts: mixing,
  * tol, tol_rel, max_iter and terms are used, the rest ignored).  sweeps_done

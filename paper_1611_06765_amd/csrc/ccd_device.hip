@@ -3170,7 +3170,9 @@ ccd_status ccd_bind_workspace(ccd_ctx* c, void* ptr, size_t bytes) {
     HIP_TRY(hipMemcpyAsync(c->ws + c->r_static.off, img.data(), img.size(), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipMemsetAsync(c->ws + c->r_t0.off, 0, c->ws_bytes - c->r_t0.off, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (!c->io.words && !c->io.init((c->r_ehist.off + c->r_ehist.bytes + 7 - c->r_ecorr.off) / 8, c->ws)) {
+    size_t stage = 0;
+    for (const HostProblem& H : c->probs) stage = std::max(stage, HostIO::stage_of(8 * (size_t)H.n_amp));
+    if (!c->io.words && !c->io.init((c->r_ehist.off + c->r_ehist.bytes + 7 - c->r_ecorr.off) / 8, stage, c->ws)) {
         set_error("ccd_bind_workspace: no host memory");
         return CCD_EHIP;
     }

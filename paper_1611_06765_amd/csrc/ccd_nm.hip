@@ -2117,7 +2117,7 @@ extern "C" ccd_status ccd_nm_bind_workspace(ccd_nm_ctx* c, void* ptr, size_t byt
         ccd::set_error("ccd_nm_bind_workspace: already bound");
         return CCD_ESTATE;
     }
-    if (!c->io.words && !c->io.init(kNmHist, ptr)) {
+    if (!c->io.words && !c->io.init(kNmHist, ccd::HostIO::stage_of(8 * (size_t)c->n_amp), ptr)) {
         ccd::set_error("ccd_nm_bind_workspace: no host memory");
         return CCD_EHIP;
     }

@@ -310,3 +310,22 @@ def test_ladder_on_four_waves_equals_eight(specs):
             r = alone.iterate(mixing=0.5, max_iter=3, terms=mask, history=True)
             assert np.array_equal(e[p], r["history"][0]), (mask, p)
             assert np.array_equal(batch.get_amplitudes(p), alone.get_amplitudes(0)), (mask, p)
+
+
+@pytest.mark.parametrize("specs", [[(14, 4, 0.1)], [(14, 12, 0.1)], [(54, 16, 0.1)], [(66, 36, 0.1)],
+                                   [(54, 16, 0.1), (14, 4, 0.1), (14, 12, 0.1), (2, 1, 0.1)],
+                                   [(14, 12, 0.1), (14, 4, 0.1)]],
+                         ids=lambda s: "-".join(f"{x[0]}_{x[1]}" for x in s))
+def test_amplitudes_come_back_as_they_were_set(specs):
+    """Downloads of 6 and 68 KB (one kernel into pinned memory of that size), 1.0 and
+    7.9 MB (through two and four slots, the last one partly filled), alone and in
+    contexts whose other problems need another area: the same bits."""
+    c = _ctx([ccd.problem(*x) for x in specs])
+    rng = np.random.default_rng(5)
+    t = [rng.normal(0.0, 1e-2, c.info(p)["n_amplitudes"]) for p in range(c.n)]
+    for _ in range(2):
+        for p in range(c.n):
+            c.set_amplitudes(t[p], p)
+        for p in range(c.n):
+            assert np.array_equal(c.get_amplitudes(p), t[p]), p
+        t = [x[::-1].copy() for x in t]

@@ -176,3 +176,13 @@ def test_ring_by_size_of_the_cross_channels(orc, A, n2, sweeps):
         assert _amplitudes_match(c2, o3), mask
     lo, hi = {4: (1, 16), 28: (17, 32), 76: (33, 64), 108: (65, 112), 132: (113, 1000)}[A]
     assert lo <= c.info()["max_ph"] <= hi
+
+
+@pytest.mark.parametrize("A,n2", [(4, 4), (28, 4), (76, 12)])
+def test_amplitudes_come_back_as_they_were_set(A, n2):
+    """Downloads of 2 KB, 36 KB and 2.2 MB: one kernel, or four slots."""
+    c = _ctx(A, n2, 0.2)
+    t = np.random.default_rng(6).normal(0.0, 1e-2, c.info()["n_amplitudes"])
+    for x in (t, t[::-1].copy()):
+        c.set_amplitudes(x)
+        assert np.array_equal(c.get_amplitudes(), x)
