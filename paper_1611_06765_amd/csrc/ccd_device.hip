@@ -498,17 +498,17 @@ __device__ __forceinline__ DirItem dir_item(const DevPtrs& d, const DevChan& c, 
     return r;
 }
 
-// FP64: direct64 on eight waves
-constexpr int kDirThreads = 512;
-
-// The mixed modes: FP64 in LDS, converted at the FP32 MFMA, on the first four
-// waves of the block.  The staging row stride follows the channel's tiles, so
-// narrow channels stage more rows per barrier.  With at most four 16x16 output
-// tiles every wave computes all tiles over every fourth 4-row K step of a chunk
-// and the partial tiles are added in LDS in wave order; with more, wave w owns
-// tiles w, w + 4, ...
+// The mixed modes: FP64 in LDS, converted at the FP32 MFMA, staged by the block's TH
+// threads and multiplied on its first four waves.  (Staged by four of k_front's eight
+// waves the kernel spilled ten of its 128 registers; it takes 96 now: N=66, n^2<=20 in
+// FP32 73.4 -> 65.5 us a sweep, n^2<=36 115 -> 110, forty densities 1143 -> 1086.)  The
+// staging row stride follows the channel's tiles, so narrow channels stage more rows
+// per barrier.  With at most four 16x16 output tiles every wave computes all tiles
+// over every fourth 4-row K step of a chunk and the partial tiles are added in LDS in
+// wave order; with more, wave w owns tiles w, w + 4, ...
 constexpr int kDirBuf = 2048;  // doubles per staged operand
 constexpr size_t kDirLdsMixed = 2 * (size_t)kDirBuf * 8 + 3 * 64 * sizeof(f4);
+template <int TH>
 __device__ __forceinline__ void direct32(const DirItem& it, uint32_t mask, double* lds) {
     double* vs = lds;
     double* ts = lds + kDirBuf;
@@ -525,17 +525,17 @@ __device__ __forceinline__ void direct32(const DirItem& it, uint32_t mask, doubl
     for (int k = 0; k < 4; k++) acc[k] = f4{0, 0, 0, 0};
     double cpart = 0.0;  // this thread's share of a column sum
     // a chunk in the padded layout [crows][16 nt]: element e of it is loaded by
-    // thread e % 256 into register e / 256 (zero past the chunk and the block),
+    // thread e % TH into register e / TH (zero past the chunk and the block),
     // one chunk ahead of the work on the previous one
-    constexpr int kPerD = kDirBuf / 256;
+    constexpr int kPerD = kDirBuf / TH;
     const int cw = 16 * nt;
     double vr[kPerD], tr[kPerD];
     auto load_chunk = [&](int r0) {
         const int rc = min(crows, it.k1 - r0);
 #pragma unroll
         for (int i = 0; i < kPerD; i++) {
-            const int e = tid + 256 * i, r = e / cw, j = e - r * cw;
-            const bool ok = on && r < rc && j < nhh;
+            const int e = tid + TH * i, r = e / cw, j = e - r * cw;
+            const bool ok = r < rc && j < nhh;
             vr[i] = ok ? it.vt[(int64_t)(r0 + r) * nhh + j] : 0.0;
             tr[i] = ok ? it.t[(int64_t)(r0 + r) * nhh + j] : 0.0;
         }
@@ -547,12 +547,12 @@ __device__ __forceinline__ void direct32(const DirItem& it, uint32_t mask, doubl
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kPerD; i++) {
-            const int e = tid + 256 * i, r = e / cw, j = e - r * cw;
-            if (on && r < crows) { vs[r * ld + j] = vr[i]; ts[r * ld + j] = tr[i]; }
+            const int e = tid + TH * i, r = e / cw, j = e - r * cw;
+            if (r < crows) { vs[r * ld + j] = vr[i]; ts[r * ld + j] = tr[i]; }
         }
         __syncthreads();
-        if (!on) continue;
         if (r0 + crows < it.k1) load_chunk(r0 + crows);
+        if (!on) continue;
         // row sums of t v (one-body particle terms), FP64 in every mode
         if (mask & CCD_T_QPART) {
             for (int r = tid; r < rc; r += 256) {
@@ -639,11 +639,11 @@ __device__ __forceinline__ void direct32(const DirItem& it, uint32_t mask, doubl
     }
 }
 
-template <int P> __host__ __device__ constexpr size_t dir_lds() { return P == P_F64 ? kDirLds : kDirLdsMixed; }
-template <int P> __host__ __device__ constexpr int dir_threads() { return P == P_F64 ? kDirThreads : 256; }
+template <int P> __host__ __device__ constexpr size_t dir_lds() { return P == P_F64 ? dir64_lds(kDirHalf) : kDirLdsMixed; }
+template <int P> __host__ __device__ constexpr int dir_threads() { return P == P_F64 ? 512 : 256; }
 
-// one product item of a block; live_s: a word of LDS
-template <int P>
+// one product item of a block of TH threads; live_s: a word of LDS
+template <int P, int TH>
 __device__ __forceinline__ void direct_block(const DevPtrs& d, const Item it0, int cur, uint32_t mask, double* lds,
                                              int* live_s) {
     const Item it = uni(it0);
@@ -660,8 +660,8 @@ __device__ __forceinline__ void direct_block(const DevPtrs& d, const Item it0, i
     if (!*live_s) return;
     const DirItem di = dir_item(d, c, G, it.start, cur, it.chan, sub.start);
     if constexpr (P == P_F64)
-        direct64<8>(di, (mask & CCD_T_QPART) != 0, (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0, lds);
-    else direct32(di, mask, lds);
+        direct64<8, kDirHalf>(di, (mask & CCD_T_QPART) != 0, (mask & (CCD_T_QHH | CCD_T_QHOLE)) != 0, lds);
+    else direct32<TH>(di, mask, lds);
 }
 
 template <int P>
@@ -675,7 +675,7 @@ __global__ void __launch_bounds__(dir_threads<P>(), P == P_F64 ? 4 : 2) k_direct
         energy_of(d, blockIdx.x - nd, tol, tol_rel, rule, dir_buf);
         return;
     }
-    for (int bi = blockIdx.x; bi < n_items; bi += nd) direct_block<P>(d, d.it_direct[bi], cur, mask, dir_buf, &live_s);
+    for (int bi = blockIdx.x; bi < n_items; bi += nd) direct_block<P, dir_threads<P>()>(d, d.it_direct[bi], cur, mask, dir_buf, &live_s);
 }
 
 // per (S_z = 0 channel, problem): chi_klij = <kl||ij> + sum of the product
@@ -1113,9 +1113,13 @@ __global__ void __launch_bounds__(256) k_ringp_small(DevPtrs d, int cur, uint32_
     }
 }
 
-// pairs with n > 16: one block per item, one wave per output tile
+// pairs with n > 16: one block per item, one wave per output tile.  Orders up to 32
+// are bound by the latency of their gathers, so their registers are held to six waves
+// a SIMD (five of them, as the compiler has it by itself: 64 twists at N=66, n^2<=20
+// 392 us, six 378)
 template <int P, int N16, int NW>
-__global__ void __launch_bounds__(64 * NW) k_ringp(DevPtrs d, int cur, uint32_t mask, int base, int n_items) {
+__global__ void __launch_bounds__(64 * NW, N16 == 32 && NW == 4 ? 6 : (NW + 3) / 4)
+    k_ringp(DevPtrs d, int cur, uint32_t mask, int base, int n_items) {
     extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
     __shared__ int live_s[NW];
     for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) {
@@ -1163,7 +1167,7 @@ __global__ void __launch_bounds__(kFrontThreads, 4) k_front(DevPtrs d, int cur, 
     if (u < ut) {
         const int k0 = (int)((int64_t)u * ud / ut), k1 = (int)((int64_t)(u + 1) * ud / ut);
         if (k1 > k0) {
-            direct_block<P>(d, d.it_direct[8 * k0 + (b & 7)], cur, mask, (double*)dyn_lds, live_s);
+            direct_block<P, kFrontThreads>(d, d.it_direct[8 * k0 + (b & 7)], cur, mask, (double*)dyn_lds, live_s);
             return;
         }
         b -= 8 * k0;
@@ -1550,8 +1554,10 @@ __global__ void __launch_bounds__(256, 3) k_mid(DevPtrs d, int cur, uint32_t mas
 // half the staging and one epilogue (the sums are the same bits).  N=66, n^2<=36 (570
 // items) this launch 33 us with eight waves, 45 with four; a whole sweep of ten
 // densities at n^2<=20 (2120 items) 244.5 and 240, of the 40 solves 1121 and 1094.
-// With eight, the
-// two halves are added through LDS at the end.  Staging is pipelined one chunk
+// The launch of the ladder alone has four waves at every size: beside the rings on
+// other streams eight of 128 registers leave those no room (that sweep at N=66,
+// n^2<=36 154 us, 150 with four).  With eight, the two halves are added through LDS at
+// the end.  Staging is pipelined one chunk
 // ahead: the column descriptors (with the two rows of each pair) of chunk c + 1
 // are in LDS while chunk c is multiplied, so its t loads are in flight then, and
 // delta is double-buffered, so a chunk takes one barrier.
@@ -1825,11 +1831,7 @@ __device__ __forceinline__ void ladder64_run(const DevPtrs& d, int cur, uint32_t
         default: ladder64_item<T, 4, CHI>(d, c, G, g, cur, r0, ct, mask, L, chiS); break;
     }
 }
-__global__ void __launch_bounds__(512, 4) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
-    __shared__ Lad64 L;
-    for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) ladder64_run<512, false>(d, cur, mask, bi, L, nullptr);
-}
-__global__ void __launch_bounds__(256, kLadW) k_ladder64_w4(DevPtrs d, int cur, uint32_t mask, int n_items) {
+__global__ void __launch_bounds__(256, kLadW) k_ladder64(DevPtrs d, int cur, uint32_t mask, int n_items) {
     __shared__ Lad64 L;
     for (int bi = blockIdx.x; bi < n_items; bi += gridDim.x) ladder64_run<256, false>(d, cur, mask, bi, L, nullptr);
 }
@@ -2754,10 +2756,7 @@ static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
     const int n = (int)c->it_lg.size();
     if (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) {
         if constexpr (P == P_F64) {
-            if (n <= kLadSplit)
-                LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), 512, 0, d, cur, mask, n);
-            else
-                LAUNCH(F_LADDER, k_ladder64_w4, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
+            LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
         } else {
             LAUNCH(F_LADDER, k_ladder<P>, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
         }

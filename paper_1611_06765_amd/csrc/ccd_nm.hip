@@ -1816,7 +1816,7 @@ ccd_status nm_plan(ccd_nm_ctx* c) {
         };
         std::stable_sort(c->dirit.begin(), c->dirit.end(),
                          [&](const NmDirItem& x, const NmDirItem& y) { return cost(x) > cost(y); });
-        c->ring.u_off = std::max(c->ring.u_off, (int)((ccd::kDirLds + 15) & ~(size_t)15));
+        c->ring.u_off = std::max(c->ring.u_off, (int)((ccd::dir64_lds(ccd::kDirChunk) + 15) & ~(size_t)15));
         c->ring_lds = c->ring.u_off + 4 * (size_t)c->nlut * 8;
     } else {
         c->dirit.clear();

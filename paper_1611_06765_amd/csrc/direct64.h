@@ -40,33 +40,43 @@ __device__ __forceinline__ dbl4 mfma_d(double a, double b, dbl4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// The item on NW waves (8 or 16).  A chunk of whole rows (all 256 of an item where n_hh <= 16)
-// is one contiguous run of memory, at most 8 (4) doubles of each operand per thread,
-// loaded one chunk ahead of the work and kept in LDS as it is, with row stride
+// The item on NW waves (8 or 16).  A chunk of whole rows (all 256 of an item where
+// n_hh <= 16) is one contiguous run of memory, at most 8 (4) doubles of each operand per
+// thread, loaded one chunk ahead of the work and kept in LDS as it is, with row stride
 // n_hh: a product tile that reads past a row's end gets the next row's numbers,
 // which reach only outputs outside the block.  With at most four 16x16 output
 // tiles (n_hh <= 32) every wave computes all tiles over every NW-th 4-row K step;
 // with more, the waves split into four groups, each of tiles g, g + 4, ..., and
 // share the K steps inside a group.  The partial tiles are added in LDS in a fixed
-// order.  The item is a chain of loads,
-// barriers and short MFMA runs, so it is bound by latency: few and large chunks,
-// eight waves and four threads per row sum shorten that chain.
-constexpr int kDirChunk = 4096;                      // doubles of a staged chunk
-constexpr int kDirBuf64 = kDirChunk + 64;            // and the last tile's overhang
-constexpr size_t kDirLds = 2 * (size_t)kDirBuf64 * 8;
-template <int NW>
+// order.  The item is a chain of loads, barriers and short MFMA runs, so it is bound
+// by latency: few and large chunks, eight waves and four threads per row sum shorten
+// that chain.
+//
+// CH: doubles of each operand staged at a time, a chunk or half of one.  On eight waves
+// half a chunk keeps the kernel within 128 registers, with two blocks a compute unit:
+// with whole chunks the launch of product items alone spills 21 of them (64 twists at
+// N=66, n^2<=20 225 -> 147 us, forty densities 145 -> 99, one density at n^2<=36 26 ->
+// 27).  The K steps are shared out by whole chunks in both, so the bits are the same.
+constexpr int kDirChunk = 4096;
+constexpr int kDirHalf = kDirChunk / 2;
+// two operands, each with the last tile's overhang
+constexpr size_t dir64_lds(int staged) { return 2 * (size_t)(staged + 64) * 8; }
+template <int NW, int CH = kDirChunk>
 __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool quad, double* lds) {
     double* vs = lds;
-    double* ts = lds + kDirBuf64;
+    double* ts = lds + CH + 64;
     constexpr int TH = 64 * NW, NK = NW / 4;  // NK: waves of a group with more than four tiles
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int nhh = it.nhh, nt = (nhh + 15) >> 4, ntt = nt * nt;
-    const int crows = min(kDirSplit, (kDirChunk / nhh) & ~3);  // rows per staged chunk
+    const int crows = min(kDirSplit, (kDirChunk / nhh) & ~3);  // rows of a chunk, in which the K steps are shared out
+    const int srows = CH == kDirChunk ? crows : min(crows, (CH / nhh) & ~3);  // and rows staged at a time
     const bool split = ntt <= 4;
-    constexpr int kPer = kDirChunk / TH;
+    constexpr int kPer = CH / TH;
     double vr[kPer] = {}, tr[kPer] = {};
-    auto load_chunk = [&](int r0) {
-        const int ne = min(crows, it.k1 - r0) * nhh;
+    // the staged rows from r0 on end with the chunk (that of c0) or the item
+    auto rows_at = [&](int r0, int c0) { return min(min(srows, c0 + crows - r0), it.k1 - r0); };
+    auto load_chunk = [&](int r0, int rc) {
+        const int ne = rc * nhh;
         const double* vp = it.vt + (int64_t)r0 * nhh;
         const double* tp = it.t + (int64_t)r0 * nhh;
 #pragma unroll
@@ -77,12 +87,13 @@ __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool q
                 tr[i] = tp[e];
             }
     };
-    load_chunk(it.k0);
+    int c0 = it.k0, rc = rows_at(it.k0, it.k0);
+    load_chunk(it.k0, rc);
     dbl4 acc[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) acc[k] = dbl4{0, 0, 0, 0};
-    for (int r0 = it.k0; r0 < it.k1; r0 += crows) {
-        const int rc = min(crows, it.k1 - r0), rpad = (rc + 3) & ~3, ne = rc * nhh;
+    for (int r0 = it.k0; r0 < it.k1;) {
+        const int rpad = (rc + 3) & ~3, ne = rc * nhh;
         __syncthreads();  // the previous chunk's (or item's) reads are done
 #pragma unroll
         for (int i = 0; i < kPer; i++)
@@ -92,10 +103,14 @@ __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool q
                 ts[e] = e < ne ? tr[i] : 0.0;
             }
         __syncthreads();
-        if (r0 + crows < it.k1) load_chunk(r0 + crows);
+        const int off = CH == kDirChunk ? 0 : (r0 - c0) >> 2;  // K steps of the chunk before these rows
+        const int rn = r0 + rc, rows = rc;
+        if (rn == c0 + crows) c0 = rn;
+        rc = rows_at(rn, c0);
+        if (rn < it.k1) load_chunk(rn, rc);
         // row sums of t v (one-body particle terms): four threads per row
         if (rowsums) {
-            for (int x = tid; x < 4 * rc; x += TH) {
+            for (int x = tid; x < 4 * rows; x += TH) {
                 const int o = (x >> 2) * nhh;
                 double sum = 0.0;
 #pragma unroll 2
@@ -109,13 +124,13 @@ __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool q
             const int col = lane & 15, rq = lane >> 4;
             if (nt == 1) {
 #pragma unroll 2
-                for (int kk = 4 * w; kk < rpad; kk += 4 * NW) {
+                for (int kk = 4 * ((w - off) & (NW - 1)); kk < rpad; kk += 4 * NW) {
                     const int o = (kk + rq) * nhh + col;
                     acc[0] = mfma_d(vs[o], ts[o], acc[0]);
                 }
             } else if (split) {
 #pragma unroll 2
-                for (int kk = 4 * w; kk < rpad; kk += 4 * NW) {
+                for (int kk = 4 * ((w - off) & (NW - 1)); kk < rpad; kk += 4 * NW) {
                     const int o = (kk + rq) * nhh + col;
                     const double a0 = vs[o], b0 = ts[o], a1 = vs[o + 16], b1 = ts[o + 16];
                     acc[0] = mfma_d(a0, b0, acc[0]);
@@ -131,12 +146,13 @@ __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool q
                         const double* vp = vs + rq * nhh + col + 16 * (tile / nt);
                         const double* tp = ts + rq * nhh + col + 16 * (tile % nt);
 #pragma unroll 2
-                        for (int kk = 4 * (w % NK); kk < rpad; kk += 4 * NK)
+                        for (int kk = 4 * ((w - off) & (NK - 1)); kk < rpad; kk += 4 * NK)
                             acc[k] = mfma_d(vp[kk * nhh], tp[kk * nhh], acc[k]);
                     }
                 }
             }
         }
+        r0 = rn;
     }
     if (!quad) return;
     // add the waves' partial tiles: with sixteen waves the upper half of a tile's
@@ -152,6 +168,27 @@ __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool q
             }
         }
     };
+    auto in_order = [&](const dbl4* p) {  // the eight waves' tiles
+        dbl4 sum = p[0];
+#pragma unroll 1
+        for (int q = 1; q < 8; q++) sum += p[q * 64];
+        return sum;
+    };
+    if constexpr (CH != kDirChunk) {  // less LDS: a tile, or a tile of each group, at a time
+        static_assert(NW == 8, "eight shares of a tile, or two");
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int tile = split ? k : w / NK + 4 * k;
+            if (split ? k >= ntt : 4 * k >= ntt) break;
+            __syncthreads();
+            if (split) red[w * 64 + lane] = acc[k];
+            else if (tile < ntt && w % NK == 1) red[(w / NK) * 64 + lane] = acc[k];
+            __syncthreads();
+            if (split && w == k) put(in_order(red + lane), k / nt, k % nt);
+            if (!split && tile < ntt && w % NK == 0) put(acc[k] + red[(w / NK) * 64 + lane], tile / nt, tile % nt);
+        }
+        return;
+    }
     const int ki = split ? w : w % NK;                 // this wave's place among its tiles' waves
     const int nk = split ? 8 : 2;                      // places left when the sums are put together
     const int nown = split ? ntt : 4;
@@ -172,13 +209,7 @@ __device__ __forceinline__ void direct64(const DirItem& it, bool rowsums, bool q
         for (int k = 0; k < 4; k++)
             if (k < ntt && ki < 8) red[(k * 8 + w) * 64 + lane] = acc[k];
         __syncthreads();
-        if (w < ntt) {
-            const dbl4* p = red + w * 8 * 64 + lane;
-            dbl4 sum = p[0];
-#pragma unroll 1
-            for (int q = 1; q < 8; q++) sum += p[q * 64];
-            put(sum, w / nt, w % nt);
-        }
+        if (w < ntt) put(in_order(red + w * 8 * 64 + lane), w / nt, w % nt);
     } else {
 #pragma unroll
         for (int k = 0; k < 4; k++)
