@@ -644,7 +644,7 @@ template <int P> __host__ __device__ constexpr int dir_threads() { return P == P
 
 // one product item of a block of TH threads; live_s: a word of LDS
 template <int P, int TH>
-__device__ __forceinline__ void direct_block(const DevPtrs& d, const Item it0, int cur, uint32_t mask, double* lds,
+__device__ __forceinline__ void direct_block(const DevPtrs& d, const Item& it0, int cur, uint32_t mask, double* lds,
                                              int* live_s) {
     const Item it = uni(it0);
     if (it.chan < 0) return;

@@ -10,16 +10,23 @@
 
 namespace ccd {
 
-// A descriptor that is the same in every lane, moved to scalar registers: a
-// kernel that loops over work items and stores in between cannot load it there
-// by itself, and then carries every field and address in vector registers.
+// A descriptor that is the same in every lane, in scalar registers.  A kernel that
+// loops over work items and stores in between cannot load it there by itself, and
+// then carries every field and address in vector registers.  The tables do not change
+// while a kernel runs, so it is read as constant memory, by scalar loads: a launch of
+// many small items is bound by the chain item -> channel -> group (vector loads of all
+// their words with a readfirstlane each, then scalar ones, us: k_update over a thousand
+// boxes of N=14, n^2<=4 147 -> 115, over 64 twists at N=66, n^2<=20 223 -> 201, their
+// product items 150 -> 141, ladders 262 -> 254).
 template <typename T>
 __device__ __forceinline__ T uni(const T& v) {
     static_assert(sizeof(T) % 4 == 0, "whole words");
     struct Words { int32_t w[sizeof(T) / 4]; };
-    Words x = __builtin_bit_cast(Words, v);
+    using Constant = const __attribute__((address_space(4))) int32_t;
+    Constant* p = (Constant*)(uintptr_t)&v;
+    Words x;
 #pragma unroll
-    for (size_t k = 0; k < sizeof(T) / 4; k++) x.w[k] = __builtin_amdgcn_readfirstlane(x.w[k]);
+    for (size_t k = 0; k < sizeof(T) / 4; k++) x.w[k] = __builtin_amdgcn_readfirstlane(p[k]);
     return __builtin_bit_cast(T, x);
 }
 
