@@ -201,8 +201,9 @@ ccd_status ccd_iterate(ccd_ctx* ctx, const ccd_solver_opts* opts, int32_t* sweep
  * (nullable, CCD_TUNE_LEN entries) receives each slot's best time per pass.
  * It recomputes the sweep's intermediates from the current amplitudes but does
  * not advance the iteration.  A fresh context has all slots 0, with which a
- * sweep runs as three launches on the context's stream; any other table runs
- * the families as launches of their own, the rings on forked streams. */
+ * sweep runs as three launches on the context's stream; any other table, and a
+ * large batch, runs the families as launches of their own, the rings on forked
+ * streams. */
 #define CCD_TUNE_DIRECT      0
 #define CCD_TUNE_DCHI        1
 #define CCD_TUNE_RING_SMALL  2

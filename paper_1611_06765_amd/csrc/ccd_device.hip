@@ -24,7 +24,8 @@
 // stream: k_front (product items, every ring item, the energy step), k_ladder with
 // the one-body items beside it (chi_klij added from the product items' parts where
 // it is used), and k_update (one-body sums per row and column inline).  The
-// launches one by one remain for kernel timing and for chosen launch shapes.
+// launches one by one remain for large batches (one_stream), for kernel timing and
+// for chosen launch shapes.
 // Problems with the same (N, nmax2, twist) form a group that shares the integer
 // tables (states, pair lists, position maps, work lists); the sweep kernels'
 // work items are (item, problem) pairs over them, and the work lists are cut
@@ -167,7 +168,7 @@ struct DevPtrs {
     int32_t* streak;         // per problem: consecutive sweeps that passed the tail test
 };
 
-// lists of a sweep on one stream; kListRing + b: ring items of size bucket b
+// lists of a sweep; kListRing + b: ring items of size bucket b
 enum { kListDirect = 0, kListSmall, kListRing, kListLadder = kListRing + 4, kListOneBody, kListUpdate, kLists };
 struct SweepLists {
     int n[kLists] = {0};
@@ -2047,7 +2048,7 @@ struct ccd_ctx {
     // slot s is cl_items[cl_run[k (P + 1) + s] .. cl_run[k (P + 1) + s + 1])
     std::vector<Item> cl_items;
     std::vector<int32_t> cl_run;
-    SweepLists lists;       // the lists that the three launches take
+    SweepLists lists;       // the lists that a sweep's launches take
     bool live_lists = false;  // ... are those of the problems still iterating (r_lists)
     int64_t n_dpart = 0, n_dcolp = 0;
     int ring_lo[4] = {0}, ring_n[4] = {0};  // big pair items by padded size n16 = 32, 48, 64, 80
@@ -2669,15 +2670,30 @@ static int grid_for(const ccd_ctx* c, int slot, int nb) {
     return std::min(nb, m * 256);
 }
 
-// Whether a sweep runs as three launches on the context's stream: with every
-// launch shape at its default.  It was the faster form at every size and batch
-// measured (see k_front); chosen shapes and kernel timing are those of the
-// separate launches.
-static bool one_stream(const ccd_ctx* c) {
+// every launch shape at its default, and no kernel timing
+static bool default_shapes(const ccd_ctx* c) {
     if (c->timing) return false;
     for (int k = 0; k < CCD_TUNE_LEN; k++)
         if (c->tune[k] != 0) return false;
     return true;
+}
+
+// Whether a sweep runs as three launches on the context's stream (k_front): with the
+// default shapes, unless the pairs of order up to 32 alone are waves for ten rounds of
+// the chip or more.  Their time is the latency of their gathers, which the 24 to 28 waves
+// a compute unit of their own launches cover better than the 16 of k_front, and with so
+// many of them the launches and forks no longer count.  Maps that several problems
+// share stay in the L2, which shortens that latency.  us a sweep by three launches, by
+// separate ones, and the waves in thousands; maps shared: N=38, n^2<=12 forty times 195,
+// 191 (38); N=66, n^2<=36 ten times 912, 947 (51); N=66, n^2<=20 twenty times 501, 506
+// (52), forty 1100, 1031 (103); N=14, n^2<=4 a thousand times 722, 624 (129).  Maps of
+// their own (twists): N=66, n^2<=20 eight 197, 237 (21); N=38, n^2<=12 27 140, 153 (24);
+// twelve boxes of different sizes 289, 292 (29); N=14, n^2<=10 125 181, 167 (42); N=54,
+// n^2<=16 27 307, 290 (44); N=66, n^2<=20 27 782, 773 (70), 64 1934, 1784 (165).
+static bool one_stream(const ccd_ctx* c) {
+    if (!default_shapes(c)) return false;
+    const bool shared = c->probs.size() >= 2 * c->dgroups.size();
+    return c->lists.n[kListSmall] + 4 * (int64_t)c->lists.n[kListRing] <= (shared ? 60000 : 40000);
 }
 
 // the energy step left over from the previous sweep, as its own launch
@@ -2690,7 +2706,7 @@ static ccd_status flush_energy(ccd_ctx* c, const DevPtrs& d) {
 
 template <int P>
 static ccd_status L_direct(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
-    const int n = (int)c->it_direct.size(), ns = (int)c->it_dsum.size();
+    const int n = c->lists.n[kListDirect], ns = (int)c->it_dsum.size();
     if (mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) {
         const int nd = grid_for(c, CCD_TUNE_DIRECT, n);
         if (c->energy_pending && nd > 0) {
@@ -2708,7 +2724,7 @@ static ccd_status L_direct(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask)
 }
 
 static ccd_status L_dchi(ccd_ctx* c, const DevPtrs& d, uint32_t mask) {
-    const int n = (int)c->it_dchi.size();
+    const int n = c->lists.n[kListOneBody];
     LAUNCH(F_DCHI, k_dchi, grid_for(c, CCD_TUNE_DCHI, n), 256, 0, d, mask, n);
     int maxe = 0;
     for (const DevGroup& D : c->dgroups) maxe = std::max(maxe, D.n_rows_all + D.n_cols_all);
@@ -2721,7 +2737,7 @@ static ccd_status L_dchi(ccd_ctx* c, const DevPtrs& d, uint32_t mask) {
 
 template <int P>
 static ccd_status L_ring_small(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
-    const int n = (int)c->it_ring_s.size();
+    const int n = c->lists.n[kListSmall];
     if (mask & (CCD_T_RING | CCD_T_QRING))
         LAUNCH(F_RING_S, k_ringp_small<P>, grid_for(c, CCD_TUNE_RING_SMALL, (n + 3) / 4), 256, 0, d, cur, mask, n);
     return CCD_OK;
@@ -2730,7 +2746,7 @@ static ccd_status L_ring_small(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t m
 // waves per block of each ring size class: slot value 0 -> NWA, 1 -> NWB
 template <int P, int N16, int NWA, int NWB>
 static ccd_status L_ring_class(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask, int k) {
-    const int n = c->ring_n[k], lo = c->ring_lo[k];
+    const int n = c->lists.n[kListRing + k], lo = c->lists.ring_lo[k];
     const int grid = grid_for(c, CCD_TUNE_RING, n);
     if (c->tune[CCD_TUNE_RING_NW32 + k] == 0)
         LAUNCH(F_RING32 + k, (k_ringp<P, N16, NWA>), grid, 64 * NWA, pair_lds<P>(N16), d, cur, mask, lo, n);
@@ -2753,7 +2769,7 @@ static ccd_status L_ring(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask, i
 constexpr int kLadSplit = 1024;  // ladder items above which four waves take one (see ladder64_item)
 template <int P>
 static ccd_status L_ladder(ccd_ctx* c, const DevPtrs& d, int cur, uint32_t mask) {
-    const int n = (int)c->it_lg.size();
+    const int n = c->lists.n[kListLadder];
     if (mask & (CCD_T_PP | CCD_T_HH | CCD_T_QHH)) {
         if constexpr (P == P_F64) {
             LAUNCH(F_LADDER, k_ladder64, grid_for(c, CCD_TUNE_LADDER, n), 256, 0, d, cur, mask, n);
@@ -2850,7 +2866,7 @@ static ccd_status launch_contractions(ccd_ctx* c, const DevPtrs& d, int cur, uin
     ccd_status s = CCD_OK;
     // a pending energy step that no k_direct launch of this sweep can carry
     // runs first, on its own
-    if (c->energy_pending && !((mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) && !c->it_direct.empty())) {
+    if (c->energy_pending && !((mask & (CCD_T_QHH | CCD_T_QHOLE | CCD_T_QPART)) && c->lists.n[kListDirect] > 0)) {
         s = flush_energy(c, d);
         if (s != CCD_OK) return s;
     }
@@ -3268,7 +3284,7 @@ static ccd_status run_phase(ccd_ctx* c, const ccd_solver_opts* o, int prec, doub
             // capture, so the chunks keep the one length there, and the lists)
             if (stops && !graph && !all_done && used < budget) {
                 const int live = (int)std::count_if(act.begin(), act.end(), [](int32_t a) { return a > 0; });
-                if (live < listed && one_stream(c)) {
+                if (live < listed && default_shapes(c)) {
                     if ((st = live_lists(c, act)) != CCD_OK) return st;
                     listed = live;
                 }

@@ -329,3 +329,58 @@ def test_amplitudes_come_back_as_they_were_set(specs):
         for p in range(c.n):
             assert np.array_equal(c.get_amplitudes(p), t[p]), p
         t = [x[::-1].copy() for x in t]
+
+
+def _kernels(run):
+    """names of the kernels that a call launches"""
+    from torch.profiler import ProfilerActivity, profile
+    import torch
+    run()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        run()
+        torch.cuda.synchronize()
+    names = " ".join(e.key for e in p.key_averages())
+    if "k_update" not in names:
+        pytest.skip("the profiler sees no kernels here")
+    return names
+
+
+def _twists(n, nmax2, mesh):
+    return [ccd.problem(n, nmax2, 0.12, twist=t) for t in ccd.twist_mesh(mesh)[0]]
+
+
+@pytest.mark.parametrize("probs,separate", [(lambda: [ccd.problem(66, 36, 0.16)], False),
+                                            (lambda: [ccd.problem(14, 4, 0.1)] * 100, False),
+                                            (lambda: [ccd.problem(14, 4, 0.1)] * 500, True),
+                                            (lambda: _twists(14, 10, 4), False), (lambda: _twists(14, 10, 5), True)],
+                         ids=["one", "100 boxes", "500 boxes", "64 twists", "125 twists"])
+def test_large_batches_run_as_separate_launches(probs, separate):
+    """The three launches of k_front hold fewer waves of small pairs at a time
+    than the pairs' own launches, and lose to them where there are many."""
+    c = _ctx(probs())
+    names = _kernels(lambda: c.iterate(mixing=0.5, max_iter=2))
+    assert ("k_front" in names, "k_ringp_small" in names) == (not separate, separate), names
+
+
+@pytest.mark.parametrize("probs", [lambda: [ccd.problem(14, 4, r) for r in np.linspace(0.03, 0.2, 500)],
+                                   lambda: _twists(14, 10, 5),
+                                   lambda: _twists(38, 12, 4) + [ccd.problem(66, 12, 0.03)]],
+                         ids=["500 boxes", "125 twists", "64 twists and a box"])
+def test_large_batches_equal_their_own_contexts(probs):
+    """Batches that start as separate launches and, as their problems stop, go on
+    with shorter lists and then as three launches: sweeps, energies and
+    amplitudes of problems alone in their contexts, bit for bit."""
+    probs = probs()
+    batch = _ctx(probs)
+    opt = dict(mixing=0.5, tol_rel=2e-8, max_iter=150, stop_rule=1, history=True, check_every=4)
+    r = batch.iterate(**opt)
+    more = batch.iterate(mixing=0.5, max_iter=3, history=True)["history"]
+    assert len(set(r["sweeps"].tolist())) > 1
+    for p in sorted({0, 1, len(probs) // 2, len(probs) - 2, len(probs) - 1, int(np.argmax(r["sweeps"])),
+                     int(np.argmin(r["sweeps"]))}):
+        alone = _ctx([probs[p]])
+        a = alone.iterate(**opt)
+        assert a["sweeps"][0] == r["sweeps"][p]
+        assert np.array_equal(a["history"][0], r["history"][p], equal_nan=True)
+        assert np.array_equal(alone.iterate(mixing=0.5, max_iter=3, history=True)["history"][0], more[p])
+        assert np.array_equal(alone.get_amplitudes(), batch.get_amplitudes(p))
