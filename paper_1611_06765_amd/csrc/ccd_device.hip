@@ -1114,12 +1114,15 @@ __global__ void __launch_bounds__(256) k_ringp_small(DevPtrs d, int cur, uint32_
     }
 }
 
-// pairs with n > 16: one block per item, one wave per output tile.  Orders up to 32
-// are bound by the latency of their gathers, so their registers are held to six waves
-// a SIMD (five of them, as the compiler has it by itself: 64 twists at N=66, n^2<=20
-// 392 us, six 378)
+// pairs with n > 16: one block per item, one wave per output tile.  Bound by the
+// latency of their gathers, so registers are held to the waves a SIMD that LDS allows:
+// at order 32 six (the compiler takes five: 64 twists at N=66, n^2<=20 392 us, six 378),
+// at order 64 on sixteen waves two blocks of them (one in FP32: 463 us, two 414; BF16,
+// with a third matrix, does not get below 72 registers)
 template <int P, int N16, int NW>
-__global__ void __launch_bounds__(64 * NW, N16 == 32 && NW == 4 ? 6 : (NW + 3) / 4)
+constexpr int kRingWaves = N16 == 32 && NW == 4 ? 6 : N16 == 64 && NW == 16 && P != P_BF16 ? 8 : (NW + 3) / 4;
+template <int P, int N16, int NW>
+__global__ void __launch_bounds__(64 * NW, (kRingWaves<P, N16, NW>))
     k_ringp(DevPtrs d, int cur, uint32_t mask, int base, int n_items) {
     extern __shared__ __attribute__((aligned(16))) char dyn_lds[];
     __shared__ int live_s[NW];
