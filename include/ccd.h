@@ -197,8 +197,9 @@ ccd_status ccd_iterate(ccd_ctx* ctx, const ccd_solver_opts* opts, int32_t* sweep
  * the context's own problems: reps passes of the sweep's contractions and
  * update (forked streams included, since a shape that is faster alone can be
  * slower beside the kernels it shares the GPU with), after a warm pass, and
- * keeps a candidate only if it beats the current one by 2%; best_ms
- * (nullable, CCD_TUNE_LEN entries) receives each slot's best time per pass.
+ * keeps a candidate only if it beats the current one by 2%, and the table found
+ * only if it beats that of all zeros by as much; best_ms (nullable,
+ * CCD_TUNE_LEN entries) receives each slot's best time per pass.
  * It recomputes the sweep's intermediates from the current amplitudes but does
  * not advance the iteration.  A fresh context has all slots 0, with which a
  * sweep runs as three launches on the context's stream; any other table, and a

@@ -3047,7 +3047,8 @@ static ccd_status run_sweeps(ccd_ctx* c, int n, double alpha, double tol, double
 // and update can be launched repeatedly without advancing the iteration.
 // Slots are tuned one at a time in pipeline order, each candidate timed over
 // reps such passes after one warm pass; a candidate replaces the incumbent
-// only when it is 2% faster.
+// only when it is 2% faster, and the table found replaces that of all zeros
+// only when it is.
 template <typename F>
 static ccd_status time_family(ccd_ctx* c, F&& launch, int reps, hipEvent_t e0, hipEvent_t e1, double& ms) {
     ccd_status s = launch();
@@ -3102,6 +3103,20 @@ static ccd_status autotune_impl(ccd_ctx* c, int reps, double* best_ms, hipEvent_
         }
         c->tune[sp.slot] = bestv;
         if (best_ms) best_ms[sp.slot] = best;
+    }
+    // The search changes one slot at a time, and any slot but 0 makes separate
+    // launches of the sweep, so from a table with several of them it may never have
+    // come by the default sweep: the table found has to beat that too.
+    int32_t found[CCD_TUNE_LEN];
+    std::memcpy(found, c->tune, sizeof(found));
+    if (!default_shapes(c)) {
+        double ms_found = 0.0, ms_default = 0.0;
+        s = time_family(c, sweep_body, reps, e0, e1, ms_found);
+        if (s != CCD_OK) return s;
+        std::memset(c->tune, 0, sizeof(c->tune));
+        s = time_family(c, sweep_body, reps, e0, e1, ms_default);
+        if (s != CCD_OK) return s;
+        if (ms_found < 0.98 * ms_default) std::memcpy(c->tune, found, sizeof(found));
     }
     return CCD_OK;
 }
