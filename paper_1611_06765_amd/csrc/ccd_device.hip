@@ -2792,18 +2792,34 @@ static ccd_status L_update(ccd_ctx* c, const DevPtrs& d, int cur, double alpha, 
     return CCD_OK;
 }
 
+// LDS of a k_front block: the most that the kinds of items in use need (`of`: small
+// pairs, the size buckets 32, 48, 64, 80; the last one's order if it is kept in fewer rows)
+template <int P>
+constexpr size_t front_lds(bool direct, bool small, const bool (&of)[4], int rows80) {
+    size_t m = 64;
+    auto use = [&](bool on, size_t b) { if (on && b > m) m = b; };
+    use(direct, dir_lds<P>());
+    use(small, 8 * ((pair_lds<P>(16) + 15) & ~(size_t)15));
+    use(of[0], 2 * ((pair_lds<P>(32) + 15) & ~(size_t)15));
+    use(of[1], pair_lds<P>(48));
+    use(of[2], pair_lds<P>(64));
+    use(of[3], pair_lds<P>(80, rows80));
+    return m;
+}
 template <int P>
 static size_t front_lds(const ccd_ctx* c) {
-    size_t m = 0;
-    auto use = [&](bool on, size_t b) { if (on) m = std::max(m, b); };
-    use(!c->it_direct.empty(), dir_lds<P>());
-    use(!c->it_ring_s.empty(), 8 * ((pair_lds<P>(16) + 15) & ~(size_t)15));
-    use(c->ring_n[0] > 0, 2 * ((pair_lds<P>(32) + 15) & ~(size_t)15));
-    use(c->ring_n[1] > 0, pair_lds<P>(48));
-    use(c->ring_n[2] > 0, pair_lds<P>(64));
-    use(c->ring_n[3] > 0, c->max_pair <= kRing80M ? pair_lds<P>(80, kRing80M) : pair_lds<P>(80));
-    return std::max<size_t>(m, 64);
+    const bool of[4] = {c->ring_n[0] > 0, c->ring_n[1] > 0, c->ring_n[2] > 0, c->ring_n[3] > 0};
+    return front_lds<P>(!c->it_direct.empty(), !c->it_ring_s.empty(), of, c->max_pair <= kRing80M ? kRing80M : 0);
 }
+// and of any context
+template <int P>
+constexpr size_t front_lds_max() {
+    const bool all[4] = {true, true, true, true};
+    return front_lds<P>(true, true, all, 0);
+}
+static_assert(front_lds_max<P_F64>() <= 160 * 1024 && front_lds_max<P_F32>() <= 160 * 1024 &&
+                  front_lds_max<P_BF16>() <= 160 * 1024,
+              "a block fits the LDS of a compute unit");
 
 // The contractions of a sweep on the context's stream alone: two launches, the
 // update's being the third.
@@ -2933,7 +2949,7 @@ template <int P>
 static hipError_t set_ring_attrs() {
     hipError_t e;
     if ((e = hipFuncSetAttribute((const void*)k_front<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)std::max(dir_lds<P>(), pair_lds<P>(80)))) != hipSuccess)
+                                 (int)front_lds_max<P>())) != hipSuccess)
         return e;
     if ((e = hipFuncSetAttribute((const void*)k_direct<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)dir_lds<P>())) != hipSuccess)
