@@ -186,3 +186,31 @@ def test_amplitudes_come_back_as_they_were_set(A, n2):
     for x in (t, t[::-1].copy()):
         c.set_amplitudes(x)
         assert np.array_equal(c.get_amplitudes(), x)
+
+
+@pytest.mark.parametrize("n2", [5, 6])
+@pytest.mark.parametrize("mask", [1, 2, 8, 32, 64, 20, 127])
+def test_wide_blocks_with_the_ring_in_pairs(orc, n2, mask):
+    """A = 132: blocks of up to 66 hole pairs, too many for the three-launch sweep,
+    while the cross channels (32 and 48 members) still take the ring over pairs in a
+    launch of its own, beside the generic products: each term alone, the ring's two and
+    all together, two sweeps."""
+    c = _ctx(132, n2, 0.2)
+    info = c.info()
+    assert info["max_hh"] > 64 and info["max_ph"] <= 112
+    o3 = orc.O3(orc.NM(132, n2, 0.2))
+    r = c.iterate(mixing=0.7, max_iter=2, terms=mask)
+    for s in range(2):
+        assert _close(r["history"][s], o3.sweep(0.7, mask)), s
+    assert _amplitudes_match(c, o3)
+
+
+@pytest.mark.parametrize("mask", [107, 127])
+def test_channel_products_for_every_term(orc, mask):
+    """A = 132, n^2 <= 18: cross channels of 120 members, so that every term goes
+    through the generic products; all but the ring's, then all."""
+    c = _ctx(132, 18, 0.2)
+    assert c.info()["max_ph"] > 112
+    o3 = orc.O3(orc.NM(132, 18, 0.2))
+    assert _close(c.iterate(mixing=0.7, max_iter=1, terms=mask)["history"][0], o3.sweep(0.7, mask))
+    assert _amplitudes_match(c, o3)
