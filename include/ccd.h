@@ -282,13 +282,15 @@ ccd_status ccd_measure_ceilings(void* dev_buf, size_t bytes, void* hip_stream, d
  * eq. ccd3 with the terms opts->terms (all eight = CCD_T_ALL), linear mixing
  * opts->mixing, stop when |dE_n - dE_(n-1)| < tol + tol_rel |dE_n| (FP64; the
  * other options are ignored).  A sweep goes through the two-body and one-body
- * intermediates, O(n_h^2 n_p^4 + n_h^3 n_p^3 + n_h^4 n_p^2), in one block for
- * n <= 11: a validation path, not the fast one.  2 <= n <= 48.
+ * intermediates, O(n_h^2 n_p^4 + n_h^3 n_p^3 + n_h^4 n_p^2), in one block where
+ * one compute unit's LDS holds everything (n <= 10, and n = 11 with at most 6
+ * holes): a validation path, not the fast one.  2 <= n <= 48.
  * dev_work: ccd_dense_workspace_size bytes of caller-owned device memory,
  * 256-byte aligned; an area that holds the elements, two sets of amplitudes and
  * one energy per 256 of them is enough for sweeps of O(n_h^4 n_p^4).  Outputs are
  * host pointers (nullable; e_hist: max_iter doubles, NAN past the last sweep).
- * Synchronises hip_stream once per launch of up to 64 sweeps.
+ * Synchronises hip_stream for the MBPT2 energy and then once per 64 sweeps (one
+ * block), per 4 or 1 (larger spaces) or per sweep (the smaller area).
  * Returns CCD_OK, CCD_NOT_CONVERGED, CCD_DIVERGED, CCD_EINVAL (also when a hole
  * is not below every particle in Fock energy), CCD_EHIP. */
 ccd_status ccd_dense_workspace_size(int32_t n, int32_t n_holes, size_t* bytes);

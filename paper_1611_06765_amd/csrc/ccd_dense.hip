@@ -196,10 +196,11 @@ __device__ __forceinline__ double dense_block_sum(double x, double* sh) {
     return s;
 }
 
-// Model spaces whose elements, amplitudes and intermediates fit one compute unit's
-// LDS (n <= 11): the sweeps of a whole solve in one launch of one block, up to
-// max_sweeps of them.  A sweep is a chain of short sums between barriers, where the
-// launches, copy and host read of separate kernels bound it at about 65 us.  The
+// Model spaces whose elements, two sets of amplitudes and intermediates fit 150 KiB of
+// one compute unit's LDS (all of n <= 10, and n = 11 with at most 6 holes): the sweeps
+// of a whole solve in one launch of one block, up to max_sweeps of them.  A sweep is a
+// chain of short sums between barriers, where the launches, copy and host read of
+// separate kernels bound it at about 65 us.  The
 // paper's table, 8 states and 4 particles, a solve of 21 sweeps: 1590 us by a launch
 // of k_dense_sweep and a read each, 271 us here; 10 states: 2560 -> 573 us (separate
 // launches of these phases: 720).  ctl: the energy before (in), the sweeps run and

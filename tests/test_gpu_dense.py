@@ -105,3 +105,22 @@ def test_sweeps_in_one_block_by_launches_and_without_intermediates(orc, n, nh, m
     for s in range(5):
         assert r["history"][s] == pytest.approx(ref[s], rel=RTOL, abs=1e-15), s
         assert hist[s] == pytest.approx(ref[s], rel=RTOL, abs=1e-15), s
+
+
+@pytest.mark.parametrize("n, nh, one_block", [(10, 1, True), (10, 5, True), (11, 1, True), (11, 5, True), (11, 6, True),
+                                              (11, 7, False), (11, 9, False), (11, 10, False), (12, 2, False)])
+def test_one_block_where_its_lds_holds_everything(orc, n, nh, one_block):
+    """The elements, two sets of amplitudes and the intermediates fit 150 KiB up to
+    10 states, and of 11 up to 6 holes: on both sides of that every sweep's energy is
+    the oracle's, of a run past one launch's 64 sweeps too.  A whole run then waits for
+    the stream once per launch of up to 64 sweeps, otherwise every four sweeps."""
+    from test_gpu_batched import _kernels
+    h, v = _random_hamiltonian(n, seed=n + nh)
+    o = orc.O1(h, v, nh)
+    ref = [o.sweep(0.8, ccd.CCD_T_ALL) for _ in range(70)]
+    r = ccd.dense_solve(h, v, nh, mixing=0.8, tol=0.0, max_iter=70)
+    assert r["sweeps"] == 70
+    for s in range(70):
+        assert r["history"][s] == pytest.approx(ref[s], rel=RTOL, abs=1e-15), s
+    names = _kernels(lambda: ccd.dense_solve(h, v, nh, mixing=0.8, tol=0.0, max_iter=2), "k_dense_mbpt2")
+    assert ("k_dense_one" in names, "k_dense_new" in names) == (one_block, not one_block)
