@@ -6,9 +6,10 @@ batch, FP64 contractions, linear mixing 0.5, started from the MBPT2 amplitudes.
 One step = one Jacobi sweep of all ten solves (every term of eq. ccd3).
 
 value = CCD iterations per second, counting one iteration per solve per sweep
-(10 per step).  Inputs are resident in HBM before the timed region.  Per-kernel
-durations come from HIP events recorded by the library on its own stream during
-a second, identical region.  The same measurement at N=66, n^2<=36, rho=0.16
+(10 per step).  Inputs are resident in HBM before the timed region.  The times of
+the sweep's launches, and of every kernel family as a launch of its own, come from
+HIP events recorded by the library on its own stream during a second and a third
+region of the same sweeps.  The same measurement at N=66, n^2<=36, rho=0.16
 (one solve) is reported as c3_fp64.
 
 Beside the throughput line, wall time to convergence of the three other forms
@@ -147,8 +148,8 @@ def ring_class_flops(ccd, ctx, p=0):
 
 
 def kernel_symbol(family, tuning, precision=0):
-    """The kernel a family's single launch runs in the sweep, as rocprofv3
-    names it (the ring variant follows the tuned waves per block)."""
+    """The kernel of a family's launch of its own, as rocprofv3 names it (the ring
+    variant follows the tuned waves per block)."""
     if family == "ladder":
         return "k_ladder64" if precision == 0 else "void k_ladder<%d>" % precision
     if family == "direct":
@@ -159,70 +160,98 @@ def kernel_symbol(family, tuning, precision=0):
     return "void k_ringp<%d, %d, %d>" % (precision, n16, nwb if tuning[6 + k] else nwa)
 
 
+def launch_symbol(launch, precision=0, ladder_items=0):
+    """The kernel of a launch of the three-launch sweep, as rocprofv3 names it
+    (an FP64 ladder launch of more than 1024 items has four waves an item)."""
+    if launch == "front":
+        return "void k_front<%d>" % precision
+    if launch == "mid":
+        return "void k_mid64<%d>" % (256 if ladder_items > 1024 else 512) if precision == 0 else "void k_mid<%d>" % precision
+    return "void k_update<true>"
+
+
+def ladder_items(ccd, ctx, p=0):
+    """Ladder work items of a problem: 128 momentum pairs by 16 columns of an S_z = 0 block."""
+    ch = ctx.export_map(ccd.CCD_MAP_CHANNELS, p).reshape(-1, 6)
+    # a momentum pair {p, K - p} has two rows, at most one of a block (p = K - p) has one
+    return int(sum(-(-((int(npp) + 1) // 2) // 128) * -(-int(nhh) // 16) for *_, sz, nhh, npp in ch if sz == 0))
+
+
+def _timed_kernels(ctx, run, steps, mode):
+    """Milliseconds and launches per step of every family that `run` launches under kernel timing."""
+    ctx.set_timing(mode)
+    ctx.kernel_times(reset=True)
+    run()
+    kt = ctx.kernel_times(reset=True)
+    ctx.set_timing(False)
+    kernels = {k: {"ms_per_step": v[0] / steps, "launches_per_step": v[1] / steps} for k, v in kt.items() if v[1]}
+    total_ms = sum(v["ms_per_step"] for v in kernels.values())
+    for v in kernels.values():
+        v["share"] = v["ms_per_step"] / total_ms
+    return kernels
+
+
 def measure_sweeps(ccd, ctx, steps, warmup, tuning, ceilings, workload, precision=0):
-    """Time `steps` FP64 sweeps of every problem of ctx (inputs resident), then
-    the same sweeps again with the library's per-kernel HIP events on its own
-    stream; per-family times, the useful FP64 flops of each contraction family
-    and the roofline of the longest single launch."""
+    """Time `steps` sweeps of every problem of ctx (inputs resident), then the same
+    sweeps with the library's HIP events around each of their launches, and once
+    more with every kernel family as a launch of its own; times per launch and
+    family, their useful FP64 flops and the roofline of the sweep's longest launch."""
     import torch
     info = ctx.info(0)
     nsolve = ctx.n
+    run = lambda: ctx.iterate(mixing=MIXING, tol=0.0, max_iter=steps, precision=precision)  # noqa: E731
     ctx.iterate(mixing=MIXING, tol=0.0, max_iter=max(1, warmup), precision=precision)
     ctx.set_tuning(tuning)
     ctx.iterate(mixing=MIXING, tol=0.0, max_iter=2, precision=precision)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    ctx.iterate(mixing=MIXING, tol=0.0, max_iter=steps, precision=precision)
+    run()
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
-    ctx.set_timing(True)
-    ctx.kernel_times(reset=True)
     t1 = time.perf_counter()
-    ctx.iterate(mixing=MIXING, tol=0.0, max_iter=steps, precision=precision)
+    launches = _timed_kernels(ctx, run, steps, ccd.CCD_TIME_LAUNCHES)
     torch.cuda.synchronize()
     el_ev = time.perf_counter() - t1
-    kt = ctx.kernel_times(reset=True)
-    ctx.set_timing(False)
-    # per-step time of each kernel family (a family may launch several times a step)
-    kernels = {k: {"ms_per_step": v[0] / steps, "launches_per_step": v[1] / steps}
-               for k, v in kt.items() if v[1]}
-    total_ms = sum(v["ms_per_step"] for v in kernels.values())
-    for v in kernels.values():
-        v["share"] = v["ms_per_step"] / total_ms
+    alone = _timed_kernels(ctx, run, steps, True)
     # useful FP64 flops of one step, per family (unordered pairs, as executed;
     # the pp ladder over momentum pairs); the ring per size class of its pair
     # blocks {Q, -Q}: 4 n m (n + m) for cross channels of n and m pairs
-    ring_cls = ring_class_flops(ccd, ctx)
     fam_flops = {"ladder": nsolve * (info["flops_pp"] + info["flops_hh"] / 2),
                  "direct": nsolve * info["flops_hh"] / 2}
-    for k, f in ring_cls.items():
+    for k, f in ring_class_flops(ccd, ctx).items():
         fam_flops[k] = nsolve * f
-    fam_ms = {k: kernels.get(k, {}).get("ms_per_step", 0.0) for k in fam_flops}
-    for k in fam_ms:
-        if fam_ms[k] > 0:
-            kernels[k]["tflops"] = fam_flops[k] / (fam_ms[k] * 1e-3) / 1e12
-    # dominant kernel: the longest single launch among the contraction kernels
-    per_launch = {k: fam_ms[k] / max(1.0, kernels[k]["launches_per_step"])
-                  for k in fam_ms if fam_ms[k] > 0 and k != "ring_small"}
+    three = "ring_small" not in launches  # the sweep ran as three launches
+    if three:
+        launches = {{"direct": "front", "ladder": "mid"}.get(k, k): v for k, v in launches.items()}
+        lau_flops = {"mid": fam_flops["ladder"], "front": sum(f for k, f in fam_flops.items() if k != "ladder")}
+    else:
+        lau_flops = fam_flops
+    for kernels, flops in ((launches, lau_flops), (alone, fam_flops)):
+        for k, v in kernels.items():
+            if k in flops and v["ms_per_step"] > 0:
+                v["tflops"] = flops[k] / (v["ms_per_step"] * 1e-3) / 1e12
+    # dominant kernel: the longest single launch among the contraction kernels of the timed sweep
+    per_launch = {k: launches[k]["ms_per_step"] / max(1.0, launches[k]["launches_per_step"])
+                  for k in lau_flops if launches.get(k, {}).get("ms_per_step", 0.0) > 0 and k != "ring_small"}
     dom = max(per_launch, key=lambda k: per_launch[k])
-    achieved = fam_flops[dom] / (per_launch[dom] * 1e-3) / 1e12
-    # the contraction precision's published dense peak: FP64 (the direct
-    # product and the one-body terms stay FP64 in every mode), FP32 or BF16
+    achieved = lau_flops[dom] / (per_launch[dom] * 1e-3) / 1e12
+    # the contraction precision's published dense peak: FP64, FP32 or BF16
     peak = PEAK_FP64_TFLOPS if precision == 0 or dom == "direct" else {1: 157.3, 2: 2500.0}[precision]
-    roof = {"kernel": kernel_symbol(dom, tuning, precision), "bound": "mfma",
-            "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+    roof = {"kernel": (launch_symbol(dom, precision, nsolve * ladder_items(ccd, ctx)) if three
+                       else kernel_symbol(dom, tuning, precision)),
+            "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": achieved / peak, "traffic": measured_traffic(dom, workload) if workload else None,
-            "family": dom, "ms_per_launch": per_launch[dom], "flops_per_launch": fam_flops[dom]}
+            "family": dom, "ms_per_launch": per_launch[dom], "flops_per_launch": lau_flops[dom]}
     # the same rate against what this part's matrix cores reach in a resident
     # loop of the instruction the kernel uses (context, not the peak)
     if precision == 0 or dom == "direct":
-        meas = ceilings["fp64_mfma_4x4x4_tflops"] if dom == "ladder" else ceilings["fp64_mfma_16x16x4_tflops"]
+        meas = ceilings["fp64_mfma_4x4x4_tflops" if dom in ("ladder", "mid") else "fp64_mfma_16x16x4_tflops"]
     else:
         meas = ceilings.get("fp32_mfma_16x16x4_tflops" if precision == 1 else "bf16_mfma_16x16x32_tflops", 1.0)
     roof["measured_ceiling"] = meas
     roof["frac_of_measured_ceiling"] = achieved / meas
     return {"elapsed_s": el, "ms_per_step": el * 1e3 / steps, "ms_per_step_with_events": el_ev * 1e3 / steps,
-            "kernels": kernels, "roofline": roof}
+            "kernels": launches, "families_alone": alone, "roofline": roof}
 
 
 def sweep_rate_c3(ccd, stream, steps, warmup, ceilings, precision=0):
@@ -240,7 +269,8 @@ def sweep_rate_c3(ccd, stream, steps, warmup, ceilings, precision=0):
             "ccd_iterations_per_s": 1e3 / m["ms_per_step"], "ms_per_sweep": m["ms_per_step"],
             "tflops": fl / (m["ms_per_step"] * 1e-3) / 1e12,
             "context_tflops_ordered_pair_form": info["flops_ordered"] / (m["ms_per_step"] * 1e-3) / 1e12,
-            "amplitudes": info["n_amplitudes"], "kernels": m["kernels"], "roofline": m["roofline"]}
+            "amplitudes": info["n_amplitudes"], "kernels": m["kernels"], "families_alone": m["families_alone"],
+            "roofline": m["roofline"]}
 
 
 def snm_rate(ccd, stream, steps, warmup):
@@ -663,7 +693,9 @@ def main():
         # ordered-pair GEMM form (4.5x the executed flops at this workload)
         "context_tflops_ordered_pair_form": flops_ord / (ms_step * 1e-3) / 1e12,
         "ms_per_step_with_events": m["ms_per_step_with_events"],
+        # the launches of the timed sweep, then every kernel family as a launch of its own
         "kernels": kernels,
+        "families_alone": m["families_alone"],
         "roofline": roof,
         "ceilings": ceilings,
         "e_corr_last": energies,

@@ -346,13 +346,17 @@ ccd_status ccd_export_tables(const ccd_ctx* ctx, int32_t problem, double* tkin, 
 
 /* Per-kernel GPU timing with HIP events recorded on the context's stream.
  * While enabled every family is a launch of its own, bracketed by two events,
- * and the sweep runs on the context's stream alone, so the times do not overlap;
- * ccd_kernel_times returns, per kernel family, the summed milliseconds and
+ * and the sweep runs on the context's stream alone, so the times do not overlap.
+ * With CCD_TIME_LAUNCHES the launches are those of a solve: of the three-launch
+ * sweep the first (product items, every ring item, the previous sweep's energy)
+ * counts as direct, the second (ladder, one-body sums) as ladder, the third as
+ * update.  ccd_kernel_times returns, per kernel family, the summed milliseconds and
  * launch counts since the last reset.  Families (ccd_kernel_name, in order):
  * init, direct (the chi_klij product items), dsum (their column sums), dchi
  * (one-body sums), ring_small, ring32, ring48, ring64, ring80 (the ring pair
  * blocks by padded order), ladder, update, energy.  ms and launches hold
  * ccd_kernel_families() entries.  Synchronises the stream. */
+#define CCD_TIME_LAUNCHES 2
 ccd_status ccd_set_timing(ccd_ctx* ctx, int32_t enabled);
 int32_t ccd_kernel_families(void);
 const char* ccd_kernel_name(int32_t family);

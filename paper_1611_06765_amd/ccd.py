@@ -37,6 +37,7 @@ CCD_MAP_STATES, CCD_MAP_CHANNELS, CCD_MAP_HH, CCD_MAP_PP, CCD_MAP_PH_CHANNELS, C
 (CCD_TUNE_DIRECT, CCD_TUNE_DCHI, CCD_TUNE_RING_SMALL, CCD_TUNE_RING, CCD_TUNE_LADDER, CCD_TUNE_UPDATE,
  CCD_TUNE_RING_NW32, CCD_TUNE_RING_NW48, CCD_TUNE_RING_NW64, CCD_TUNE_RING_NW80) = range(10)
 CCD_TUNE_LEN = 10
+CCD_TIME_LAUNCHES = 2
 
 
 class ccd_problem(C.Structure):
@@ -407,6 +408,8 @@ class Context:
         return used.astype(bool)
 
     def set_timing(self, on=True):
+        """Per-kernel timing: True times every family as a launch of its own,
+        CCD_TIME_LAUNCHES the launches that a solve makes."""
         _check(_lib.ccd_set_timing(self._h, int(on)), "ccd_set_timing")
 
     def kernel_times(self, reset=False):

@@ -1555,9 +1555,11 @@ __global__ void __launch_bounds__(256, 3) k_mid(DevPtrs d, int cur, uint32_t mas
 // says which), since an item is a serial chain of K steps and one problem has few
 // items; with more of them than two rounds of the chip (kLadSplit) the waves come
 // from other items, and T = 256, four waves with both halves' sums in registers, has
-// half the staging and one epilogue (the sums are the same bits).  N=66, n^2<=36 (570
-// items) this launch 33 us with eight waves, 45 with four; a whole sweep of ten
-// densities at n^2<=20 (2120 items) 244.5 and 240, of the 40 solves 1121 and 1094.
+// half the staging and one epilogue (the sums are the same bits).  us a sweep with
+// eight waves and with four at every size, by items: N=66, n^2<=36 103.4, 114.2 (520),
+// N=66, n^2<=20 four times 108.8, 112.5 (832), five times 135.5, 135.7 (1040), six times
+// 155.0, 152.9 (1248), ten times 238.7, 235.5 (2080); N=14, n^2<=4 fifty times 46.3,
+// 43.9 (1250); the long items of N=66, n^2<=36 three times 252.4, 255.0 (1560).
 // The launch of the ladder alone has four waves at every size: beside the rings on
 // other streams eight of 128 registers leave those no room (that sweep at N=66,
 // n^2<=36 154 us, 150 with four).  With eight, the two halves are added through LDS at
@@ -2069,8 +2071,8 @@ struct ccd_ctx {
     int cur = 0;
     std::vector<double> emp2;
     HostIO io;
-    // timing
-    bool timing = false;
+    // timing: 0 off, 1 every family a launch of its own, CCD_TIME_LAUNCHES the launches as they are
+    int timing = 0;
     std::vector<hipEvent_t> ev_pool;
     std::vector<std::pair<int, int>> pending;  // (family, first event index)
     size_t ev_used = 0;
@@ -2085,7 +2087,7 @@ struct ccd_ctx {
     hipStream_t aux[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev_fork = nullptr, ev_mid = nullptr, ev_join[3] = {nullptr, nullptr, nullptr};
     bool aux_ok = false;
-    // inside run_sweeps (kernel timing off) a sweep's energy step is left to
+    // inside run_sweeps (families not timed) a sweep's energy step is left to
     // the next sweep's k_direct launch, or to the end of the run
     bool defer_energy = false, energy_pending = false;
     double pend_tol = 0.0, pend_tol_rel = 0.0;
@@ -2673,9 +2675,9 @@ static int grid_for(const ccd_ctx* c, int slot, int nb) {
     return std::min(nb, m * 256);
 }
 
-// every launch shape at its default, and no kernel timing
+// every launch shape at its default, and the families not timed one by one
 static bool default_shapes(const ccd_ctx* c) {
-    if (c->timing) return false;
+    if (c->timing == 1) return false;
     for (int k = 0; k < CCD_TUNE_LEN; k++)
         if (c->tune[k] != 0) return false;
     return true;
@@ -2971,7 +2973,7 @@ static ccd_status sweep(ccd_ctx* c, double alpha, double tol, double tol_rel, in
     if (s != CCD_OK) return s;
     s = flush_energy(c, d);  // not left by a k_direct launch of this sweep (none)
     if (s != CCD_OK) return s;
-    if (c->defer_energy && !c->timing) {
+    if (c->defer_energy && c->timing != 1) {
         // the energy step of this sweep rides on the next sweep's k_direct launch
         // (or runs at the end of the run), so that nothing sits between this
         // update and the next sweep's fork
@@ -3569,7 +3571,7 @@ ccd_status ccd_set_timing(ccd_ctx* c, int32_t on) {
     if (!c) { set_error("NULL context"); return CCD_EINVAL; }
     ccd_status s = harvest(c);
     if (s != CCD_OK) return s;
-    c->timing = on != 0;
+    c->timing = on == CCD_TIME_LAUNCHES ? CCD_TIME_LAUNCHES : on != 0;
     return CCD_OK;
 }
 
@@ -3582,8 +3584,8 @@ ccd_status ccd_autotune(ccd_ctx* c, int32_t precision, int32_t reps, double* bes
     }
     ccd_status s = harvest(c);
     if (s != CCD_OK) return s;
-    const bool timing = c->timing;
-    c->timing = false;
+    const int timing = c->timing;
+    c->timing = 0;
     const int P = (int)c->probs.size();
     std::vector<int32_t> ones(P, 1);
     HIP_TRY(hipMemcpyAsync(c->ws + c->r_active.off, ones.data(), P * 4, hipMemcpyHostToDevice, c->stream));

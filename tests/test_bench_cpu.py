@@ -39,3 +39,22 @@ def test_traffic_records_match_the_current_source():
     assert t is not None and 50e6 < t < 500e6
     assert bench.measured_traffic("ladder", bench.TRAFFIC_C3) is not None
     assert bench.measured_traffic("ring64", "no such workload") is None
+
+
+def test_launch_symbols():
+    """The three launches of a sweep; the FP64 ladder's by its number of items (N=66:
+    520 at n^2<=36, ten times 208 at n^2<=20)."""
+    assert bench.launch_symbol("front") == "void k_front<0>" and bench.launch_symbol("front", 2) == "void k_front<2>"
+    items = [bench.ladder_items(ccd, ccd.Context([ccd.problem(66, n2, 0.16)])) for n2 in (36, 20)]
+    assert items == [520, 208]
+    assert bench.launch_symbol("mid", 0, items[0]) == "void k_mid64<512>"
+    assert bench.launch_symbol("mid", 0, 10 * items[1]) == "void k_mid64<256>"
+    assert bench.launch_symbol("mid", 1, 10 * items[1]) == "void k_mid<1>"
+    assert bench.launch_symbol("update") == "void k_update<true>"
+
+
+def test_traffic_records_of_the_timed_launches():
+    """The launches whose roofline the sweep lines report have records too."""
+    for workload in (bench.TRAFFIC_C2, bench.TRAFFIC_C3):
+        t = bench.measured_traffic("front", workload)
+        assert t is not None and 50e6 < t < 1e9, workload

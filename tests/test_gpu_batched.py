@@ -395,3 +395,23 @@ def test_autotuner_finds_the_default_shapes_from_any_table():
         c.set_tuning(table)
         found, _ = c.autotune(ccd.CCD_PREC_FP64, reps=1)
         assert not found.any(), (table, found)
+
+
+@pytest.mark.parametrize("probs", [[(66, 36, 0.16)], [(66, 20, 0.05), (66, 20, 0.16)]], ids=["one", "two"])
+def test_timing_of_the_launches_that_a_solve_makes(probs):
+    """CCD_TIME_LAUNCHES leaves the three-launch sweep as it is (the energy of a run's
+    last sweep is one launch more); True makes every family a launch of its own.
+    Both change no bits."""
+    probs = [ccd.problem(*x) for x in probs]
+    want = _ctx(probs).iterate(mixing=0.5, max_iter=6, history=True, check_every=6)["history"]
+    for mode, names in ((ccd.CCD_TIME_LAUNCHES, {"direct": 6, "ladder": 6, "update": 6, "energy": 1}),
+                        (True, {"direct": 6, "dsum": 6, "ring_small": 6, "ring32": 6, "ring48": 6, "ring64": 6,
+                                "ladder": 6, "update": 6, "energy": 6})):
+        c = _ctx(probs)
+        c.set_timing(mode)
+        got = c.iterate(mixing=0.5, max_iter=6, history=True, check_every=6)["history"]
+        kt = {k: v[1] for k, v in c.kernel_times().items() if v[1]}
+        assert np.array_equal(got, want)
+        assert {k: kt.get(k, 0) for k in names} == names, kt
+        assert ("ring64" in kt) == (mode is True)
+        assert all(ms > 0 for ms, n in c.kernel_times().values() if n)
