@@ -1138,13 +1138,13 @@ __global__ void __launch_bounds__(64 * NW, (kRingWaves<P, N16, NW>))
 // launches, and forking them over streams costs an event record, a wait and two
 // queue crossings each (about 10 us apiece); side by side in one grid they need
 // none of it.  512 threads: a product item, a pair of order 48 .. 80 on eight
-// waves, two pairs of order 32 on four each, or eight small pairs on one each; 128
-// registers and at most 80 KB of LDS (except for pairs beyond order 68), two
-// blocks per compute unit.  A sweep in us, nine launches over four streams -> these
+// waves, two pairs of order 32 on four each, or eight small pairs on one each; at most
+// 128 registers, none spilled (114 in FP64, 96 in the mixed modes), and 80 KB of LDS
+// (except for pairs beyond order 68), two blocks per compute unit.  A sweep in us, nine launches over four streams -> these
 // three with the ladder and update below: N=14, n^2<=4 94 -> 19; N=54, n^2<=36 112 ->
-// 84; N=66, n^2<=20 115 -> 52 (five densities 165 -> 137, ten 248 -> 240); N=66,
-// n^2<=36 141 -> 104 (three 288 -> 256).  This launch takes 61 us at N=66, n^2<=36 and
-// 162 us for the ten densities, where the ring's gathers and scattered stores (521 MB)
+// 84; N=66, n^2<=20 111 -> 51 (ten densities 249 -> 236); N=66, n^2<=36 141 -> 103
+// (three 288 -> 253, BF16 132 -> 112).  This launch takes 60 us at N=66, n^2<=36 and
+// 159 us for the ten densities, where the ring's gathers and scattered stores (518 MB)
 // bound it.
 constexpr int kFrontThreads = 512;
 struct Front {
@@ -1951,8 +1951,8 @@ __device__ __forceinline__ void update_item(const DevPtrs& d, const Item ig, int
 // have done.  The lists of all problems keep each XCD on one problem's data, so when
 // a problem stops its XCD idles; these spread each problem over all of them.  Ten
 // densities at N=66, n^2<=20, of which 10 / 5 / 1 iterate: a sweep 245 / 235 / 199 us
-// from the lists of all problems, 266 / 145 / 52 from these (hence the former until
-// the first one stops); the solve to its last sweep (42) 10.6 -> 9.1 ms.
+// from the lists of all problems, 266 / 145 / 52 from these (kernels that took 245 us
+// with all ten; hence the former until the first one stops); the solve to its last sweep (42) 10.6 -> 9.1 ms.
 constexpr int kCarry = 32;
 __global__ void __launch_bounds__(256) k_live_lists(DevPtrs d, int P, int cur) {
     __shared__ double sh[4];

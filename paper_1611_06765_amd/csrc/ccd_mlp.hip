@@ -30,12 +30,13 @@ namespace {
 // A wave takes NT tiles of four amplitudes (16 rows) at a time, the next ones'
 // features on their way meanwhile, and a grid of the blocks that fit the chip at
 // once (three per compute unit in BF16 at 168 registers, two in FP32) strides over
-// them, so W2 is staged once per resident block.  1 037 776 amplitudes in BF16: 275
-// us with one tile at a time, 2048 blocks and the accumulators in the AGPR file, 225
-// with two, 208 with 168 plain registers (four tiles 226, at two waves a SIMD; the
-// next step's layer 1 issued among this step's MFMAs 220); 60 000 amplitudes 33 ->
-// 22 us.  FP32 1336 -> 1205.  What is left is the activations' VALU time beside the
-// MFMAs (see tile_predict).
+// them, so W2 is staged once per resident block.  1 037 776 amplitudes in BF16: 240 ->
+// 176 us a call in a long row of calls, 257 -> 192 waited for.  By step, in bursts of
+// five calls after an idle GPU, which take longer: 275 us with one tile at a time, 2048
+// blocks and the accumulators in the AGPR file, 225 with two, 208 with 168 plain
+// registers (four tiles 226, at two waves a SIMD; the next step's layer 1 issued among
+// this step's MFMAs 220); 60 000 amplitudes 33 -> 22 us.  FP32 1336 -> 1220.  What is
+// left is the activations' VALU time beside the MFMAs (see tile_predict).
 template <bool BF16, int NT>
 __global__ void __launch_bounds__(256, 3) k_mlp_fwd(const float* __restrict__ P, const float* __restrict__ feat,
                                                  int64_t n, float* __restrict__ y) {
