@@ -102,6 +102,7 @@ struct HostIO {
 
     // bytes (a multiple of 8) from device memory to dst, after all work on s
     hipError_t download(void* dst, const void* src, size_t bytes, hipStream_t s) {
+        if (bytes == 0) return hipStreamSynchronize(s);  // (a problem may have no amplitudes)
         std::lock_guard<std::mutex> lock(mu);
         if (stage_of(bytes) > stage_cap || !here()) {
             hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);

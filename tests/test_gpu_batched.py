@@ -331,6 +331,22 @@ def test_amplitudes_come_back_as_they_were_set(specs):
         t = [x[::-1].copy() for x in t]
 
 
+def test_a_problem_without_amplitudes():
+    """Eight neutrons in the 14 states of n^2 <= 1 under a general twist have no pair
+    excitation that keeps the momentum: nothing to copy, no correlation, and no
+    difference to the problem beside it."""
+    c = _ctx([ccd.problem(14, 4, 0.16), ccd.problem(8, 1, 0.1, twist=(0.1, 0.2, 0.3))])
+    one = _ctx([ccd.problem(14, 4, 0.16)])
+    assert c.info(1)["n_amplitudes"] == 0
+    for ctx in (c, one):
+        ctx.iterate(mixing=0.5, tol=1e-8, max_iter=60, check_every=4)
+    assert c.get_amplitudes(1).size == 0
+    c.set_amplitudes(np.empty(0), 1)
+    assert c.energy(1)[1:] == (0.0, 0.0)
+    assert np.array_equal(c.get_amplitudes(0), one.get_amplitudes(0))
+    assert c.energy(0) == one.energy(0)
+
+
 def _kernels(run, always="k_update"):
     """names of the kernels that a call launches (always: one that it launches in any case)"""
     from torch.profiler import ProfilerActivity, profile
